@@ -1013,7 +1013,7 @@ int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
                   dim3(EXP_THREADS), 0, s, E);
         CasProbeTriArgs Q;
         Q.I = L.I; Q.n = hi - lo; Q.T = run_index(L.Trun); Q.Tk = L.Tk; Q.seed = p.seed; Q.total = total;
-        MJ_LAUNCHM(prof, "k_cas_probe_tri", k_cas_probe_tri, dim3(grid_for(hi - lo, 256, 16384)), dim3(256), 0, s, Q);
+        MJ_LAUNCHM(prof, "k_cas_probe_tri", k_cas_probe_tri, dim3(grid_for(hi - lo, 256, 2048)), dim3(256), 0, s, Q);
     }
     // an intermediate of another size than the plan's: the total is all ones
     MJ_LAUNCHM(prof, "k_poison_u64", k_poison_u64, dim3(1), dim3(64), 0, s, total, (uint64_t)1, L.err);
@@ -1670,7 +1670,7 @@ int mj_join2_size(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, uint64_t* out,
         P.dir = L.dir; P.pool = L.pool;
         P.bkt_seed = bseed; P.bkt_bits = bits; P.slot_seed = sseed;
         P.total = total;
-        MJ_LAUNCH(&ctx->prof, "k_probe_sum", k_probe_sum, dim3(grid_for(S->n, 256, 4096)), dim3(256), 0, s, P);
+        MJ_LAUNCH(&ctx->prof, "k_probe_sum", k_probe_sum, dim3(grid_for(S->n, 1024, 2048)), dim3(256), 0, s, P);
     }
     unsigned long long h = 0;
     MJ_HIP(hipMemcpyAsync(&h, total, 8, hipMemcpyDeviceToHost, s));
@@ -1705,6 +1705,27 @@ static PlanLayout plan_layout(void* ws, int kind, uint64_t n_r, uint64_t n_s, ui
     return L;
 }
 
+// mx[to[i]] = the largest value of column col[i] of src[i] over all i < jobs
+// (0 for an empty column); synchronous, through `stats` on the device
+static int column_maxima(Prof* prof, const mj_rel* const* src, const int* col, const int* to, int jobs, uint32_t* stats,
+                         uint32_t* mx, int nmx, hipStream_t s) {
+    MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, stats, (uint64_t)nmx, 0u);
+    ColMaxArgs C{};
+    uint64_t most = 0;
+    for (int i = 0; i < jobs; ++i) {
+        C.col[i] = col[i] ? src[i]->col1 : src[i]->col0;
+        C.stride[i] = src[i]->stride;
+        C.n[i] = src[i]->n;
+        C.out[i] = stats + to[i];
+        most = std::max(most, src[i]->n);
+    }
+    C.per = grid_for(most, 1024, 512);
+    MJ_LAUNCH(prof, "k_col_max", k_col_max, dim3(C.per * (uint32_t)jobs), dim3(256), 0, s, C);
+    MJ_HIP(hipMemcpyAsync(mx, stats, 4 * (size_t)nmx, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipStreamSynchronize(s));
+    return MJ_OK;
+}
+
 uint64_t mj_plan_workspace(int kind, uint64_t n_r, uint64_t n_s, uint64_t n_t) {
     return plan_layout(nullptr, kind, n_r, n_s, n_t).bytes;
 }
@@ -1732,31 +1753,19 @@ int mj_plan(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, const mj_re
 
     if (kind == MJ_LINEAR) {
         if (a_domain == 0 && R->n) return MJ_ERR_KEY_RANGE;
+        // one pass for the largest A of R and, where the tables may be
+        // direct-indexed, the largest B of R and S and the largest C of S and T
+        const bool dense = !(requests & MJ_PLAN_NO_DENSE) && R->n && S->n && T->n;
+        uint32_t mx[3] = {0, 0, 0};
         if (R->n) {
-            uint32_t* d = PL.stats;
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, d, (uint64_t)1, 0u);
-            MJ_LAUNCH(&ctx->prof, "k_col_max", k_col_max, dim3(grid_for(R->n, 256, 2048)), dim3(256), 0, s,
-                               R->col0, R->stride, R->n, d);
-            uint32_t mx = 0;
-            MJ_HIP(hipMemcpyAsync(&mx, d, 4, hipMemcpyDeviceToHost, s));
-            MJ_HIP(hipStreamSynchronize(s));
-            if (mx >= a_domain) return MJ_ERR_KEY_RANGE;
+            const mj_rel* src[COL_MAX_JOBS] = {R, R, S, S, T};
+            const int col[COL_MAX_JOBS] = {0, 1, 0, 1, 0}, to[COL_MAX_JOBS] = {0, 1, 1, 2, 2};
+            if ((st = column_maxima(&ctx->prof, src, col, to, dense ? COL_MAX_JOBS : 1, PL.stats, mx, 3, s))) return st;
+            if (mx[0] >= a_domain) return MJ_ERR_KEY_RANGE;
         }
         // B and C in small dense domains: direct-indexed tables
-        if (!(requests & MJ_PLAN_NO_DENSE) && R->n && S->n && T->n) {
-            uint32_t* d = PL.stats;
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, d, (uint64_t)2, 0u);
-            const mj_rel* src[4] = {R, S, S, T};
-            const int col[4] = {1, 0, 1, 0};          // B of R and S, C of S and T
-            for (int i = 0; i < 4; ++i) {
-                const mj_rel& r = *src[i];
-                MJ_LAUNCH(&ctx->prof, "k_col_max", k_col_max, dim3(grid_for(r.n, 256, 2048)), dim3(256), 0, s,
-                          col[i] ? r.col1 : r.col0, r.stride, r.n, d + (i < 2 ? 0 : 1));
-            }
-            uint32_t mx[2] = {0, 0};
-            MJ_HIP(hipMemcpyAsync(mx, d, 8, hipMemcpyDeviceToHost, s));
-            MJ_HIP(hipStreamSynchronize(s));
-            const uint64_t bdom = uint64_t(mx[0]) + 1, cdom = uint64_t(mx[1]) + 1;
+        if (dense) {
+            const uint64_t bdom = uint64_t(mx[1]) + 1, cdom = uint64_t(mx[2]) + 1;
             if (dense_ok(bdom, std::max(R->n, S->n)) && dense_ok(cdom, std::max(S->n, T->n))) {
                 p.b_domain = (uint32_t)bdom;
                 p.c_domain = (uint32_t)cdom;
@@ -1781,13 +1790,9 @@ int mj_plan(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, const mj_re
         // direct index (the relation is symmetric: its first column holds
         // every id)
         if (yes && !(requests & MJ_PLAN_NO_DENSE)) {
-            uint32_t* d = PL.stats;
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, d, (uint64_t)1, 0u);
-            MJ_LAUNCH(&ctx->prof, "k_col_max", k_col_max, dim3(grid_for(R->n, 256, 2048)), dim3(256), 0, s,
-                      R->col0, R->stride, R->n, d);
             uint32_t mx = 0;
-            MJ_HIP(hipMemcpyAsync(&mx, d, 4, hipMemcpyDeviceToHost, s));
-            MJ_HIP(hipStreamSynchronize(s));
+            const int zero = 0;
+            if ((st = column_maxima(&ctx->prof, &R, &zero, &zero, 1, PL.stats, &mx, 1, s))) return st;
             const uint64_t vdom = uint64_t(mx) + 1;
             uint32_t bits, shift;
             if (dense_ok(vdom, R->n) && key_ranges(R->n, (uint32_t)vdom, bits, shift)) {

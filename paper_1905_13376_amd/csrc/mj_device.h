@@ -66,6 +66,23 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 }
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) { return wave_sum_u64(v); }
+
+// *total += the workgroup's sum of v, with one atomic.  A kernel that ends
+// in a sum adds it per workgroup, not per wave: the L2 serves atomics on one
+// address one after another (about 12 ns each), so 65,536 waves' adds alone
+// took 0.8 ms.  All threads of the workgroup call it; blockDim.x is a
+// multiple of the wave, at most 1024.
+__device__ __forceinline__ void block_add_u64(unsigned long long* total, unsigned long long v) {
+    __shared__ unsigned long long part[1024 / WAVE];
+    v = wave_sum_u64(v);
+    if (lane_id() == 0) part[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long s = 0;
+        for (uint32_t w = 0; w < blockDim.x / WAVE; ++w) s += part[w];
+        if (s) atomicAdd(total, s);
+    }
+}
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return wave_sum_u32(v); }
 
 // Heavy keys: the active lanes of the wave whose key equals the first

@@ -963,8 +963,16 @@ __global__ void k_deg_hist(const DirEntry* dir, const uint2* pool, uint32_t nbkt
 __global__ void k_sketch_features(const uint32_t* hist3, uint64_t nr, uint64_t ns, uint64_t nt,
                                   int kind, float* f);
 
-// max of a column (key-range check)
-__global__ void k_col_max(const uint32_t* col, int64_t stride, uint64_t n, uint32_t* out);
+// max of columns (key-range checks): *out[j] = max(*out[j], values of column j)
+constexpr int COL_MAX_JOBS = 5;
+struct ColMaxArgs {
+    const uint32_t* col[COL_MAX_JOBS];
+    int64_t stride[COL_MAX_JOBS];
+    uint64_t n[COL_MAX_JOBS];
+    uint32_t* out[COL_MAX_JOBS];
+    uint32_t per;                // workgroups per column
+};
+__global__ void k_col_max(ColMaxArgs A);
 struct FillU64Args { unsigned long long* p; uint64_t n; unsigned long long v; };   // p[0..n) = v
 struct FillU32Args { uint32_t* p; uint64_t n; uint32_t v; };
 MJ_KERNEL_DECL(k_fill_u64, FillU64Args);

@@ -505,8 +505,7 @@ MJ_KERNEL(k_cas_probe_tri, 256, CasProbeTriArgs) {
         if (!run_lookup(A.T, mix32(iv.y, A.seed), ts, y)) continue;
         acc += count_low(A.Tk, ts, ts + y, mix32(iv.x, A.seed));
     }
-    acc = wave_sum_u64(acc);
-    if (lane_id() == 0 && acc) atomicAdd(A.total, acc);
+    block_add_u64(A.total, acc);
 }
 
 }  // namespace mj
