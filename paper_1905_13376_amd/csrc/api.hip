@@ -642,8 +642,8 @@ struct RunBuf {
 };
 
 struct PassBuf {                      // work queues of one pass of the cyclic join
-    uint32_t* light;
-    uint32_t* ctr;                    // nlight, light_next, nheavy_groups, heavy_next
+    uint2* light;
+    uint32_t* ctr;                    // [TRI_CTR_WORDS] nlight, -, nheavy_groups, heavy_next; the light queues
     uint32_t* heavy_group;
     uint32_t* heavy_items;
     unsigned long long* heavy_off;
@@ -682,8 +682,8 @@ void take_runs(Bump& B, RunBuf& X, uint64_t n, bool with_dir) {
 }
 
 void take_pass(Bump& B, PassBuf& P, uint64_t n_stage, uint64_t n_s) {
-    P.light = B.take<uint32_t>(std::max<uint64_t>(n_s, 1));
-    P.ctr = B.take<uint32_t>(4);
+    P.light = B.take<uint2>(std::max<uint64_t>(n_s, 1));
+    P.ctr = B.take<uint32_t>(TRI_CTR_WORDS);
     P.n_heavy_cap = (uint32_t)(n_stage / (TRI_LIGHT_X + 1) + n_s / (TRI_LIGHT_S + 1) + 2);
     P.heavy_group = B.take<uint32_t>(P.n_heavy_cap);
     P.heavy_items = B.take<uint32_t>(P.n_heavy_cap);
@@ -934,7 +934,7 @@ int tri_prepare(Prof* prof, int num_cu, const mj_rel& R, const mj_rel& S, const 
     // work queues of the two passes
     for (int q = 0; q < 2; ++q) {
         const PassBuf& P = L.P[q];
-        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, P.ctr, (uint64_t)4, 0u);
+        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(256), 0, s, P.ctr, (uint64_t)TRI_CTR_WORDS, 0u);
         MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(grid_for(P.n_heavy_cap, 256, 4096)), dim3(256), 0, s,
                   P.heavy_items, (uint64_t)P.n_heavy_cap, 0u);
         TriClassifyArgs C;
@@ -943,7 +943,7 @@ int tri_prepare(Prof* prof, int num_cu, const mj_rel& R, const mj_rel& S, const 
         C.share = 1u << p.log2_share;
         C.nlight = P.ctr + 0; C.light = P.light;
         C.nheavy_groups = P.ctr + 2; C.heavy_group = P.heavy_group; C.heavy_items = P.heavy_items;
-        MJ_LAUNCHM(prof, "k_tri_classify", k_tri_classify, dim3(grid_for(S.n, 256, 16384)), dim3(256), 0, s, C);
+        MJ_LAUNCHM(prof, "k_tri_classify", k_tri_classify, dim3(grid_for(S.n, 1024, 4096)), dim3(256), 0, s, C);
         if ((st = launch_scan_u32(prof, P.heavy_items, P.n_heavy_cap, L.partial, P.heavy_off, s))) return st;
     }
     return MJ_OK;
@@ -962,7 +962,7 @@ TriJoinArgs tri_join_args(const TriLayout& L, const mj_plan_t& p, unsigned long 
     J.Grpl = pass == 0 ? L.Sl : L.Sl2;
     J.Itrl = pass == 0 ? L.Tl : L.Rl;
     J.strict = pass == 0 ? 1u : 0u;
-    J.nlight = P.ctr + 0; J.light = P.light; J.light_next = P.ctr + 1;
+    J.nlight = P.ctr + 0; J.light = P.light; J.light_next = P.ctr + TRI_QUEUE_PAD;
     J.heavy_group = P.heavy_group; J.heavy_off = P.heavy_off; J.n_heavy_cap = P.n_heavy_cap;
     J.heavy_next = P.ctr + 3; J.share = 1u << p.log2_share; J.total = out;
     return J;
@@ -1494,7 +1494,7 @@ int run_oriented(Prof* prof, int num_cu, const mj_rel& Erel, const mj_plan_t& p,
     std::swap(Rp.col0, Rp.col1);
     if (q.n_s) {
         if ((st = tri_prepare(prof, num_cu, Rp, Sp, Sp, q, L, out, s))) return st;
-        const uint32_t persistent = (uint32_t)num_cu * 8;
+        const uint32_t persistent = (uint32_t)num_cu * TRI_LIGHT_PER_CU;
         for (int pass = 0; pass < 2; ++pass) {
             TriJoinArgs J = tri_join_args(L, q, out, pass);
             MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
@@ -2050,7 +2050,7 @@ int mj_triangle3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_r
     MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, out, (uint64_t)1, 0ull);
     if (R->n == 0 || S->n == 0 || T->n == 0) return MJ_OK;
     if ((st = tri_prepare(prof, ctx->num_cu, *R, *S, *T, p, L, out, s))) return st;
-    const uint32_t persistent = (uint32_t)ctx->num_cu * 8;
+    const uint32_t persistent = (uint32_t)ctx->num_cu * TRI_LIGHT_PER_CU;
     for (int pass = 0; pass < 2; ++pass) {
         TriJoinArgs J = tri_join_args(L, p, out, pass);
         MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
@@ -2555,6 +2555,10 @@ static size_t cell_table_bytes(size_t nl, size_t nt) {
     return align256(nl * sizeof(LinearCellArgs)) + align256((nl + 1) * 4) + align256(nt * sizeof(TriJoinArgs));
 }
 
+// Work counters of the batch's cell stage: the heavy items' one (on a line of
+// its own), then the light queues'.
+static size_t batch_counter_bytes() { return align256(4 * TRI_QUEUE_PAD * (1 + TRI_QUEUES)); }
+
 uint64_t mj_batch_workspace(const mj_batch_item* items, int n) {
     if (!items || n < 0) return 0;
     // the joins' work recorded with a stand-in context and workspace, for
@@ -2567,7 +2571,7 @@ uint64_t mj_batch_workspace(const mj_batch_item* items, int n) {
     const size_t tables = schedule_batch(B.chains, steps);
     const size_t nn = (size_t)n;
     return B.join_bytes + align256(tables) + cell_table_bytes(nn, 2 * nn) + 2 * align256((2 * nn + 1) * 8) +
-           align256(16) + 256;
+           batch_counter_bytes() + 256;
 }
 
 int mj_batch_count(mj_ctx* ctx, const mj_batch_item* items, int n, void* ws, uint64_t ws_bytes,
@@ -2606,7 +2610,7 @@ int mj_batch_count(mj_ctx* ctx, const mj_batch_item* items, int n, void* ws, uin
     const size_t stage = align256(tables) + cell_table_bytes(nl, nt);
     const size_t want = std::max<size_t>(stage, 256);
     char* dev = base + B.join_bytes;
-    if (uint64_t(B.join_bytes) + stage + 2 * align256((nt + 1) * 8) + align256(16) > ws_bytes)
+    if (uint64_t(B.join_bytes) + stage + 2 * align256((nt + 1) * 8) + batch_counter_bytes() > ws_bytes)
         return MJ_ERR_WORKSPACE;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     MJ_HIP(hipStreamIsCapturing(s, &cap));
@@ -2689,9 +2693,10 @@ int mj_batch_count(mj_ctx* ctx, const mj_batch_item* items, int n, void* ws, uin
         T.njoins = (uint32_t)nt;
         T.light_base = reinterpret_cast<unsigned long long*>(q);
         T.heavy_base = reinterpret_cast<unsigned long long*>(q + align256((nt + 1) * 8));
-        T.next = reinterpret_cast<unsigned long long*>(q + 2 * align256((nt + 1) * 8));
+        T.heavy_next = reinterpret_cast<unsigned long long*>(q + 2 * align256((nt + 1) * 8));
+        T.light_next = reinterpret_cast<uint32_t*>(T.heavy_next) + TRI_QUEUE_PAD;
         MJ_LAUNCH(prof, "k_tri_batch_prefix", k_tri_batch_prefix, dim3(1), dim3(64), 0, s, T);
-        MJ_LAUNCH(prof, "k_tri_light_batch", k_tri_light_batch, dim3((uint32_t)ctx->num_cu * 8),
+        MJ_LAUNCH(prof, "k_tri_light_batch", k_tri_light_batch, dim3((uint32_t)ctx->num_cu * TRI_LIGHT_PER_CU),
                   dim3(TRI_THREADS), 0, s, T);
         MJ_LAUNCH(prof, "k_tri_heavy_batch", k_tri_heavy_batch, dim3((uint32_t)ctx->num_cu * 2),
                   dim3(TRI_HEAVY_THREADS), 0, s, T);

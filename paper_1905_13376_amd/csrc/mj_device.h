@@ -59,6 +59,15 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
+// v of lane j, j the same in every lane (a scalar read on the device).
+__device__ __forceinline__ uint32_t wave_read(uint32_t v, int j) {
+#if __has_builtin(__builtin_amdgcn_readlane)
+    return __builtin_amdgcn_readlane(v, j);
+#else
+    return __shfl(v, j, WAVE);
+#endif
+}
+
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);

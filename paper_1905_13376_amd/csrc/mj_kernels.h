@@ -607,14 +607,18 @@ MJ_KERNEL_DECL(k_rs_scan1, RsScan1Args);
 // --------------------------------------------------------------- triangle
 constexpr int TRI_THREADS = 256;           // light kernel: one table per wave
 constexpr int TRI_HEAVY_THREADS = 1024;    // heavy kernel: one table per workgroup
-constexpr uint32_t TRI_LIGHT_X = 512;      // R list length handled by one wave
-constexpr uint32_t TRI_LIGHT_CAP = 1024;   // its LDS table (load <= 1/2)
-static_assert(TRI_LIGHT_CAP <= 65536, "used slots are kept as 16-bit numbers");
+constexpr uint32_t TRI_LIGHT_X = 512;      // staged list length handled by one wave
+constexpr uint32_t TRI_LIGHT_DIR_BITS = 10;// its directory
 constexpr uint32_t TRI_LIGHT_S = 4096;     // S group size handled by one wave
-constexpr uint32_t TRI_HEAVY_X = 4096;     // R slice handled by one workgroup
-constexpr uint32_t TRI_HEAVY_CAP = 8192;
-constexpr uint32_t TRI_HEAVY_S = 2048;     // S tuples per heavy item (chunks of 64 per wave)
-constexpr uint32_t TRI_SHORT_LIST = 16;    // heavy: lists walked by one lane
+constexpr uint32_t TRI_HEAVY_X = 4096;     // slice of a staged list handled by one workgroup
+constexpr uint32_t TRI_HEAVY_DIR_BITS = 13;// its directory
+static_assert(TRI_HEAVY_X <= 65535, "directory entries hold 16-bit positions and counts");
+constexpr uint32_t TRI_HEAVY_S = 4096;     // S tuples per heavy item (chunks of at most 64 per wave)
+constexpr uint32_t TRI_SHORT_LIST = 16;    // lists walked by one lane
+constexpr uint32_t TRI_LIGHT_PER_CU = 6;   // workgroups of the light kernel that fit a CU (LDS)
+constexpr uint32_t TRI_QUEUES = 32;        // queues of light items, their counters
+constexpr uint32_t TRI_QUEUE_PAD = 32;     // this many words apart (a cache line each)
+constexpr uint32_t TRI_CTR_WORDS = TRI_QUEUE_PAD * (1 + TRI_QUEUES);   // nlight, -, nheavy_groups, heavy_next; queues
 
 struct RunIndex {                          // runs of equal high words of sorted keys
     const uint32_t* run_key;               // [nruns]
@@ -744,8 +748,6 @@ struct TriKeyArgs {
     unsigned long long* out;
 };
 
-struct TriHeavyItem { uint32_t r0, r1, s0, s1; };
-
 // One pass of the cyclic join: the lists of the staged relation (R per B,
 // or T per C) are loaded into LDS one group at a time; the groups come from
 // S sorted by that same attribute; each s of a group whose iterated list
@@ -757,7 +759,7 @@ struct TriClassifyArgs {
     RunIndex Stg, Grp;
     uint32_t share;
     uint32_t* nlight;
-    uint32_t* light;
+    uint2* light;                          // (group, run of its staged list)
     uint32_t* nheavy_groups;
     uint32_t* heavy_group;
     uint32_t* heavy_items;
@@ -770,8 +772,8 @@ struct TriJoinArgs {
     const uint32_t* Itrl;                  // iterated relations
     uint32_t strict;
     const uint32_t* nlight;
-    const uint32_t* light;
-    uint32_t* light_next;
+    const uint2* light;
+    uint32_t* light_next;                  // [TRI_QUEUES] counters, TRI_QUEUE_PAD words apart
     const uint32_t* heavy_group;
     const unsigned long long* heavy_off;
     uint32_t n_heavy_cap;
@@ -794,7 +796,8 @@ struct TriBatchArgs {
     uint32_t njoins;
     unsigned long long* light_base;      // [njoins + 1]
     unsigned long long* heavy_base;      // [njoins + 1]
-    unsigned long long* next;            // [2] work counters
+    uint32_t* light_next;                // [TRI_QUEUES] counters, TRI_QUEUE_PAD words apart
+    unsigned long long* heavy_next;
 };
 __global__ void k_tri_light_batch(TriBatchArgs B);
 __global__ void k_tri_heavy_batch(TriBatchArgs B);

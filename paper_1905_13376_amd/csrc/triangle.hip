@@ -90,53 +90,110 @@ __device__ __forceinline__ void heavy_shape(uint32_t x, uint32_t gn, uint32_t sh
     nsr = (gn + TRI_HEAVY_S - 1) / TRI_HEAVY_S;
 }
 
+// Light groups are appended with one atomic per workgroup and round of 1024
+// groups (one per wave serialised on the counter's address: 370 us a pass at
+// scale 22); each entry carries its group's run and its staged list's run.
 MJ_KERNEL(k_tri_classify, 256, TriClassifyArgs) {
+    __shared__ uint32_t wsum[256 / WAVE];
+    __shared__ uint32_t sbase;
     const uint64_t ng = *A.Grp.nruns;
-    for (uint64_t g = vg.bid * (uint64_t)blockDim.x + threadIdx.x; g < ng;
-         g += (uint64_t)vg.nblk * blockDim.x) {
-        uint32_t rs, x;
-        if (!run_lookup(A.Stg, A.Grp.run_key[g], rs, x)) continue;
-        const uint32_t gn = A.Grp.run_start[g + 1] - A.Grp.run_start[g];
-        if (x <= TRI_LIGHT_X && gn <= TRI_LIGHT_S) {
-            const uint32_t q = atomicAdd(A.nlight, 1u);
-            A.light[q] = (uint32_t)g;
-        } else {
-            uint32_t nsl, nsr;
-            heavy_shape(x, gn, A.share, nsl, nsr);
-            const uint32_t h = atomicAdd(A.nheavy_groups, 1u);
-            A.heavy_group[h] = (uint32_t)g;
-            A.heavy_items[h] = nsl * nsr;
+    const int lane = lane_id(), w = threadIdx.x / WAVE;
+    for (uint64_t g0 = vg.bid * 1024ull; g0 < ng; g0 += vg.nblk * 1024ull) {   // uniform over the block
+        uint32_t key[4], run[4], nlight = 0;
+        bool live[4], light[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t g = g0 + u * 256 + threadIdx.x;
+            live[u] = g < ng;
+            key[u] = live[u] ? A.Grp.run_key[g] : 0u;
         }
+        run_find4(A.Stg, key, live, run);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            light[u] = false;
+            if (run[u] == 0xFFFFFFFFu) continue;
+            const uint64_t g = g0 + u * 256 + threadIdx.x;
+            const uint32_t x = A.Stg.run_start[run[u] + 1] - A.Stg.run_start[run[u]];
+            const uint32_t gn = A.Grp.run_start[g + 1] - A.Grp.run_start[g];
+            light[u] = x <= TRI_LIGHT_X && gn <= TRI_LIGHT_S;
+            if (light[u]) {
+                ++nlight;
+            } else {
+                uint32_t nsl, nsr;
+                heavy_shape(x, gn, A.share, nsl, nsr);
+                const uint32_t h = atomicAdd(A.nheavy_groups, 1u);
+                A.heavy_group[h] = (uint32_t)g;
+                A.heavy_items[h] = nsl * nsr;
+            }
+        }
+        uint32_t v = nlight;                          // inclusive prefix over the wave
+#pragma unroll
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const uint32_t y = __shfl_up(v, off, WAVE);
+            if (lane >= off) v += y;
+        }
+        if (lane == WAVE - 1) wsum[w] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t t = 0;
+            for (int q = 0; q < 256 / WAVE; ++q) t += wsum[q];
+            sbase = t ? atomicAdd(A.nlight, t) : 0u;
+        }
+        __syncthreads();
+        uint32_t at = sbase + v - nlight;
+        for (int q = 0; q < w; ++q) at += wsum[q];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (light[u]) A.light[at++] = make_uint2((uint32_t)(g0 + u * 256 + threadIdx.x), run[u]);
+        __syncthreads();                              // wsum and sbase are used again
     }
 }
 
-// ------------------------------------------------------------ LDS A-tables
-// open addressing on m(a); value = multiplicity; m(a) = 0xFFFFFFFF in `spec`
-__device__ __forceinline__ void atab_add(uint32_t* keys, uint32_t* vals, uint32_t mask,
-                                         uint32_t* spec, uint32_t a) {
-    if (a == EMPTY_KEY) { atomicAdd(spec, 1u); return; }
-    uint32_t s = a & mask;                    // m(a) is already a hash
-    while (true) {
-        const uint32_t cur = keys[s];
-        if (cur == a) { atomicAdd(&vals[s], 1u); return; }
-        if (cur == EMPTY_KEY) {
-            const uint32_t old = atomicCAS(&keys[s], EMPTY_KEY, a);
-            if (old == EMPTY_KEY || old == a) { atomicAdd(&vals[s], 1u); return; }
-        }
-        s = (s + 1u) & mask;
-    }
+// ------------------------------------------------------------- staged lists
+// A staged list lies in LDS as it is, sorted by m(a), with a directory over
+// the range of its values: the values are hashes, so equal-width buckets
+// hold about the same number each.  dir[bucket] = first position | number of
+// entries << 16.  A lookup reads one directory word and then the bucket's
+// entries (one or two), where an open-addressing table at half load made a
+// wave walk as far as the longest of its 64 probe chains; equal entries are
+// counted, so duplicates need no multiplicity field.  Bound by the lookups'
+// instructions (about one vector instruction an entry), then by the latency
+// of the streamed lists.  Oriented join of the R-MAT graph of scale 22
+// (1.3e10 streamed entries): light kernel 48.1 -> 12.5 ms, heavy kernel
+// 24.2 -> 13.7 ms against hash tables and one list in flight.
+struct ListTab {
+    uint32_t* dir;
+    uint32_t* val;
+    uint32_t base, top, shift;        // bucket of a: (a - base) >> shift, when a - base <= top
+};
+
+__device__ __forceinline__ void listtab_index(const ListTab& T, uint32_t q) {
+    const uint32_t b = (T.val[q] - T.base) >> T.shift;
+    const bool head = q == 0 || ((T.val[q - 1] - T.base) >> T.shift) != b;
+    atomicAdd(&T.dir[b], 0x10000u + (head ? q : 0u));
 }
 
-__device__ __forceinline__ uint32_t atab_get(const uint32_t* keys, const uint32_t* vals,
-                                             uint32_t mask, uint32_t spec, uint32_t a) {
-    if (a == EMPTY_KEY) return spec;
-    uint32_t s = a & mask;
-    while (true) {
-        const uint32_t cur = keys[s];
-        if (cur == a) return vals[s];
-        if (cur == EMPTY_KEY) return 0u;
-        s = (s + 1u) & mask;
+// entries equal to the four keys; every read of a step is in flight together
+__device__ __forceinline__ uint32_t listtab_count4(const ListTab& T, const uint32_t (&key)[4], const bool (&live)[4]) {
+    uint32_t p[4], n[4], acc = 0, most = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t o = key[u] - T.base;
+        const bool in = live[u] && o <= T.top;
+        const uint32_t d = T.dir[in ? o >> T.shift : 0u];
+        p[u] = d & 0xFFFFu;
+        n[u] = in ? d >> 16 : 0u;
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) most = max(most, n[u]);
+    for (uint32_t i = 0; i < most; ++i) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = T.val[i < n[u] ? p[u] + i : 0u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += i < n[u] && v[u] == key[u] ? 1u : 0u;
+    }
+    return acc;
 }
 
 // number of entries of sorted low words keys[lo, hi) equal to a
@@ -155,204 +212,207 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 // ------------------------------------------------------- streaming lists
-// First index in [lo, hi) of a sorted list whose value is not below v (or,
-// with `upper`, above v).  The wave probes 64 evenly spaced pivots per
-// round, so a list of n entries takes about log_65(n) rounds of independent
-// loads instead of log_2(n) dependent ones.
-__device__ __forceinline__ uint32_t wave_bound(const uint32_t* keys, uint32_t lo, uint32_t hi,
-                                               uint32_t v, bool upper) {
-    const int lane = lane_id();
-    while (hi - lo > WAVE) {
-        const uint32_t n = hi - lo;                   // n >= 65: pivots strictly increase
-        const uint32_t p = lo + (uint32_t)((uint64_t)n * (lane + 1) / (WAVE + 1));
-        const uint32_t k = keys[p];
-        const int below = __popcll(__ballot(upper ? k <= v : k < v));
-        const uint32_t nlo = below == 0 ? lo : lo + (uint32_t)((uint64_t)n * below / (WAVE + 1)) + 1;
-        const uint32_t nhi = below == WAVE ? hi : lo + (uint32_t)((uint64_t)n * (below + 1) / (WAVE + 1));
-        lo = nlo;
-        hi = nhi;
-    }
-    bool in = false;
-    if (lo + lane < hi) {
-        const uint32_t k = keys[lo + lane];
-        in = upper ? k <= v : k < v;
-    }
-    return lo + (uint32_t)__popcll(__ballot(in));
-}
-
 // One chunk of up to 64 S tuples of a group, lane j holding tuple si (when
-// `valid`): each tuple's iterated list streams past the staged table.  Lists
-// of at most TRI_SHORT_LIST entries are walked by their own lane; longer
-// ones one after another by the whole wave (64 consecutive entries per load,
-// UNROLL loads in flight per lane), so a long list is read with coalesced
-// loads.  When the staged list is a slice, only the part of a long list in
-// the slice's A range [alo, ahi] is read (a short list's other entries find
-// nothing).  Returns the lane's partial sum.
+// `valid`): each tuple's iterated list streams past the staged one.  When the
+// staged list is a slice, only the part of a list in the slice's range of A
+// is read: every lane finds its own list's part by two binary searches, 64
+// lists at a time.  Lists of at most TRI_SHORT_LIST entries are then walked
+// by their own lane; longer ones by the whole wave in pieces of 64
+// consecutive entries, four pieces (of one list or of several) per step, the
+// next step's pieces loaded before the present ones are looked up.  Returns
+// the lane's partial sum.
 __device__ __forceinline__ unsigned long long stream_chunk(const TriJoinArgs& A, uint32_t si, bool valid,
-                                                           uint32_t x, const uint32_t* keys,
-                                                           const uint32_t* vals, uint32_t mask, uint32_t sp,
-                                                           bool sliced, uint32_t alo, uint32_t ahi) {
+                                                           uint32_t x, const ListTab& T, bool sliced) {
     const int lane = lane_id();
-    constexpr int UNROLL = 4;
     unsigned long long acc = 0;
     uint32_t ts = 0, y = 0;
     if (!(valid && run_lookup(A.Itr, A.Grpl[si], ts, y)) ||
         (A.strict ? y >= x : y > x))                  // the other pass owns this s
         y = 0;
-    if (y <= TRI_SHORT_LIST) {                        // UNROLL loads in flight, then their probes
+    if (sliced && y > 4) {                            // the part inside [base, base + top]
+        uint32_t l = ts, h = ts + y, l2 = ts, h2 = ts + y;
+        const uint32_t last = T.base + T.top;
+        while (l < h || l2 < h2) {
+            const uint32_t m = (l + h) >> 1, m2 = (l2 + h2) >> 1;
+            const uint32_t k = l < h ? A.Itrl[m] : 0u, k2 = l2 < h2 ? A.Itrl[m2] : 0u;
+            if (l < h) { if (k < T.base) l = m + 1; else h = m; }
+            if (l2 < h2) { if (k2 <= last) l2 = m2 + 1; else h2 = m2; }
+        }
+        ts = l;
+        y = l2 - l;
+    }
+    if (y > 0 && y <= TRI_SHORT_LIST) {
         const uint32_t te = ts + y;
-        for (uint32_t t0 = ts; t0 < te; t0 += UNROLL) {
-            uint32_t key[UNROLL];
+        uint32_t key[4];
+        bool live[4];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) key[u] = t0 + u < te ? A.Itrl[t0 + u] : 0u;
+        for (int u = 0; u < 4; ++u) {
+            live[u] = ts + u < te;
+            key[u] = live[u] ? A.Itrl[ts + u] : 0u;
+        }
+        for (uint32_t t0 = ts; t0 < te; t0 += 4) {
+            uint32_t nkey[4];
+            bool nlive[4];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                if (t0 + u < te) acc += atab_get(keys, vals, mask, sp, key[u]);
+            for (int u = 0; u < 4; ++u) {
+                nlive[u] = t0 + 4 + u < te;
+                nkey[u] = nlive[u] ? A.Itrl[t0 + 4 + u] : 0u;
+            }
+            acc += listtab_count4(T, key, live);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { key[u] = nkey[u]; live[u] = nlive[u]; }
         }
     }
     unsigned long long longm = __ballot(y > TRI_SHORT_LIST);
-    while (longm) {                                   // wave-uniform
-        const int j = __ffsll((long long)longm) - 1;
-        longm &= longm - 1;
-        uint32_t l = __shfl(ts, j, WAVE);
-        uint32_t l2 = l + __shfl(y, j, WAVE);
-        if (sliced && l2 - l > WAVE) {                // the part inside [alo, ahi]
-            l = wave_bound(A.Itrl, l, l2, alo, false);
-            l2 = wave_bound(A.Itrl, l, l2, ahi, true);
-        }
-        for (uint32_t t0 = l; t0 < l2; t0 += UNROLL * WAVE) {
-            uint32_t key[UNROLL];
+    uint32_t t = 0, te = 0;                           // the list being cut into pieces (wave-uniform)
+    uint32_t key[4];
+    bool live[4];
+    auto fetch = [&](uint32_t (&k)[4], bool (&lv)[4]) -> bool {
+        bool any = false;
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                const uint32_t t = t0 + u * WAVE + lane;
-                key[u] = t < l2 ? A.Itrl[t] : 0u;
+        for (int u = 0; u < 4; ++u) {
+            if (t >= te && longm) {
+                const int j = __ffsll((long long)longm) - 1;
+                longm &= longm - 1;
+                t = wave_read(ts, j);
+                te = t + wave_read(y, j);
             }
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                if (t0 + u * WAVE + lane < l2) acc += atab_get(keys, vals, mask, sp, key[u]);
+            lv[u] = t + lane < te;
+            k[u] = lv[u] ? A.Itrl[t + lane] : 0u;
+            any = any || t < te;
+            t = min(t + WAVE, te);
         }
+        return any;                                   // wave-uniform
+    };
+    bool more = fetch(key, live);
+    while (more) {
+        uint32_t nkey[4];
+        bool nlive[4];
+        more = fetch(nkey, nlive);
+        acc += listtab_count4(T, key, live);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { key[u] = nkey[u]; live[u] = nlive[u]; }
     }
     return acc;
 }
 
 // ------------------------------------------------------------- light groups
-// One wave, one S group: R's list of b into the wave's LDS table, then every
-// s(b,c) of the group streams T's list of c past it, 64 tuples at a time
-// (stream_chunk).  Returns the lane's sum.
-struct WaveTable {
-    uint32_t* keys;
-    uint32_t* vals;
-    uint16_t* used;                   // slots taken (< TRI_LIGHT_CAP), for the clean-up
-    uint32_t* nused;
-    uint32_t* spec;
-};
-
-__device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint32_t g, const WaveTable& W) {
+// One wave, one S group: the staged list (at most TRI_LIGHT_X entries) and its
+// directory in 6 KB of LDS per wave, so six workgroups (24 waves) fit a CU;
+// then every s(b,c) of the group streams its iterated list past it, 64 tuples
+// at a time (stream_chunk).  Returns the lane's sum.
+__device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint2 item, const ListTab& T) {
     const int lane = lane_id();
-    const uint32_t mask = TRI_LIGHT_CAP - 1;
-    const uint32_t gkey = A.Grp.run_key[g];
-    const uint32_t gs = A.Grp.run_start[g], ge = A.Grp.run_start[g + 1];
-    uint32_t rs = 0, x = 0;
-    run_lookup(A.Stg, gkey, rs, x);
-    for (uint32_t q = lane; q < x; q += WAVE) {
-        const uint32_t a = A.Stgl[rs + q];
-        if (a == EMPTY_KEY) { atomicAdd(W.spec, 1u); continue; }
-        uint32_t s = a & mask;
-        while (true) {
-            const uint32_t cur = W.keys[s];
-            if (cur == a) { atomicAdd(&W.vals[s], 1u); break; }
-            if (cur == EMPTY_KEY) {
-                const uint32_t old = atomicCAS(&W.keys[s], EMPTY_KEY, a);
-                if (old == EMPTY_KEY) { W.used[atomicAdd(W.nused, 1u)] = (uint16_t)s; atomicAdd(&W.vals[s], 1u); break; }
-                if (old == a) { atomicAdd(&W.vals[s], 1u); break; }
-            }
-            s = (s + 1u) & mask;
-        }
-    }
+    const uint32_t gs = A.Grp.run_start[item.x], ge = A.Grp.run_start[item.x + 1];
+    const uint32_t rs = A.Stg.run_start[item.y], x = A.Stg.run_start[item.y + 1] - rs;
+    for (uint32_t q = lane; q < x; q += WAVE) T.val[q] = A.Stgl[rs + q];
     wave_fence();
-    const uint32_t spec = *W.spec;
+    for (uint32_t q = lane; q < x; q += WAVE) listtab_index(T, q);
+    wave_fence();
     unsigned long long acc = 0;
-    for (uint32_t c0 = gs; c0 < ge; c0 += WAVE)
-        acc += stream_chunk(A, c0 + lane, c0 + lane < ge, x, W.keys, W.vals, mask, spec, false, 0u, 0u);
+    for (uint32_t c0 = gs; c0 < ge; c0 += WAVE) acc += stream_chunk(A, c0 + lane, c0 + lane < ge, x, T, false);
     wave_fence();
-    const uint32_t nu = *W.nused;
-    for (uint32_t q = lane; q < nu; q += WAVE) { const uint32_t s = W.used[q]; W.keys[s] = EMPTY_KEY; W.vals[s] = 0; }
-    wave_fence();
-    if (lane == 0) { *W.spec = 0; *W.nused = 0; }
+    for (uint32_t q = lane; q < x; q += WAVE) T.dir[T.val[q] >> T.shift] = 0;
     wave_fence();
     return acc;
 }
 
 #define TRI_LIGHT_SETUP                                                              \
     constexpr int NW = TRI_THREADS / WAVE;                                           \
-    __shared__ uint32_t tkeys[NW][TRI_LIGHT_CAP];                                    \
-    __shared__ uint32_t tvals[NW][TRI_LIGHT_CAP];                                    \
-    __shared__ uint16_t tused[NW][TRI_LIGHT_X];                                      \
-    __shared__ uint32_t tnused[NW];                                                  \
-    __shared__ uint32_t tspec[NW];                                                   \
+    __shared__ uint32_t tdir[NW][1u << TRI_LIGHT_DIR_BITS];                          \
+    __shared__ uint32_t tval[NW][TRI_LIGHT_X];                                       \
     const int w = threadIdx.x / WAVE, lane = lane_id();                              \
-    WaveTable W{tkeys[w], tvals[w], tused[w], &tnused[w], &tspec[w]};                \
-    for (uint32_t s = lane; s < TRI_LIGHT_CAP; s += WAVE) { W.keys[s] = EMPTY_KEY; W.vals[s] = 0; } \
-    if (lane == 0) { *W.spec = 0; *W.nused = 0; }                                    \
+    const ListTab T{tdir[w], tval[w], 0u, 0xFFFFFFFFu, 32 - TRI_LIGHT_DIR_BITS};     \
+    for (uint32_t s = lane; s < (1u << TRI_LIGHT_DIR_BITS); s += WAVE) T.dir[s] = 0; \
     wave_fence();
 
-// Light items are taken a run at a time: the queue counter is one address,
-// whose atomics are served one after another (about 12 ns each), so one
-// atomic per item bounded the kernel once items numbered in the millions,
-// and each atomic's round trip also stalls the wave that waits for it.  A
-// run is a quarter of a wave's fair share, at least TRI_LIGHT_GRAB_MIN and
-// at most TRI_LIGHT_GRAB items.
+// Light items are taken a run at a time from TRI_QUEUES queues, each over its
+// own part of the items with its counter on a cache line of its own: atomics
+// on one address are served one after another (about 12 ns each), and one
+// counter for all waves took 0.3 ms a pass for the 65,536 groups of a join of
+// 10^6 tuples.  A run is a quarter of a wave's fair share, at least
+// TRI_LIGHT_GRAB_MIN and at most TRI_LIGHT_GRAB items.  A workgroup starts at
+// queue (its number modulo TRI_QUEUES); when that one is empty each lane looks
+// at one counter, and the wave goes on with the next queue that has items.
 constexpr uint32_t TRI_LIGHT_GRAB = 16, TRI_LIGHT_GRAB_MIN = 4;
+static_assert(TRI_QUEUES <= WAVE, "one lane looks at one queue");
 
 __device__ __forceinline__ uint32_t light_grab(unsigned long long nitems, unsigned long long waves) {
     const unsigned long long g = nitems / (4ull * waves);
     return (uint32_t)(g < TRI_LIGHT_GRAB_MIN ? TRI_LIGHT_GRAB_MIN : (g > TRI_LIGHT_GRAB ? TRI_LIGHT_GRAB : g));
 }
 
+// The next run [it, end) of items for the wave, or false when every queue is
+// empty.  `q` is the wave's present queue; `counters` hold the items already
+// taken of each queue (they may run past its length).  Wave-uniform.
+__device__ __forceinline__ bool light_next_run(uint32_t* counters, unsigned long long nitems, uint32_t grab,
+                                               uint32_t& q, unsigned long long& it, unsigned long long& end) {
+    const uint32_t lane = lane_id();
+    while (true) {
+        const unsigned long long q0 = nitems * q / TRI_QUEUES, q1 = nitems * (q + 1) / TRI_QUEUES;
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(&counters[q * TRI_QUEUE_PAD], grab);
+        t = __shfl(t, 0, WAVE);
+        if (q0 + t < q1) {
+            it = q0 + t;
+            end = min(it + grab, q1);
+            return true;
+        }
+        // lane l looks at queue q + l (a stale value only costs one more try)
+        const uint32_t o = (q + lane) % TRI_QUEUES;
+        const unsigned long long len = nitems * (o + 1) / TRI_QUEUES - nitems * o / TRI_QUEUES;
+        const uint32_t taken = lane == 0 ? 0xFFFFFFFFu : *(volatile uint32_t*)&counters[o * TRI_QUEUE_PAD];
+        const unsigned long long has = __ballot(lane < TRI_QUEUES && lane > 0 && taken < len);
+        if (has == 0) return false;
+        q = (q + (uint32_t)__ffsll((long long)has) - 1u) % TRI_QUEUES;
+    }
+}
+
 MJ_KERNEL(k_tri_light, TRI_THREADS, TriJoinArgs) {
     TRI_LIGHT_SETUP
+    (void)lane;
     const uint32_t nitems = *A.nlight;
     const uint32_t grab = light_grab(nitems, (unsigned long long)vg.nblk * (TRI_THREADS / WAVE));
-    unsigned long long acc = 0;
-    uint32_t it = 0, end = 0;
+    unsigned long long acc = 0, it = 0, end = 0;
+    uint32_t q = vg.bid % TRI_QUEUES;
     while (true) {
-        if (it >= end) {                              // wave-uniform
-            uint32_t t = 0;
-            if (lane == 0) t = atomicAdd(A.light_next, grab);
-            it = __shfl(t, 0, WAVE);
-            if (it >= nitems) break;
-            end = min(it + grab, nitems);
-        }
-        acc += tri_light_group(A, A.light[it], W);
+        if (it >= end && !light_next_run(A.light_next, nitems, grab, q, it, end)) break;   // wave-uniform
+        acc += tri_light_group(A, A.light[it], T);
         ++it;
     }
-    acc = wave_sum_u64(acc);
-    if (lane == 0 && acc) atomicAdd(A.total, acc);
+    block_add_u64(A.total, acc);
 }
 
 // ------------------------------------------------------------- heavy groups
-// One workgroup, one item: a slice of a hub's R list into LDS, then the
-// item's S tuples, one wave per S tuple, stream the slice's A range of T's list.
+// One workgroup, one item: a slice of a hub's staged list (at most TRI_HEAVY_X
+// entries) and its directory in 48 KB of LDS, then the item's S tuples stream
+// their iterated lists past it (only the part in the slice's range of A when
+// the staged list is sliced).  Waves take chunks of S tuples from a workgroup
+// counter.
 struct BlockTable {
-    uint32_t* keys;
-    uint32_t* vals;
-    uint32_t* spec;
-    uint32_t* chunk;                  // next chunk of 64 S tuples of the item
+    uint32_t* dir;
+    uint32_t* val;
+    uint32_t* chunk;                  // next chunk of the item's S tuples
 };
 
-// One workgroup, one item: a slice of a staged list into LDS, then the
-// item's S tuples stream their iterated lists past it (only the part in the
-// slice's A range when the staged list is sliced).  Waves take chunks of 64
-// S tuples from a workgroup counter and lane j looks up tuple j's list; lists of at most
-// TRI_SHORT_LIST entries are then walked by their own lane, longer ones one
-// after another by the whole wave (64 consecutive entries per load, several
-// loads in flight per lane).
-__device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, uint32_t it, const BlockTable& B) {
+// last h in [0, n) with off[h] <= it, given off[0] <= it: 64 entries a round
+__device__ __forceinline__ uint32_t wave_last_le(const unsigned long long* off, uint32_t n, unsigned long long it) {
+    const uint32_t lane = lane_id();
+    uint32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + WAVE - 1) / WAVE;
+        const uint32_t k = lo + lane * step;
+        const unsigned long long bal = __ballot(k < hi && off[k] <= it);
+        lo += (uint32_t)(63 - __clzll((long long)bal)) * step;
+        hi = min(hi, lo + step);
+    }
+    return lo;
+}
+
+__device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long long it, const BlockTable& B) {
     const int lane = lane_id();
-    const uint32_t mask = TRI_HEAVY_CAP - 1;
     // item -> (heavy group, slice of the staged list, range of the group)
-    uint32_t lo = 0, hi = A.n_heavy_cap;              // last h with off[h] <= it
-    while (hi - lo > 1) { uint32_t m = (lo + hi) >> 1; if (A.heavy_off[m] <= it) lo = m; else hi = m; }
+    const uint32_t lo = wave_last_le(A.heavy_off, A.n_heavy_cap, it);
     const uint32_t g = A.heavy_group[lo];
     const uint32_t local = (uint32_t)(it - A.heavy_off[lo]);
     uint32_t rs = 0, x = 0;
@@ -361,55 +421,56 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, uint32_t it, 
     uint32_t nsl, nsr;
     heavy_shape(x, gn, A.share, nsl, nsr);
     const uint32_t sa = local / nsr, sb = local % nsr;
-    TriHeavyItem H;
-    H.r0 = rs + (uint32_t)((uint64_t)x * sa / nsl);
-    H.r1 = rs + (uint32_t)((uint64_t)x * (sa + 1) / nsl);
-    H.s0 = gs + sb * TRI_HEAVY_S;
-    H.s1 = min(gs + gn, H.s0 + TRI_HEAVY_S);
-    unsigned long long acc = 0;
-    if (H.r0 == H.r1) return 0;                       // uniform across the block
-    for (uint32_t q = H.r0 + threadIdx.x; q < H.r1; q += blockDim.x)
-        atab_add(B.keys, B.vals, mask, B.spec, A.Stgl[q]);
+    const uint32_t r0 = rs + (uint32_t)((uint64_t)x * sa / nsl);
+    const uint32_t r1 = rs + (uint32_t)((uint64_t)x * (sa + 1) / nsl);
+    const uint32_t s0 = gs + sb * TRI_HEAVY_S, s1 = min(gs + gn, s0 + TRI_HEAVY_S);
+    if (r0 == r1) return 0;                           // uniform across the block
+    const uint32_t len = r1 - r0;
+    ListTab T{B.dir, B.val, A.Stgl[r0], 0u, 0u};
+    T.top = A.Stgl[r1 - 1] - T.base;
+    const uint32_t width = 32u - (uint32_t)__clz((int)(T.top | 1u));           // bits of the largest offset
+    T.shift = width > TRI_HEAVY_DIR_BITS ? width - TRI_HEAVY_DIR_BITS : 0u;
+    for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) T.val[q] = A.Stgl[r0 + q];
+    for (uint32_t q = threadIdx.x; q < (1u << TRI_HEAVY_DIR_BITS); q += blockDim.x) T.dir[q] = 0;
     __syncthreads();
-    const uint32_t sp = *B.spec;
+    for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) listtab_index(T, q);
+    __syncthreads();
     const bool sliced = nsl > 1;
-    const uint32_t alo = A.Stgl[H.r0], ahi = A.Stgl[H.r1 - 1];
+    // chunks of at most 64 S tuples, smaller ones while a wave would get fewer than two
+    const uint32_t per = min((uint32_t)WAVE, max(8u, (s1 - s0) / (2 * (blockDim.x / WAVE))));
+    unsigned long long acc = 0;
     while (true) {
         uint32_t c = 0;
         if (lane == 0) c = atomicAdd(B.chunk, 1u);
-        const uint32_t c0 = H.s0 + __shfl(c, 0, WAVE) * WAVE;
-        if (c0 >= H.s1) break;                        // wave-uniform
+        const uint32_t c0 = s0 + __shfl(c, 0, WAVE) * per;
+        if (c0 >= s1) break;                          // wave-uniform
         const uint32_t si = c0 + lane;
-        acc += stream_chunk(A, si, si < H.s1, x, B.keys, B.vals, mask, sp, sliced, alo, ahi);
+        acc += stream_chunk(A, si, (uint32_t)lane < per && si < s1, x, T, sliced);
     }
     return acc;
 }
 
 #define TRI_HEAVY_SETUP                                                   \
-    __shared__ uint32_t hkeys[TRI_HEAVY_CAP];                             \
-    __shared__ uint32_t hvals[TRI_HEAVY_CAP];                             \
-    __shared__ uint32_t hspec;                                            \
+    __shared__ uint32_t hdir[1u << TRI_HEAVY_DIR_BITS];                   \
+    __shared__ uint32_t hval[TRI_HEAVY_X];                                \
     __shared__ uint32_t hchunk;                                           \
-    __shared__ uint32_t s_item;                                           \
-    BlockTable B{hkeys, hvals, &hspec, &hchunk};                          \
-    const int lane = lane_id();
+    const BlockTable B{hdir, hval, &hchunk};
 
 MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinArgs) {
     (void)vg;
     TRI_HEAVY_SETUP
+    __shared__ uint32_t s_item;
     const uint32_t nitems = (uint32_t)A.heavy_off[A.n_heavy_cap];
     unsigned long long acc = 0;
     while (true) {
         __syncthreads();
-        if (threadIdx.x == 0) { s_item = atomicAdd(A.heavy_next, 1u); hspec = 0; hchunk = 0; }
-        for (uint32_t s = threadIdx.x; s < TRI_HEAVY_CAP; s += blockDim.x) { hkeys[s] = EMPTY_KEY; hvals[s] = 0; }
+        if (threadIdx.x == 0) { s_item = atomicAdd(A.heavy_next, 1u); hchunk = 0; }
         __syncthreads();
         const uint32_t it = s_item;
         if (it >= nitems) break;
         acc += tri_heavy_item(A, it, B);
     }
-    acc = wave_sum_u64(acc);
-    if (lane == 0 && acc) atomicAdd(A.total, acc);
+    block_add_u64(A.total, acc);
 }
 
 // ------------------------------------------------------------- batches
@@ -427,17 +488,12 @@ __global__ void __launch_bounds__(TRI_THREADS)
 k_tri_light_batch(TriBatchArgs Bt) {
     TRI_LIGHT_SETUP
     const unsigned long long nitems = Bt.light_base[Bt.njoins];
-    const unsigned long long grab = light_grab(nitems, (unsigned long long)gridDim.x * (TRI_THREADS / WAVE));
+    const uint32_t grab = light_grab(nitems, (unsigned long long)gridDim.x * (TRI_THREADS / WAVE));
     unsigned long long it = 0, end = 0, acc = 0;
     uint32_t cur = 0;                                 // the join whose count acc holds
+    uint32_t q = blockIdx.x % TRI_QUEUES;
     while (true) {
-        if (it >= end) {                              // wave-uniform
-            unsigned long long t = 0;
-            if (lane == 0) t = atomicAdd(Bt.next, grab);
-            it = __shfl(t, 0, WAVE);
-            if (it >= nitems) break;
-            end = min(it + grab, nitems);
-        }
+        if (it >= end && !light_next_run(Bt.light_next, nitems, grab, q, it, end)) break;   // wave-uniform
         const uint32_t j = batch_join_of(Bt.light_base, Bt.njoins, it);
         if (j != cur) {                               // a run may span joins: add the last one's count
             acc = wave_sum_u64(acc);
@@ -446,7 +502,7 @@ k_tri_light_batch(TriBatchArgs Bt) {
             cur = j;
         }
         const TriJoinArgs& A = Bt.joins[j];
-        acc += tri_light_group(A, A.light[it - Bt.light_base[j]], W);
+        acc += tri_light_group(A, A.light[it - Bt.light_base[j]], T);
         ++it;
     }
     acc = wave_sum_u64(acc);
@@ -461,36 +517,42 @@ k_tri_heavy_batch(TriBatchArgs Bt) {
     const unsigned long long nitems = Bt.heavy_base[Bt.njoins];
     while (true) {
         __syncthreads();
-        if (threadIdx.x == 0) { s_bitem = atomicAdd(Bt.next + 1, 1ull); hspec = 0; hchunk = 0; s_sum = 0; }
-        for (uint32_t s = threadIdx.x; s < TRI_HEAVY_CAP; s += blockDim.x) { hkeys[s] = EMPTY_KEY; hvals[s] = 0; }
+        if (threadIdx.x == 0) { s_bitem = atomicAdd(Bt.heavy_next, 1ull); hchunk = 0; s_sum = 0; }
         __syncthreads();
         const unsigned long long it = s_bitem;
         if (it >= nitems) break;
         const uint32_t j = batch_join_of(Bt.heavy_base, Bt.njoins, it);
         const TriJoinArgs& A = Bt.joins[j];
-        unsigned long long acc = tri_heavy_item(A, (uint32_t)(it - Bt.heavy_base[j]), B);
+        unsigned long long acc = tri_heavy_item(A, it - Bt.heavy_base[j], B);
         acc = wave_sum_u64(acc);
-        if (lane == 0 && acc) atomicAdd(&s_sum, acc);
+        if (lane_id() == 0 && acc) atomicAdd(&s_sum, acc);
         __syncthreads();
         if (threadIdx.x == 0 && s_sum) atomicAdd(A.total, s_sum);
     }
-    (void)s_item;
 }
 
-// per-join item counts of a batch -> exclusive prefixes (one block)
-__global__ void k_tri_batch_prefix(TriBatchArgs Bt) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    unsigned long long l = 0, h = 0;
-    for (uint32_t j = 0; j < Bt.njoins; ++j) {
-        Bt.light_base[j] = l;
-        Bt.heavy_base[j] = h;
-        l += *Bt.joins[j].nlight;
-        h += Bt.joins[j].heavy_off[Bt.joins[j].n_heavy_cap];
+// per-join item counts of a batch -> exclusive prefixes, and the batch's
+// queue counters cleared (one wave, a join per lane and round)
+__global__ void __launch_bounds__(WAVE) k_tri_batch_prefix(TriBatchArgs Bt) {
+    const uint32_t lane = threadIdx.x;
+    for (uint32_t i = lane; i < TRI_QUEUES * TRI_QUEUE_PAD; i += WAVE) Bt.light_next[i] = 0;
+    if (lane == 0) *Bt.heavy_next = 0;
+    unsigned long long l0 = 0, h0 = 0;
+    for (uint32_t j0 = 0; j0 < Bt.njoins; j0 += WAVE) {
+        const uint32_t j = j0 + lane;
+        const unsigned long long nl = j < Bt.njoins ? *Bt.joins[j].nlight : 0ull;
+        const unsigned long long nh = j < Bt.njoins ? Bt.joins[j].heavy_off[Bt.joins[j].n_heavy_cap] : 0ull;
+        unsigned long long l = nl, h = nh;
+#pragma unroll
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const unsigned long long yl = __shfl_up(l, off, WAVE), yh = __shfl_up(h, off, WAVE);
+            if ((int)lane >= off) { l += yl; h += yh; }
+        }
+        if (j < Bt.njoins) { Bt.light_base[j] = l0 + l - nl; Bt.heavy_base[j] = h0 + h - nh; }
+        l0 += __shfl(l, WAVE - 1, WAVE);
+        h0 += __shfl(h, WAVE - 1, WAVE);
     }
-    Bt.light_base[Bt.njoins] = l;
-    Bt.heavy_base[Bt.njoins] = h;
-    Bt.next[0] = 0;
-    Bt.next[1] = 0;
+    if (lane == 0) { Bt.light_base[Bt.njoins] = l0; Bt.heavy_base[Bt.njoins] = h0; }
 }
 
 // ----------------------------------------------- cascade, cyclic second join

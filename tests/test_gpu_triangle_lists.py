@@ -1,0 +1,58 @@
+"""The cyclic join's staged lists at the edges of their sizes: lists staged by
+a wave (at most 512 entries) or by a workgroup (slices of at most 4096), lists
+streamed by a lane (at most 16) or by the wave in pieces of 64, groups around
+a wave's chunk, bags (repeated tuples), every share.  Totals are integers and
+must equal the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import dev, fixed_plan
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mj():
+    import paper_1905_13376_amd as mj
+    return mj
+
+
+def _hub(rng, x, y, g, bag):
+    """One hub B value with x R tuples, g S tuples (its C values, plus one
+    small group), each C value with y T tuples; half of T's A values are R's."""
+    a = rng.permutation(1 << 20)[:max(x, 1)].astype(np.uint32)
+    if bag:
+        a = a[rng.integers(0, max(1, x // 3), size=x)]
+    R = np.stack([a[:x], np.full(x, 7, np.uint32)], axis=1)
+    c = rng.integers(0, max(1, min(g, 40)), size=g).astype(np.uint32) + 100
+    S = np.stack([np.full(g, 7, np.uint32), c], axis=1)
+    S = np.concatenate([S, np.array([[9, 100], [7, 0xFFFFFFFF]], np.uint32)])
+    cs = np.unique(S[:, 1])
+    T = []
+    for v in cs:
+        t = rng.integers(0, 1 << 20, size=y).astype(np.uint32)
+        hit = rng.random(y) < 0.5
+        t[hit] = a[rng.integers(0, a.size, size=int(hit.sum()))]
+        T.append(np.stack([np.full(y, v, np.uint32), t], axis=1))
+    T = np.concatenate(T)
+    R = np.concatenate([R, np.array([[a[0], 9], [0xFFFFFFFF, 7]], np.uint32)])
+    T = np.concatenate([T, np.array([[100, 0xFFFFFFFF]], np.uint32)])
+    return R.astype(np.uint32), S.astype(np.uint32), T.astype(np.uint32)
+
+
+@pytest.mark.parametrize("x,y,g", [
+    (1, 1, 1), (15, 16, 63), (17, 15, 64), (64, 17, 65), (65, 63, 129), (128, 64, 31), (510, 65, 257),
+    (511, 510, 70), (512, 511, 64), (513, 300, 64), (1024, 513, 4095), (4094, 257, 4097), (4095, 1025, 90),
+    (4096, 5, 700), (4097, 16, 513), (8193, 4097, 40), (20000, 1500, 8200)])
+@pytest.mark.parametrize("bag", [False, True])
+def test_staged_and_streamed_list_sizes(mj, x, y, g, bag):
+    rng = np.random.default_rng(x * 7 + y * 3 + g + bag)
+    R, S, T = _hub(rng, x, y, g, bag)
+    want = oracle.triangle3_count(R, S, T)
+    ctx = mj.Context()
+    Rd, Sd, Td = dev(R), dev(S), dev(T)
+    for share in (0, 2, 5):
+        p = fixed_plan(mj, ctx, mj.TRIANGLE, Rd, Sd, Td, algo=mj.ALGO_3WAY, log2_share=share, seed=11 + share)
+        assert int(mj.as_u64(ctx.triangle3_count(Rd, Sd, Td, plan=p))[0]) == want, share
+    ctx.close()
