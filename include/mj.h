@@ -104,7 +104,7 @@ typedef enum {
  *   linear:   nb = H*h buckets on B, nc = g buckets on C (Sec. 4)
  *   cyclic:   share = least number of buckets on A of a hub list (Sec. 5:
  *             R is split by H(A) x G(B); here G is one list per B value,
- *             and a list is cut into max(share, ceil(len / 4096)) ranges
+ *             and a list is cut into max(share, ceil(len / 2048)) ranges
  *             of A so that every piece fits in one workgroup's LDS)
  * All bucket counts are powers of two, given by their log2.             */
 typedef struct {

@@ -1498,7 +1498,7 @@ int run_oriented(Prof* prof, int num_cu, const mj_rel& Erel, const mj_plan_t& p,
         for (int pass = 0; pass < 2; ++pass) {
             TriJoinArgs J = tri_join_args(L, q, out, pass);
             MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
-            MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)num_cu * 2), dim3(TRI_HEAVY_THREADS), 0, s,
+            MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)num_cu * TRI_HEAVY_PER_CU), dim3(TRI_HEAVY_THREADS), 0, s,
                       J);
         }
     }
@@ -2054,7 +2054,7 @@ int mj_triangle3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_r
     for (int pass = 0; pass < 2; ++pass) {
         TriJoinArgs J = tri_join_args(L, p, out, pass);
         MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
-        MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)ctx->num_cu * 2), dim3(TRI_HEAVY_THREADS), 0, s, J);
+        MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)ctx->num_cu * TRI_HEAVY_PER_CU), dim3(TRI_HEAVY_THREADS), 0, s, J);
     }
     return MJ_OK;
 }
@@ -2698,7 +2698,7 @@ int mj_batch_count(mj_ctx* ctx, const mj_batch_item* items, int n, void* ws, uin
         MJ_LAUNCH(prof, "k_tri_batch_prefix", k_tri_batch_prefix, dim3(1), dim3(64), 0, s, T);
         MJ_LAUNCH(prof, "k_tri_light_batch", k_tri_light_batch, dim3((uint32_t)ctx->num_cu * TRI_LIGHT_PER_CU),
                   dim3(TRI_THREADS), 0, s, T);
-        MJ_LAUNCH(prof, "k_tri_heavy_batch", k_tri_heavy_batch, dim3((uint32_t)ctx->num_cu * 2),
+        MJ_LAUNCH(prof, "k_tri_heavy_batch", k_tri_heavy_batch, dim3((uint32_t)ctx->num_cu * TRI_HEAVY_PER_CU),
                   dim3(TRI_HEAVY_THREADS), 0, s, T);
     }
     return MJ_OK;

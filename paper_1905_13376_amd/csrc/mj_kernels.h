@@ -605,15 +605,16 @@ MJ_KERNEL_DECL(k_rs_small, RsSmallArgs);
 MJ_KERNEL_DECL(k_rs_scan1, RsScan1Args);
 
 // --------------------------------------------------------------- triangle
-constexpr int TRI_THREADS = 256;           // light kernel: one table per wave
-constexpr int TRI_HEAVY_THREADS = 1024;    // heavy kernel: one table per workgroup
-constexpr uint32_t TRI_LIGHT_X = 512;      // staged list length handled by one wave
+constexpr int TRI_THREADS = 256;           // light kernel: one staged list per wave
+constexpr int TRI_HEAVY_THREADS = 512;     // heavy kernel: one staged list per workgroup
+constexpr uint32_t TRI_LIGHT_X = 448;      // staged list length handled by one wave (six workgroups a CU)
 constexpr uint32_t TRI_LIGHT_DIR_BITS = 10;// its directory
 constexpr uint32_t TRI_LIGHT_S = 4096;     // S group size handled by one wave
-constexpr uint32_t TRI_HEAVY_X = 4096;     // slice of a staged list handled by one workgroup
-constexpr uint32_t TRI_HEAVY_DIR_BITS = 13;// its directory
+constexpr uint32_t TRI_HEAVY_X = 2048;     // slice of a staged list handled by one workgroup
+constexpr uint32_t TRI_HEAVY_DIR_BITS = 12;// its directory
+constexpr uint32_t TRI_HEAVY_PER_CU = 2048 / TRI_HEAVY_THREADS;   // workgroups that fill a CU's waves
 static_assert(TRI_HEAVY_X <= 65535, "directory entries hold 16-bit positions and counts");
-constexpr uint32_t TRI_HEAVY_S = 4096;     // S tuples per heavy item (chunks of at most 64 per wave)
+constexpr uint32_t TRI_HEAVY_S = 2048;     // S tuples per heavy item (chunks of at most 64 per wave)
 constexpr uint32_t TRI_SHORT_LIST = 16;    // lists walked by one lane
 constexpr uint32_t TRI_LIGHT_PER_CU = 6;   // workgroups of the light kernel that fit a CU (LDS)
 constexpr uint32_t TRI_QUEUES = 32;        // queues of light items, their counters

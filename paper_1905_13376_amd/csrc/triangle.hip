@@ -155,25 +155,47 @@ MJ_KERNEL(k_tri_classify, 256, TriClassifyArgs) {
 // hold about the same number each.  dir[bucket] = first position | number of
 // entries << 16.  A lookup reads one directory word and then the bucket's
 // entries (one or two), where an open-addressing table at half load made a
-// wave walk as far as the longest of its 64 probe chains; equal entries are
-// counted, so duplicates need no multiplicity field.  Bound by the lookups'
+// wave walk as far as the longest of its 64 probe chains.  A list with equal
+// entries (bags) also has run[q] = how many entries equal to val[q] start at
+// q, and a lookup steps over the bucket run by run, so that a tuple repeated
+// thousands of times costs one step.  Bound by the lookups'
 // instructions (about one vector instruction an entry), then by the latency
 // of the streamed lists.  Oriented join of the R-MAT graph of scale 22
-// (1.3e10 streamed entries): light kernel 48.1 -> 12.5 ms, heavy kernel
-// 24.2 -> 13.7 ms against hash tables and one list in flight.
+// (1.3e10 streamed entries): light kernel 48.1 -> 8.2 ms, heavy kernel
+// 24.2 -> 12.5 ms against hash tables and one list in flight.
 struct ListTab {
     uint32_t* dir;
     uint32_t* val;
+    uint16_t* run;
     uint32_t base, top, shift;        // bucket of a: (a - base) >> shift, when a - base <= top
+    bool dup;                         // some entries are equal: `run` is set
 };
 
-__device__ __forceinline__ void listtab_index(const ListTab& T, uint32_t q) {
-    const uint32_t b = (T.val[q] - T.base) >> T.shift;
-    const bool head = q == 0 || ((T.val[q - 1] - T.base) >> T.shift) != b;
+// entry q into the directory; true when it equals the entry before it
+__device__ __forceinline__ bool listtab_index(const ListTab& T, uint32_t q) {
+    const uint32_t v = T.val[q], b = (v - T.base) >> T.shift;
+    const uint32_t u = q ? T.val[q - 1] : 0u;
+    const bool head = q == 0 || ((u - T.base) >> T.shift) != b;
     atomicAdd(&T.dir[b], 0x10000u + (head ? q : 0u));
+    return q && u == v;
+}
+
+// run[q] of a run's first entry: the end of its run, by a binary search in
+// the rest of its bucket
+__device__ __forceinline__ void listtab_run(const ListTab& T, uint32_t q) {
+    const uint32_t v = T.val[q];
+    if (q && T.val[q - 1] == v) return;
+    const uint32_t d = T.dir[(v - T.base) >> T.shift];
+    uint32_t lo = q + 1, hi = (d & 0xFFFFu) + (d >> 16);
+    while (lo < hi) {
+        const uint32_t m = (lo + hi) >> 1;
+        if (T.val[m] == v) lo = m + 1; else hi = m;
+    }
+    T.run[q] = (uint16_t)(lo - q);
 }
 
 // entries equal to the four keys; every read of a step is in flight together
+template <bool DUP>
 __device__ __forceinline__ uint32_t listtab_count4(const ListTab& T, const uint32_t (&key)[4], const bool (&live)[4]) {
     uint32_t p[4], n[4], acc = 0, most = 0;
 #pragma unroll
@@ -186,6 +208,26 @@ __device__ __forceinline__ uint32_t listtab_count4(const ListTab& T, const uint3
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) most = max(most, n[u]);
+    if constexpr (DUP) {
+        uint32_t e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = p[u] + n[u];
+        bool more = most > 0;
+        while (more) {
+            more = false;
+            uint32_t v[4], r[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { v[u] = T.val[p[u] < e[u] ? p[u] : 0u]; r[u] = T.run[p[u] < e[u] ? p[u] : 0u]; }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (p[u] >= e[u]) continue;
+                acc += v[u] == key[u] ? r[u] : 0u;
+                p[u] += r[u];
+                more = more || p[u] < e[u];
+            }
+        }
+        return acc;
+    }
     for (uint32_t i = 0; i < most; ++i) {
         uint32_t v[4];
 #pragma unroll
@@ -221,6 +263,7 @@ __device__ __forceinline__ void wave_fence() {
 // consecutive entries, four pieces (of one list or of several) per step, the
 // next step's pieces loaded before the present ones are looked up.  Returns
 // the lane's partial sum.
+template <bool DUP>
 __device__ __forceinline__ unsigned long long stream_chunk(const TriJoinArgs& A, uint32_t si, bool valid,
                                                            uint32_t x, const ListTab& T, bool sliced) {
     const int lane = lane_id();
@@ -258,7 +301,7 @@ __device__ __forceinline__ unsigned long long stream_chunk(const TriJoinArgs& A,
                 nlive[u] = t0 + 4 + u < te;
                 nkey[u] = nlive[u] ? A.Itrl[t0 + 4 + u] : 0u;
             }
-            acc += listtab_count4(T, key, live);
+            acc += listtab_count4<DUP>(T, key, live);
 #pragma unroll
             for (int u = 0; u < 4; ++u) { key[u] = nkey[u]; live[u] = nlive[u]; }
         }
@@ -289,7 +332,7 @@ __device__ __forceinline__ unsigned long long stream_chunk(const TriJoinArgs& A,
         uint32_t nkey[4];
         bool nlive[4];
         more = fetch(nkey, nlive);
-        acc += listtab_count4(T, key, live);
+        acc += listtab_count4<DUP>(T, key, live);
 #pragma unroll
         for (int u = 0; u < 4; ++u) { key[u] = nkey[u]; live[u] = nlive[u]; }
     }
@@ -298,19 +341,29 @@ __device__ __forceinline__ unsigned long long stream_chunk(const TriJoinArgs& A,
 
 // ------------------------------------------------------------- light groups
 // One wave, one S group: the staged list (at most TRI_LIGHT_X entries) and its
-// directory in 6 KB of LDS per wave, so six workgroups (24 waves) fit a CU;
+// directory in 6.6 KB of LDS per wave, so six workgroups (24 waves) fit a CU;
 // then every s(b,c) of the group streams its iterated list past it, 64 tuples
 // at a time (stream_chunk).  Returns the lane's sum.
-__device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint2 item, const ListTab& T) {
+__device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint2 item, ListTab T) {
     const int lane = lane_id();
     const uint32_t gs = A.Grp.run_start[item.x], ge = A.Grp.run_start[item.x + 1];
     const uint32_t rs = A.Stg.run_start[item.y], x = A.Stg.run_start[item.y + 1] - rs;
     for (uint32_t q = lane; q < x; q += WAVE) T.val[q] = A.Stgl[rs + q];
     wave_fence();
-    for (uint32_t q = lane; q < x; q += WAVE) listtab_index(T, q);
+    bool dup = false;
+    for (uint32_t q = lane; q < x; q += WAVE) dup = listtab_index(T, q) || dup;
     wave_fence();
+    T.dup = __ballot(dup) != 0;
     unsigned long long acc = 0;
-    for (uint32_t c0 = gs; c0 < ge; c0 += WAVE) acc += stream_chunk(A, c0 + lane, c0 + lane < ge, x, T, false);
+    if (T.dup) {
+        for (uint32_t q = lane; q < x; q += WAVE) listtab_run(T, q);
+        wave_fence();
+        for (uint32_t c0 = gs; c0 < ge; c0 += WAVE)
+            acc += stream_chunk<true>(A, c0 + lane, c0 + lane < ge, x, T, false);
+    } else {
+        for (uint32_t c0 = gs; c0 < ge; c0 += WAVE)
+            acc += stream_chunk<false>(A, c0 + lane, c0 + lane < ge, x, T, false);
+    }
     wave_fence();
     for (uint32_t q = lane; q < x; q += WAVE) T.dir[T.val[q] >> T.shift] = 0;
     wave_fence();
@@ -321,8 +374,9 @@ __device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint2 item, 
     constexpr int NW = TRI_THREADS / WAVE;                                           \
     __shared__ uint32_t tdir[NW][1u << TRI_LIGHT_DIR_BITS];                          \
     __shared__ uint32_t tval[NW][TRI_LIGHT_X];                                       \
+    __shared__ uint16_t trun[NW][TRI_LIGHT_X];                                       \
     const int w = threadIdx.x / WAVE, lane = lane_id();                              \
-    const ListTab T{tdir[w], tval[w], 0u, 0xFFFFFFFFu, 32 - TRI_LIGHT_DIR_BITS};     \
+    const ListTab T{tdir[w], tval[w], trun[w], 0u, 0xFFFFFFFFu, 32 - TRI_LIGHT_DIR_BITS, false}; \
     for (uint32_t s = lane; s < (1u << TRI_LIGHT_DIR_BITS); s += WAVE) T.dir[s] = 0; \
     wave_fence();
 
@@ -385,13 +439,17 @@ MJ_KERNEL(k_tri_light, TRI_THREADS, TriJoinArgs) {
 
 // ------------------------------------------------------------- heavy groups
 // One workgroup, one item: a slice of a hub's staged list (at most TRI_HEAVY_X
-// entries) and its directory in 48 KB of LDS, then the item's S tuples stream
+// entries) and its directory in 28 KB of LDS, then the item's S tuples stream
 // their iterated lists past it (only the part in the slice's range of A when
 // the staged list is sliced).  Waves take chunks of S tuples from a workgroup
-// counter.
+// counter.  Eight waves and 2048 entries: with 16 waves and 4096 entries the
+// many lists of 449 to 1,100 entries left waves idle (17.3 -> 12.5 ms at scale
+// 22, oriented).
 struct BlockTable {
     uint32_t* dir;
     uint32_t* val;
+    uint16_t* run;
+    uint32_t* dup;
     uint32_t* chunk;                  // next chunk of the item's S tuples
 };
 
@@ -426,15 +484,22 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
     const uint32_t s0 = gs + sb * TRI_HEAVY_S, s1 = min(gs + gn, s0 + TRI_HEAVY_S);
     if (r0 == r1) return 0;                           // uniform across the block
     const uint32_t len = r1 - r0;
-    ListTab T{B.dir, B.val, A.Stgl[r0], 0u, 0u};
+    ListTab T{B.dir, B.val, B.run, A.Stgl[r0], 0u, 0u, false};
     T.top = A.Stgl[r1 - 1] - T.base;
     const uint32_t width = 32u - (uint32_t)__clz((int)(T.top | 1u));           // bits of the largest offset
     T.shift = width > TRI_HEAVY_DIR_BITS ? width - TRI_HEAVY_DIR_BITS : 0u;
     for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) T.val[q] = A.Stgl[r0 + q];
     for (uint32_t q = threadIdx.x; q < (1u << TRI_HEAVY_DIR_BITS); q += blockDim.x) T.dir[q] = 0;
     __syncthreads();
-    for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) listtab_index(T, q);
+    bool dup = false;
+    for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) dup = listtab_index(T, q) || dup;
+    if (dup) *B.dup = 1;
     __syncthreads();
+    T.dup = *B.dup != 0;                              // uniform across the block
+    if (T.dup) {
+        for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) listtab_run(T, q);
+        __syncthreads();
+    }
     const bool sliced = nsl > 1;
     // chunks of at most 64 S tuples, smaller ones while a wave would get fewer than two
     const uint32_t per = min((uint32_t)WAVE, max(8u, (s1 - s0) / (2 * (blockDim.x / WAVE))));
@@ -445,7 +510,8 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
         const uint32_t c0 = s0 + __shfl(c, 0, WAVE) * per;
         if (c0 >= s1) break;                          // wave-uniform
         const uint32_t si = c0 + lane;
-        acc += stream_chunk(A, si, (uint32_t)lane < per && si < s1, x, T, sliced);
+        const bool valid = (uint32_t)lane < per && si < s1;
+        acc += T.dup ? stream_chunk<true>(A, si, valid, x, T, sliced) : stream_chunk<false>(A, si, valid, x, T, sliced);
     }
     return acc;
 }
@@ -453,8 +519,9 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
 #define TRI_HEAVY_SETUP                                                   \
     __shared__ uint32_t hdir[1u << TRI_HEAVY_DIR_BITS];                   \
     __shared__ uint32_t hval[TRI_HEAVY_X];                                \
-    __shared__ uint32_t hchunk;                                           \
-    const BlockTable B{hdir, hval, &hchunk};
+    __shared__ uint16_t hrun[TRI_HEAVY_X];                                \
+    __shared__ uint32_t hdup, hchunk;                                     \
+    const BlockTable B{hdir, hval, hrun, &hdup, &hchunk};
 
 MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinArgs) {
     (void)vg;
@@ -464,7 +531,7 @@ MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinArgs) {
     unsigned long long acc = 0;
     while (true) {
         __syncthreads();
-        if (threadIdx.x == 0) { s_item = atomicAdd(A.heavy_next, 1u); hchunk = 0; }
+        if (threadIdx.x == 0) { s_item = atomicAdd(A.heavy_next, 1u); hchunk = 0; hdup = 0; }
         __syncthreads();
         const uint32_t it = s_item;
         if (it >= nitems) break;
@@ -517,7 +584,7 @@ k_tri_heavy_batch(TriBatchArgs Bt) {
     const unsigned long long nitems = Bt.heavy_base[Bt.njoins];
     while (true) {
         __syncthreads();
-        if (threadIdx.x == 0) { s_bitem = atomicAdd(Bt.heavy_next, 1ull); hchunk = 0; s_sum = 0; }
+        if (threadIdx.x == 0) { s_bitem = atomicAdd(Bt.heavy_next, 1ull); hchunk = 0; hdup = 0; s_sum = 0; }
         __syncthreads();
         const unsigned long long it = s_bitem;
         if (it >= nitems) break;

@@ -1,5 +1,5 @@
 """The cyclic join's staged lists at the edges of their sizes: lists staged by
-a wave (at most 512 entries) or by a workgroup (slices of at most 4096), lists
+a wave (at most 448 entries) or by a workgroup (slices of at most 2048), lists
 streamed by a lane (at most 16) or by the wave in pieces of 64, groups around
 a wave's chunk, bags (repeated tuples), every share.  Totals are integers and
 must equal the oracle's."""
@@ -19,11 +19,11 @@ def mj():
 
 
 def _hub(rng, x, y, g, bag):
-    """One hub B value with x R tuples, g S tuples (its C values, plus one
+    """One hub B value with x R tuples (`bag` of each A value, if set), g S tuples (its C values, plus one
     small group), each C value with y T tuples; half of T's A values are R's."""
     a = rng.permutation(1 << 20)[:max(x, 1)].astype(np.uint32)
     if bag:
-        a = a[rng.integers(0, max(1, x // 3), size=x)]
+        a = a[rng.integers(0, max(1, x // bag), size=x)]
     R = np.stack([a[:x], np.full(x, 7, np.uint32)], axis=1)
     c = rng.integers(0, max(1, min(g, 40)), size=g).astype(np.uint32) + 100
     S = np.stack([np.full(g, 7, np.uint32), c], axis=1)
@@ -42,10 +42,10 @@ def _hub(rng, x, y, g, bag):
 
 
 @pytest.mark.parametrize("x,y,g", [
-    (1, 1, 1), (15, 16, 63), (17, 15, 64), (64, 17, 65), (65, 63, 129), (128, 64, 31), (510, 65, 257),
-    (511, 510, 70), (512, 511, 64), (513, 300, 64), (1024, 513, 4095), (4094, 257, 4097), (4095, 1025, 90),
+    (1, 1, 1), (15, 16, 63), (17, 15, 64), (64, 17, 65), (65, 63, 129), (128, 64, 31), (447, 65, 257), (448, 447, 300), (449, 448, 65),
+    (511, 510, 70), (512, 511, 64), (513, 300, 64), (1024, 513, 4095), (4094, 257, 4097), (2047, 1025, 90), (2048, 64, 2049), (2049, 17, 2048),
     (4096, 5, 700), (4097, 16, 513), (8193, 4097, 40), (20000, 1500, 8200)])
-@pytest.mark.parametrize("bag", [False, True])
+@pytest.mark.parametrize("bag", [0, 3, 200])
 def test_staged_and_streamed_list_sizes(mj, x, y, g, bag):
     rng = np.random.default_rng(x * 7 + y * 3 + g + bag)
     R, S, T = _hub(rng, x, y, g, bag)
