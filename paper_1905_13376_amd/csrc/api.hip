@@ -639,15 +639,17 @@ struct RunBuf {
     uint32_t* dir;
     uint32_t bits;
     unsigned long long* nruns;
+    uint32_t* part;                   // [run_tiles(n) + 1]
 };
+
+uint32_t run_tiles(uint64_t n) { return (uint32_t)std::max<uint64_t>(1, (n + RUN_TILE - 1) / RUN_TILE); }
+uint64_t rs_tiles(uint64_t n) { return (std::max<uint64_t>(n, 1) + RS_TILE - 1) / RS_TILE; }
 
 struct PassBuf {                      // work queues of one pass of the cyclic join
     uint2* light;
-    uint32_t* ctr;                    // [TRI_CTR_WORDS] nlight, -, nheavy_groups, heavy_next; the light queues
+    uint32_t* ctr;                    // [TRI_CTR_WORDS] nlight, heavy_next, heavy (64 bits); the light queues
     uint32_t* heavy_group;
-    uint32_t* heavy_items;
     unsigned long long* heavy_off;
-    uint32_t n_heavy_cap;
 };
 
 struct TriLayout {
@@ -659,14 +661,13 @@ struct TriLayout {
     uint32_t* Sl;
     uint32_t* Sl2;
     uint32_t* Tl;
-    unsigned long long* tmp;          // radix double buffer
-    uint32_t* rs_hist;
-    uint32_t* rs_counts;
-    uint32_t* rs_starts;
-    uint32_t* flags;
-    unsigned long long* ridx;
-    unsigned long long* partial;
+    // radix double buffers of the sorts that run together (the last two are
+    // the passes' light queues, filled after the sorts)
+    unsigned long long* tmp[4];
+    uint32_t* rs_hist[4];
+    uint32_t* rs_counts;              // [4][256]
     RunBuf R, S, S2, T;
+    uint32_t* ctr;                    // both passes' counters
     PassBuf P[2];
     size_t bytes;
 };
@@ -679,15 +680,15 @@ void take_runs(Bump& B, RunBuf& X, uint64_t n, bool with_dir) {
     X.bits = dir_bits(n);
     X.dir = with_dir ? B.take<uint32_t>((uint64_t(1) << X.bits) + 1) : nullptr;
     X.nruns = B.take<unsigned long long>(1);
+    X.part = B.take<uint32_t>(run_tiles(n) + 1);
 }
 
-void take_pass(Bump& B, PassBuf& P, uint64_t n_stage, uint64_t n_s) {
-    P.light = B.take<uint2>(std::max<uint64_t>(n_s, 1));
-    P.ctr = B.take<uint32_t>(TRI_CTR_WORDS);
-    P.n_heavy_cap = (uint32_t)(n_stage / (TRI_LIGHT_X + 1) + n_s / (TRI_LIGHT_S + 1) + 2);
-    P.heavy_group = B.take<uint32_t>(P.n_heavy_cap);
-    P.heavy_items = B.take<uint32_t>(P.n_heavy_cap);
-    P.heavy_off = B.take<unsigned long long>(P.n_heavy_cap + 1);
+// the light queue has room for nmax entries (it is a sort's buffer first)
+void take_pass(Bump& B, PassBuf& P, uint64_t n_stage, uint64_t n_s, uint64_t nmax) {
+    P.light = B.take<uint2>(nmax);
+    const uint64_t heavy = n_stage / (TRI_LIGHT_X + 1) + n_s / (TRI_LIGHT_S + 1) + 2;
+    P.heavy_group = B.take<uint32_t>(heavy);
+    P.heavy_off = B.take<unsigned long long>(heavy);
 }
 
 TriLayout tri_layout(void* ws, const mj_plan_t& p) {
@@ -702,20 +703,21 @@ TriLayout tri_layout(void* ws, const mj_plan_t& p) {
     L.Sl = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
     L.Sl2 = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
     L.Tl = B.take<uint32_t>(std::max<uint64_t>(p.n_t, 1));
-    L.tmp = B.take<unsigned long long>(nmax);
-    const uint64_t ntiles = (nmax + RS_TILE - 1) / RS_TILE;
-    L.rs_hist = B.take<uint32_t>(256 * ntiles);
-    L.rs_counts = B.take<uint32_t>(256);
-    L.rs_starts = B.take<uint32_t>(257);
-    L.flags = B.take<uint32_t>(nmax);
-    L.ridx = B.take<unsigned long long>(nmax + 1);
-    L.partial = B.take<unsigned long long>((nmax + SCAN_TILE - 1) / SCAN_TILE + 1);
+    L.tmp[0] = B.take<unsigned long long>(nmax);
+    L.tmp[1] = B.take<unsigned long long>(nmax);
+    for (int i = 0; i < 4; ++i) L.rs_hist[i] = B.take<uint32_t>(256 * rs_tiles(nmax));
+    L.rs_counts = B.take<uint32_t>(4 * 256);
     take_runs(B, L.R, p.n_r, true);
     take_runs(B, L.S, p.n_s, false);
     take_runs(B, L.S2, p.n_s, false);
     take_runs(B, L.T, p.n_t, true);
-    take_pass(B, L.P[0], p.n_r, p.n_s);
-    take_pass(B, L.P[1], p.n_t, p.n_s);
+    L.ctr = B.take<uint32_t>(2 * TRI_CTR_WORDS);
+    take_pass(B, L.P[0], p.n_r, p.n_s, nmax);
+    take_pass(B, L.P[1], p.n_t, p.n_s, nmax);
+    for (int q = 0; q < 2; ++q) {
+        L.P[q].ctr = L.ctr ? L.ctr + q * TRI_CTR_WORDS : nullptr;   // (null while only sizing)
+        L.tmp[2 + q] = reinterpret_cast<unsigned long long*>(L.P[q].light);
+    }
     L.bytes = B.off + 256;
     return L;
 }
@@ -757,66 +759,122 @@ int launch_scan_u64(Prof* prof, const unsigned long long* in, uint64_t n, unsign
     return MJ_OK;
 }
 
-// Sort n 64-bit keys in place (8 stable passes of 8 bits; tmp is the other buffer).
-// LSD radix sort of 64-bit keys on bytes first_pass..7 (first_pass = 4:
-// grouped by the high word, stable in the low word); first_pass must be even
-// so that the result is back in `keys`
-int launch_radix_sort(Prof* prof, unsigned long long* keys, unsigned long long* tmp, uint64_t n,
-                      uint32_t* hist, uint32_t* counts, uint32_t* starts, hipStream_t s,
-                      uint32_t first_pass = 0) {
-    if (n <= 1) return MJ_OK;
-    if (first_pass & 1) return MJ_ERR_INVALID_ARG;
-    if (first_pass >= 8) return MJ_OK;
-    if (n <= RS_SMALL) {                 // the whole sort in one workgroup
-        uint32_t P = 2;
-        while (P < n) P <<= 1;
-        const uint32_t shift = 8 * first_pass;
-        const size_t smem = size_t(P) * sizeof(unsigned long long);
-        MJ_LAUNCHM(prof, "k_rs_small", k_rs_small, dim3(1), dim3(RS_SMALL_THREADS), smem, s, keys, (uint32_t)n,
-                  shift);
-        return MJ_OK;
-    }
-    const uint32_t ntiles = (uint32_t)((n + RS_TILE - 1) / RS_TILE);
-    unsigned long long* src = keys;
-    unsigned long long* dst = tmp;
-    for (uint32_t pass = first_pass; pass < 8; ++pass) {
-        RsArgs A;
-        A.in = src; A.out = dst; A.n = n; A.shift = 8 * pass; A.ntiles = ntiles;
-        A.hist = hist; A.starts = starts;
-        MJ_LAUNCHM(prof, "k_rs_hist", k_rs_hist, dim3(ntiles), dim3(RS_THREADS), 0, s, A);
-        if (ntiles <= RS_SCAN1_TILES) {
-            MJ_LAUNCHM(prof, "k_rs_scan1", k_rs_scan1, dim3(1), dim3(256), 0, s, A, starts);
-        } else {
-            PartLaunch P{};
-            P.njobs = 1;
-            P.job[0].hist = hist; P.job[0].ntiles = ntiles; P.job[0].counts = counts;
-            P.job[0].starts = starts; P.job[0].bits0 = 8; P.job[0].bits1 = 0;
-            MJ_LAUNCHM(prof, "k_part_rowscan", k_part_rowscan, dim3(256), dim3(PART_THREADS),
-                      PART_SCAN_CHUNK * 4, s, P);
-            MJ_LAUNCHM(prof, "k_part_scan", k_part_scan, dim3(1), dim3(PART_THREADS), 256 * 4, s, P);
-        }
-        MJ_LAUNCHM(prof, "k_rs_scatter", k_rs_scatter, dim3(ntiles), dim3(RS_THREADS), 0, s, A);
-        std::swap(src, dst);
-    }
-    return MJ_OK;            // an even number of passes: the result is back in `keys`
-}
+// One array to sort: (mix(key) << 32 | mix(other)) of a relation's tuples, or
+// with the other value itself as low word.
+struct SortSpec {
+    const mj_rel* r;
+    int key_col;
+    bool raw_low;
+    unsigned long long* keys;         // the sorted keys
+    unsigned long long* tmp;          // the passes' other buffer
+    uint32_t* hist;                   // [256][tiles]
+    uint32_t* counts;                 // [256]
+};
 
-int launch_runs(Prof* prof, const TriLayout& L, const unsigned long long* keys, uint64_t n,
-                const RunBuf& X, uint32_t* low, hipStream_t s) {
-    if (n == 0) {
-        MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, X.nruns, (uint64_t)1, 0ull);
-        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, X.run_start, (uint64_t)1, 0u);
-    } else {
-        MJ_LAUNCHM(prof, "k_run_flags", k_run_flags, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
-                  keys, n, L.flags, low);
-        int st = launch_scan_u32(prof, L.flags, n, L.partial, L.ridx, s);
-        if (st) return st;
-        MJ_LAUNCHM(prof, "k_run_compact", k_run_compact, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
-                  keys, n, L.flags, L.ridx, X.run_key, X.run_start, X.nruns);
+// Make and sort the keys of up to RS_MAX_JOBS relations: LSD radix sort on
+// bytes first_pass..7 (first_pass = 4: grouped by the high word, stable in
+// input order; 2: the low words by their top 16 bits), first_pass even so
+// that the result is in `keys`.
+int launch_sorts(Prof* prof, const SortSpec* spec, int nspec, uint32_t seed, uint32_t first_pass, hipStream_t s) {
+    if (nspec > RS_MAX_JOBS || (first_pass & 1) || first_pass >= 8) return MJ_ERR_INVALID_ARG;
+    RsLaunch small, big;
+    unsigned long long *keys[RS_MAX_JOBS], *tmp[RS_MAX_JOBS];
+    uint32_t tiles = 0, most = 0, P = 2;
+    for (int i = 0; i < nspec; ++i) {
+        const SortSpec& x = spec[i];
+        if (x.r->n == 0) continue;
+        RsJob J;
+        J.key_col = x.key_col ? x.r->col1 : x.r->col0;
+        J.val_col = x.key_col ? x.r->col0 : x.r->col1;
+        J.stride = x.r->stride; J.n = x.r->n; J.seed = seed; J.raw_low = x.raw_low ? 1u : 0u;
+        J.hist = x.hist; J.counts = x.counts;
+        if (J.n <= RS_SMALL) {               // the whole sort in one workgroup
+            J.out = x.keys;
+            small.job[small.njobs++] = J;
+            while (P < J.n) P <<= 1;
+            continue;
+        }
+        J.ntiles = (uint32_t)((J.n + RS_TILE - 1) / RS_TILE);
+        J.tile_begin = tiles;
+        tiles += J.ntiles;
+        most = std::max(most, J.ntiles);
+        keys[big.njobs] = x.keys;
+        tmp[big.njobs] = x.tmp;
+        big.job[big.njobs++] = J;
     }
-    if (X.dir)
-        MJ_LAUNCHM(prof, "k_run_dir", k_run_dir, dim3(grid_for(n + 1, 256, 16384)), dim3(256), 0, s,
-                  X.run_key, X.nruns, X.bits, X.dir);
+    if (small.njobs) {
+        small.shift = 8 * first_pass;
+        MJ_LAUNCHM(prof, "k_rs_small", k_rs_small, dim3((uint32_t)small.njobs), dim3(RS_SMALL_THREADS),
+                   size_t(P) * sizeof(unsigned long long), s, small);
+    }
+    if (!big.njobs) return MJ_OK;
+    big.rows = most > RS_SELF_TILES ? 1u : 0u;
+    for (uint32_t pass = first_pass; pass < 8; ++pass) {
+        big.shift = 8 * pass;
+        for (int i = 0; i < big.njobs; ++i) {
+            RsJob& J = big.job[i];
+            if (pass > first_pass) J.key_col = J.val_col = nullptr;
+            J.in = (pass & 1) ? tmp[i] : keys[i];
+            J.out = (pass & 1) ? keys[i] : tmp[i];
+        }
+        MJ_LAUNCHM(prof, "k_rs_hist", k_rs_hist, dim3(tiles), dim3(RS_THREADS), 0, s, big);
+        if (big.rows) {
+            PartLaunch R{};
+            R.njobs = big.njobs;
+            for (int i = 0; i < big.njobs; ++i) {
+                R.job[i].hist = big.job[i].hist; R.job[i].ntiles = big.job[i].ntiles;
+                R.job[i].counts = big.job[i].counts; R.job[i].bits0 = 8;
+            }
+            MJ_LAUNCHM(prof, "k_part_rowscan", k_part_rowscan, dim3(256 * (uint32_t)big.njobs), dim3(PART_THREADS),
+                       PART_SCAN_CHUNK * 4, s, R);
+        }
+        MJ_LAUNCHM(prof, "k_rs_scatter", k_rs_scatter, dim3(tiles), dim3(RS_THREADS), 0, s, big);
+    }
+    return MJ_OK;
+}
+static_assert(RS_MAX_JOBS <= MJ_PART_MAX_JOBS && RUN_MAX_JOBS <= MJ_PART_MAX_JOBS, "rows of all jobs in one scan");
+
+// One sorted array's runs.
+struct RunSpec {
+    const unsigned long long* keys;
+    uint64_t n;
+    RunBuf X;
+    uint32_t* low;                    // the low words, or null
+};
+
+// Run indexes of up to RUN_MAX_JOBS sorted arrays (two or three launches);
+// the first launch also clears `nclear` words and `zero` for later ones.
+int launch_runs(Prof* prof, const RunSpec* spec, int nspec, hipStream_t s, uint32_t* clear = nullptr,
+                uint32_t nclear = 0, unsigned long long* zero = nullptr) {
+    if (nspec > RUN_MAX_JOBS) return MJ_ERR_INVALID_ARG;
+    RunLaunch L;
+    L.njobs = nspec;
+    L.clear = clear; L.nclear = nclear; L.zero = zero;
+    uint32_t tiles = 0, most = 0;
+    for (int i = 0; i < nspec; ++i) {
+        RunJob& J = L.job[i];
+        const RunBuf& X = spec[i].X;
+        J.keys = spec[i].keys; J.n = spec[i].n; J.low = spec[i].low;
+        J.run_key = X.run_key; J.run_start = X.run_start; J.dir = X.dir; J.bits = X.bits; J.nruns = X.nruns;
+        J.part = X.part;
+        J.ntiles = run_tiles(J.n);
+        J.tile_begin = tiles;
+        tiles += J.ntiles;
+        most = std::max(most, J.ntiles);
+    }
+    L.scanned = most > RUN_SELF_TILES ? 1u : 0u;
+    MJ_LAUNCHM(prof, "k_run_count", k_run_count, dim3(tiles), dim3(RUN_THREADS), 0, s, L);
+    if (L.scanned) {
+        PartLaunch R{};
+        R.njobs = nspec;
+        for (int i = 0; i < nspec; ++i) {
+            R.job[i].hist = L.job[i].part; R.job[i].ntiles = L.job[i].ntiles;
+            R.job[i].counts = L.job[i].part + L.job[i].ntiles;
+        }
+        MJ_LAUNCHM(prof, "k_part_rowscan", k_part_rowscan, dim3((uint32_t)nspec), dim3(PART_THREADS),
+                   PART_SCAN_CHUNK * 4, s, R);
+    }
+    MJ_LAUNCHM(prof, "k_run_emit", k_run_emit, dim3(tiles), dim3(RUN_THREADS), 0, s, L);
     return MJ_OK;
 }
 
@@ -825,18 +883,6 @@ RunIndex run_index(const RunBuf& X) {
     I.run_key = X.run_key; I.run_start = X.run_start; I.dir = X.dir; I.bits = X.bits;
     I.nruns = X.nruns;
     return I;
-}
-
-// (mix(key) << 32 | mix(other)), or the other value itself as low word
-int tri_keys(Prof* prof, const mj_rel& r, int key_col, unsigned long long* out, uint32_t seed,
-             hipStream_t s, bool raw_low = false) {
-    if (r.n == 0) return MJ_OK;
-    TriKeyArgs K;
-    K.key_col = key_col ? r.col1 : r.col0;
-    K.val_col = key_col ? r.col0 : r.col1;
-    K.stride = r.stride; K.n = r.n; K.seed = seed; K.raw_low = raw_low ? 1u : 0u; K.out = out;
-    MJ_LAUNCHM(prof, "k_tri_keys", k_tri_keys, dim3(grid_for(r.n, 256, 16384)), dim3(256), 0, s, K);
-    return MJ_OK;
 }
 
 struct CasTriLayout {
@@ -850,9 +896,6 @@ struct CasTriLayout {
     unsigned long long* tmp;
     uint32_t* rs_hist;
     uint32_t* rs_counts;
-    uint32_t* rs_starts;
-    uint32_t* flags;
-    unsigned long long* ridx;
     RunBuf Trun;
     uint32_t* err;                    // set when |I| on the device is not the plan's
     uint2* I;
@@ -873,11 +916,8 @@ CasTriLayout cas_tri_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
     L.partial = B.take<unsigned long long>((nmax + SCAN_TILE - 1) / SCAN_TILE + 1);
     L.Tk = B.take<unsigned long long>(std::max<uint64_t>(p.n_t, 1));
     L.tmp = B.take<unsigned long long>(std::max<uint64_t>(p.n_t, 1));
-    L.rs_hist = B.take<uint32_t>(256 * ((std::max<uint64_t>(p.n_t, 1) + RS_TILE - 1) / RS_TILE));
+    L.rs_hist = B.take<uint32_t>(256 * rs_tiles(p.n_t));
     L.rs_counts = B.take<uint32_t>(256);
-    L.rs_starts = B.take<uint32_t>(257);
-    L.flags = B.take<uint32_t>(std::max<uint64_t>(p.n_t, 1));
-    L.ridx = B.take<unsigned long long>(p.n_t + 1);
     take_runs(B, L.Trun, p.n_t, true);
     L.err = B.take<uint32_t>(1);
     L.I = B.take<uint2>(0);
@@ -890,70 +930,75 @@ CasTriLayout cas_tri_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
     return L;
 }
 
-int tri_prepare(Prof* prof, int num_cu, const mj_rel& R, const mj_rel& S, const mj_rel& T,
-                const mj_plan_t& p, const TriLayout& L, unsigned long long* out, hipStream_t s) {
-    (void)num_cu; (void)out;
+// The sorted key arrays, their runs and both passes' work queues; *out is set
+// to 0.  `first_pass` as for launch_sorts: the passes need each list ordered
+// by the top 16 bits of its low words, and lists that may repeat an entry
+// fully (equal entries side by side).
+int tri_prepare(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, const mj_plan_t& p, TriLayout& L,
+                uint32_t first_pass, unsigned long long* out, hipStream_t s) {
     int st;
-    const uint32_t seed = p.seed;
     // keys: R -> (m(b), m(a)), S -> (m(b), m(c)) and (m(c), m(b)), T -> (m(c), m(a)).
     // An array made from the same (key column, other column) as an earlier
     // one -- R = S = T as one symmetric relation gives two distinct arrays,
-    // not four -- is copied from it instead of sorted again.
-    struct KeySrc { const mj_rel* r; int key_col; unsigned long long* dst; };
-    const KeySrc src[4] = {{&R, 1, L.Rk}, {&S, 0, L.Sk}, {&S, 1, L.Sk2}, {&T, 0, L.Tk}};
-    auto cols = [](const KeySrc& k, const uint32_t*& kc, const uint32_t*& vc) {
-        kc = k.key_col ? k.r->col1 : k.r->col0;
-        vc = k.key_col ? k.r->col0 : k.r->col1;
-    };
+    // not four -- is that array: its keys, low words and runs serve both.
+    const struct { const mj_rel* r; int key_col; } src[4] = {{&R, 1}, {&S, 0}, {&S, 1}, {&T, 0}};
+    unsigned long long** keys[4] = {&L.Rk, &L.Sk, &L.Sk2, &L.Tk};
+    uint32_t** low[4] = {&L.Rl, &L.Sl, &L.Sl2, &L.Tl};
+    RunBuf* runs[4] = {&L.R, &L.S, &L.S2, &L.T};
+    int rep[4];
+    SortSpec sort[4];
+    int nsort = 0;
     for (int i = 0; i < 4; ++i) {
-        const uint32_t *ki, *vi;
-        cols(src[i], ki, vi);
-        int same = -1;
-        for (int j = 0; j < i && same < 0; ++j) {
-            const uint32_t *kj, *vj;
-            cols(src[j], kj, vj);
-            if (ki == kj && vi == vj && src[i].r->stride == src[j].r->stride && src[i].r->n == src[j].r->n)
-                same = j;
-        }
-        const uint64_t n = src[i].r->n;
-        if (same >= 0) {
-            if (n)
-                MJ_LAUNCHM(prof, "k_copy_u64", k_copy_u64, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s,
-                           src[i].dst, src[same].dst, n);
+        auto cols = [&](int k) {
+            return std::make_tuple(src[k].key_col ? src[k].r->col1 : src[k].r->col0,
+                                   src[k].key_col ? src[k].r->col0 : src[k].r->col1, src[k].r->stride, src[k].r->n);
+        };
+        rep[i] = i;
+        for (int j = 0; j < i && rep[i] == i; ++j)
+            if (cols(i) == cols(j)) rep[i] = j;
+        if (rep[i] != i) {
+            if (!runs[rep[i]]->dir) runs[rep[i]]->dir = runs[i]->dir;
             continue;
         }
-        if ((st = tri_keys(prof, *src[i].r, src[i].key_col, src[i].dst, seed, s))) return st;
-        if ((st = launch_radix_sort(prof, src[i].dst, L.tmp, n, L.rs_hist, L.rs_counts, L.rs_starts, s)))
-            return st;
+        sort[nsort] = {src[i].r, src[i].key_col, false, *keys[i], L.tmp[nsort], L.rs_hist[nsort], L.rs_counts + 256 * nsort};
+        ++nsort;
     }
+    if ((st = launch_sorts(prof, sort, nsort, p.seed, first_pass, s))) return st;
     // lists of R per B and of T per C; groups of S per B and per C
-    if ((st = launch_runs(prof, L, L.Rk, R.n, L.R, L.Rl, s))) return st;
-    if ((st = launch_runs(prof, L, L.Tk, T.n, L.T, L.Tl, s))) return st;
-    if ((st = launch_runs(prof, L, L.Sk, S.n, L.S, L.Sl, s))) return st;
-    if ((st = launch_runs(prof, L, L.Sk2, S.n, L.S2, L.Sl2, s))) return st;
+    RunSpec run[4];
+    int nrun = 0;
+    for (int i = 0; i < 4; ++i)
+        if (rep[i] == i) run[nrun++] = {*keys[i], src[i].r->n, *runs[i], *low[i]};
+    if ((st = launch_runs(prof, run, nrun, s, L.ctr, 2 * TRI_CTR_WORDS, out))) return st;
+    for (int i = 0; i < 4; ++i)
+        if (rep[i] != i) {
+            *keys[i] = *keys[rep[i]];
+            *low[i] = *low[rep[i]];
+            *runs[i] = *runs[rep[i]];
+        }
     // work queues of the two passes
+    TriClassifyPair C;
+    C.per = grid_for(S.n, 1024, 2048);
     for (int q = 0; q < 2; ++q) {
         const PassBuf& P = L.P[q];
-        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(256), 0, s, P.ctr, (uint64_t)TRI_CTR_WORDS, 0u);
-        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(grid_for(P.n_heavy_cap, 256, 4096)), dim3(256), 0, s,
-                  P.heavy_items, (uint64_t)P.n_heavy_cap, 0u);
-        TriClassifyArgs C;
-        C.Stg = run_index(q == 0 ? L.R : L.T);
-        C.Grp = run_index(q == 0 ? L.S : L.S2);
-        C.share = 1u << p.log2_share;
-        C.nlight = P.ctr + 0; C.light = P.light;
-        C.nheavy_groups = P.ctr + 2; C.heavy_group = P.heavy_group; C.heavy_items = P.heavy_items;
-        MJ_LAUNCHM(prof, "k_tri_classify", k_tri_classify, dim3(grid_for(S.n, 1024, 4096)), dim3(256), 0, s, C);
-        if ((st = launch_scan_u32(prof, P.heavy_items, P.n_heavy_cap, L.partial, P.heavy_off, s))) return st;
+        C.pass[q].Stg = run_index(q == 0 ? L.R : L.T);
+        C.pass[q].Grp = run_index(q == 0 ? L.S : L.S2);
+        C.pass[q].share = 1u << p.log2_share;
+        C.pass[q].nlight = P.ctr; C.pass[q].light = P.light;
+        C.pass[q].heavy = reinterpret_cast<unsigned long long*>(P.ctr + 2);
+        C.pass[q].heavy_group = P.heavy_group; C.pass[q].heavy_off = P.heavy_off;
     }
+    MJ_LAUNCHM(prof, "k_tri_classify", k_tri_classify, dim3(2 * C.per), dim3(256), 0, s, C);
     return MJ_OK;
 }
 
 // pass 0 stages R's lists per B (groups: S by B, iterated: T's lists per C,
 // taken when strictly shorter); pass 1 stages T's lists per C (groups: S by
 // C, iterated: R's lists per B, taken when not longer)
-TriJoinArgs tri_join_args(const TriLayout& L, const mj_plan_t& p, unsigned long long* out, int pass) {
+TriJoinArgs tri_join_args(const TriLayout& L, const mj_plan_t& p, uint32_t first_pass, unsigned long long* out,
+                          int pass) {
     TriJoinArgs J;
+    J.low_bits = 8 * first_pass;
     const PassBuf& P = L.P[pass];
     J.Stg = run_index(pass == 0 ? L.R : L.T);
     J.Grp = run_index(pass == 0 ? L.S : L.S2);
@@ -962,10 +1007,22 @@ TriJoinArgs tri_join_args(const TriLayout& L, const mj_plan_t& p, unsigned long 
     J.Grpl = pass == 0 ? L.Sl : L.Sl2;
     J.Itrl = pass == 0 ? L.Tl : L.Rl;
     J.strict = pass == 0 ? 1u : 0u;
-    J.nlight = P.ctr + 0; J.light = P.light; J.light_next = P.ctr + TRI_QUEUE_PAD;
-    J.heavy_group = P.heavy_group; J.heavy_off = P.heavy_off; J.n_heavy_cap = P.n_heavy_cap;
-    J.heavy_next = P.ctr + 3; J.share = 1u << p.log2_share; J.total = out;
+    J.nlight = P.ctr; J.light = P.light; J.light_next = P.ctr + TRI_QUEUE_PAD;
+    J.heavy = reinterpret_cast<unsigned long long*>(P.ctr + 2);
+    J.heavy_group = P.heavy_group; J.heavy_off = P.heavy_off;
+    J.heavy_next = P.ctr + 1; J.share = 1u << p.log2_share; J.total = out;
     return J;
+}
+
+// both passes' light groups, then their heavy ones
+int tri_join(Prof* prof, int num_cu, const TriLayout& L, const mj_plan_t& p, uint32_t first_pass,
+             unsigned long long* out, hipStream_t s) {
+    TriJoinPair J;
+    for (int pass = 0; pass < 2; ++pass) J.pass[pass] = tri_join_args(L, p, first_pass, out, pass);
+    MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3((uint32_t)num_cu * TRI_LIGHT_PER_CU), dim3(TRI_THREADS), 0, s, J);
+    MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)num_cu * TRI_HEAVY_PER_CU), dim3(TRI_HEAVY_THREADS), 0,
+               s, J);
+    return MJ_OK;
 }
 
 int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel* T, uint64_t* out,
@@ -980,12 +1037,11 @@ int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
     MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, total, (uint64_t)1, 0ull);
     if (R->n == 0 || S->n == 0 || T->n == 0 || p.join2_size == 0) return MJ_OK;
     // join 2's side: T as sorted (m(c), m(a)) keys with its lists per C
-    int st = tri_keys(prof, *T, 0, L.Tk, p.seed, s);
+    const SortSpec sort = {T, 0, false, L.Tk, L.tmp, L.rs_hist, L.rs_counts};
+    int st = launch_sorts(prof, &sort, 1, p.seed, 0, s);
     if (st) return st;
-    if ((st = launch_radix_sort(prof, L.Tk, L.tmp, T->n, L.rs_hist, L.rs_counts, L.rs_starts, s))) return st;
-    TriLayout TL{};                    // launch_runs only uses flags / ridx / partial
-    TL.flags = L.flags; TL.ridx = L.ridx; TL.partial = L.partial;
-    if ((st = launch_runs(prof, TL, L.Tk, T->n, L.Trun, nullptr, s))) return st;
+    const RunSpec run = {L.Tk, T->n, L.Trun, nullptr};
+    if ((st = launch_runs(prof, &run, 1, s))) return st;
     // join 1: as in the linear cascade
     const uint32_t nb = 1u << p.log2_nb;
     PartLaunch P{};
@@ -1219,13 +1275,9 @@ int run_star_cascade(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
 struct FmLayout {
     unsigned long long* Tk;
     unsigned long long* Sk;
-    unsigned long long* tmp;
-    uint32_t* rs_hist;
-    uint32_t* rs_counts;
-    uint32_t* rs_starts;
-    uint32_t* flags;
-    unsigned long long* ridx;
-    unsigned long long* partial;
+    unsigned long long* tmp[2];
+    uint32_t* rs_hist[2];
+    uint32_t* rs_counts;              // [2][256]
     RunBuf T, S;
     uint32_t* tsk;                    // [T runs][FM_WORDS]
     uint32_t* wsk;                    // [S runs][FM_WORDS]
@@ -1251,17 +1303,14 @@ void fm_ranges(uint64_t n_r, uint32_t a_domain, uint32_t& bits, uint32_t& shift,
 FmLayout fm_layout(void* ws, uint64_t nr, uint64_t ns, uint64_t nt, uint32_t a_domain) {
     Bump B(ws);
     FmLayout L{};
-    const uint64_t nmax = std::max<uint64_t>({nr, ns, nt, 1});
     L.Tk = B.take<unsigned long long>(std::max<uint64_t>(nt, 1));
     L.Sk = B.take<unsigned long long>(std::max<uint64_t>(ns, 1));
-    L.tmp = B.take<unsigned long long>(nmax);
-    const uint64_t ntiles = (nmax + RS_TILE - 1) / RS_TILE;
-    L.rs_hist = B.take<uint32_t>(256 * ntiles);
-    L.rs_counts = B.take<uint32_t>(256);
-    L.rs_starts = B.take<uint32_t>(257);
-    L.flags = B.take<uint32_t>(nmax);
-    L.ridx = B.take<unsigned long long>(nmax + 1);
-    L.partial = B.take<unsigned long long>((nmax + SCAN_TILE - 1) / SCAN_TILE + 1);
+    for (int i = 0; i < 2; ++i) {
+        const uint64_t n = std::max<uint64_t>(i ? ns : nt, 1);
+        L.tmp[i] = B.take<unsigned long long>(n);
+        L.rs_hist[i] = B.take<uint32_t>(256 * rs_tiles(n));
+    }
+    L.rs_counts = B.take<uint32_t>(2 * 256);
     take_runs(B, L.T, nt, true);
     take_runs(B, L.S, ns, true);
     L.tsk = B.take<uint32_t>(std::max<uint64_t>(nt, 1) * FM_WORDS);
@@ -1352,7 +1401,7 @@ int run_dense(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, con
 // --------------------------------------------- degree-oriented cyclic join
 struct OrientLayout {
     unsigned long long *K, *K2, *tmp;  // sorted degrees: the keys (m(u), m(v)) and the sort's buffers
-    uint32_t *rs_hist, *rs_counts, *rs_starts;
+    uint32_t *rs_hist[2], *rs_counts;
     RunBuf U;
     RelPart V;                         // dense ids: the first ends by range of id ...
     uint32_t* vkeys;
@@ -1389,9 +1438,8 @@ OrientLayout orient_layout(void* ws, uint64_t n, bool with_check, uint32_t vdom 
         L.K = B.take<unsigned long long>(m);
         L.K2 = with_check ? B.take<unsigned long long>(m) : nullptr;
         L.tmp = B.take<unsigned long long>(m);
-        L.rs_hist = B.take<uint32_t>(256 * ((m + RS_TILE - 1) / RS_TILE));
-        L.rs_counts = B.take<uint32_t>(256);
-        L.rs_starts = B.take<uint32_t>(257);
+        for (int i = 0; i < 2; ++i) L.rs_hist[i] = i == 0 || with_check ? B.take<uint32_t>(256 * rs_tiles(m)) : nullptr;
+        L.rs_counts = B.take<uint32_t>(2 * 256);
         take_runs(B, L.U, n, true);
     }
     L.flags = B.take<uint32_t>(m);
@@ -1426,10 +1474,9 @@ size_t oriented_bytes(const mj_plan_t& p) {
 int symmetric_simple(Prof* prof, const mj_rel& E, uint32_t seed, void* ws, bool& yes, hipStream_t s) {
     OrientLayout L = orient_layout(ws, E.n, true);
     int st;
-    if ((st = tri_keys(prof, E, 0, L.K, seed, s))) return st;
-    if ((st = tri_keys(prof, E, 1, L.K2, seed, s))) return st;
-    if ((st = launch_radix_sort(prof, L.K, L.tmp, E.n, L.rs_hist, L.rs_counts, L.rs_starts, s))) return st;
-    if ((st = launch_radix_sort(prof, L.K2, L.tmp, E.n, L.rs_hist, L.rs_counts, L.rs_starts, s))) return st;
+    const SortSpec sort[2] = {{&E, 0, false, L.K, L.tmp, L.rs_hist[0], L.rs_counts},
+                              {&E, 1, false, L.K2, L.ridx, L.rs_hist[1], L.rs_counts + 256}};
+    if ((st = launch_sorts(prof, sort, 2, seed, 0, s))) return st;
     MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, L.err, (uint64_t)1, 0u);
     MJ_LAUNCH(prof, "k_sym_check", k_sym_check, dim3(grid_for(E.n, 256, 8192)), dim3(256), 0, s, L.K, L.K2,
               E.n, L.err);
@@ -1472,12 +1519,10 @@ int run_oriented(Prof* prof, int num_cu, const mj_rel& Erel, const mj_plan_t& p,
                   dim3(grid_for((Erel.n + 3) / 4, 256, 16384)), dim3(256), 0, s, A);
     } else {
         // degrees: runs of m(u) over the relation (grouped on the high word)
-        if ((st = tri_keys(prof, Erel, 0, O.K, p.seed, s))) return st;
-        if ((st = launch_radix_sort(prof, O.K, O.tmp, Erel.n, O.rs_hist, O.rs_counts, O.rs_starts, s, 4)))
-            return st;
-        TriLayout TL{};
-        TL.flags = O.flags; TL.ridx = O.ridx; TL.partial = O.partial;
-        if ((st = launch_runs(prof, TL, O.K, Erel.n, O.U, nullptr, s))) return st;
+        const SortSpec sort = {&Erel, 0, false, O.K, O.tmp, O.rs_hist[0], O.rs_counts};
+        if ((st = launch_sorts(prof, &sort, 1, p.seed, 4, s))) return st;
+        const RunSpec run = {O.K, Erel.n, O.U, nullptr};
+        if ((st = launch_runs(prof, &run, 1, s))) return st;
         A.U = run_index(O.U);
         MJ_LAUNCHM(prof, "k_orient_flags", k_orient_flags, dim3(grid_for((Erel.n + 1) / 2, 256, 16384)),
                   dim3(256), 0, s, A);
@@ -1493,14 +1538,11 @@ int run_oriented(Prof* prof, int num_cu, const mj_rel& Erel, const mj_plan_t& p,
     Rp = Sp;
     std::swap(Rp.col0, Rp.col1);
     if (q.n_s) {
-        if ((st = tri_prepare(prof, num_cu, Rp, Sp, Sp, q, L, out, s))) return st;
-        const uint32_t persistent = (uint32_t)num_cu * TRI_LIGHT_PER_CU;
-        for (int pass = 0; pass < 2; ++pass) {
-            TriJoinArgs J = tri_join_args(L, q, out, pass);
-            MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
-            MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)num_cu * TRI_HEAVY_PER_CU), dim3(TRI_HEAVY_THREADS), 0, s,
-                      J);
-        }
+        // the kept edges repeat no entry: their lists need only the order of
+        // the low words' top 16 bits
+        constexpr uint32_t first_pass = 2;
+        if ((st = tri_prepare(prof, Rp, Sp, Sp, q, L, first_pass, out, s))) return st;
+        if ((st = tri_join(prof, num_cu, L, q, first_pass, out, s))) return st;
     }
     MJ_LAUNCHM(prof, "k_orient_finish", k_orient_finish, dim3(1), dim3(64), 0, s, A, q.n_s);
     return MJ_OK;
@@ -1508,10 +1550,9 @@ int run_oriented(Prof* prof, int num_cu, const mj_rel& Erel, const mj_plan_t& p,
 
 // --------------------------------------------------- materialised linear join
 struct EmitLayout {
-    unsigned long long *Sk, *Tk, *tmp;
-    uint32_t *rs_hist, *rs_counts, *rs_starts;
-    uint32_t* flags;
-    unsigned long long *ridx, *partial;
+    unsigned long long *Sk, *Tk, *tmp[2];
+    uint32_t *rs_hist[2], *rs_counts;
+    unsigned long long* partial;
     RunBuf S, T;
     uint32_t *sc, *td, *tdeg, *tst, *sst, *pdeg;
     unsigned long long *P_S, *wout, *O_I, *O_R;
@@ -1525,13 +1566,12 @@ EmitLayout emit_layout(void* ws, uint64_t nr, uint64_t ns, uint64_t nt) {
     const uint64_t nmax = std::max<uint64_t>({nr, ns, nt, 1});
     L.Sk = B.take<unsigned long long>(std::max<uint64_t>(ns, 1));
     L.Tk = B.take<unsigned long long>(std::max<uint64_t>(nt, 1));
-    L.tmp = B.take<unsigned long long>(nmax);
-    const uint64_t ntiles = (nmax + RS_TILE - 1) / RS_TILE;
-    L.rs_hist = B.take<uint32_t>(256 * ntiles);
-    L.rs_counts = B.take<uint32_t>(256);
-    L.rs_starts = B.take<uint32_t>(257);
-    L.flags = B.take<uint32_t>(nmax);
-    L.ridx = B.take<unsigned long long>(nmax + 1);
+    for (int i = 0; i < 2; ++i) {
+        const uint64_t n = std::max<uint64_t>(i ? ns : nt, 1);
+        L.tmp[i] = B.take<unsigned long long>(n);
+        L.rs_hist[i] = B.take<uint32_t>(256 * rs_tiles(n));
+    }
+    L.rs_counts = B.take<uint32_t>(2 * 256);
     L.partial = B.take<unsigned long long>((nmax + SCAN_TILE - 1) / SCAN_TILE + 1);
     take_runs(B, L.S, ns, true);
     take_runs(B, L.T, nt, true);
@@ -2047,16 +2087,12 @@ int mj_triangle3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_r
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prof* prof = &ctx->prof;
     unsigned long long* out = reinterpret_cast<unsigned long long*>(total);
-    MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, out, (uint64_t)1, 0ull);
-    if (R->n == 0 || S->n == 0 || T->n == 0) return MJ_OK;
-    if ((st = tri_prepare(prof, ctx->num_cu, *R, *S, *T, p, L, out, s))) return st;
-    const uint32_t persistent = (uint32_t)ctx->num_cu * TRI_LIGHT_PER_CU;
-    for (int pass = 0; pass < 2; ++pass) {
-        TriJoinArgs J = tri_join_args(L, p, out, pass);
-        MJ_LAUNCHM(prof, "k_tri_light", k_tri_light, dim3(persistent), dim3(TRI_THREADS), 0, s, J);
-        MJ_LAUNCHM(prof, "k_tri_heavy", k_tri_heavy, dim3((uint32_t)ctx->num_cu * TRI_HEAVY_PER_CU), dim3(TRI_HEAVY_THREADS), 0, s, J);
+    if (R->n == 0 || S->n == 0 || T->n == 0) {
+        MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, out, (uint64_t)1, 0ull);
+        return MJ_OK;
     }
-    return MJ_OK;
+    if ((st = tri_prepare(prof, *R, *S, *T, p, L, 0, out, s))) return st;
+    return tri_join(prof, ctx->num_cu, L, p, 0, out, s);
 }
 
 int mj_cascade2_count(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, const mj_rel* T,
@@ -2191,23 +2227,21 @@ int mj_linear3_distinct(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_
                       reinterpret_cast<unsigned long long*>(est), (uint64_t)a_domain, 0ull);   // 0.0
         return MJ_OK;
     }
-    TriLayout TL{};                    // launch_runs only uses flags / ridx / partial
-    TL.flags = L.flags; TL.ridx = L.ridx; TL.partial = L.partial;
-    // T grouped by C: (mix(c), mix(d)) sorted; per run the OR of bit(mix(d))
-    if ((st = tri_keys(prof, *T, 0, L.Tk, seed, s))) return st;
-    // (only the grouping by the high word matters to an OR of sketches)
-    if ((st = launch_radix_sort(prof, L.Tk, L.tmp, T->n, L.rs_hist, L.rs_counts, L.rs_starts, s, 4))) return st;
-    if ((st = launch_runs(prof, TL, L.Tk, T->n, L.T, nullptr, s))) return st;
+    // T grouped by C as (mix(c), mix(d)) and S by B as (mix(b), mix(c)): only
+    // the grouping by the high word matters to an OR of sketches
+    const SortSpec sort[2] = {{T, 0, false, L.Tk, L.tmp[0], L.rs_hist[0], L.rs_counts},
+                              {S, 0, false, L.Sk, L.tmp[1], L.rs_hist[1], L.rs_counts + 256}};
+    if ((st = launch_sorts(prof, sort, 2, seed, 4, s))) return st;
+    const RunSpec run[2] = {{L.Tk, T->n, L.T, nullptr}, {L.Sk, S->n, L.S, nullptr}};
+    if ((st = launch_runs(prof, run, 2, s))) return st;
+    // per run of T the OR of bit(mix(d))
     FmTArgs Ft;
     Ft.T = run_index(L.T); Ft.Tk = L.Tk; Ft.tsk = L.tsk;
     MJ_LAUNCH(prof, "k_fm_tsketch", k_fm_tsketch, dim3(grid_for(T->n, FM_THREADS, 16384)), dim3(FM_THREADS),
               0, s, Ft);
     MJ_LAUNCH(prof, "k_fm_tsketch_long", k_fm_tsketch_long, dim3(grid_for(T->n, FM_THREADS, 4096)),
               dim3(FM_THREADS), 0, s, Ft);
-    // S grouped by B: per run the OR of T's sketches of its C values
-    if ((st = tri_keys(prof, *S, 0, L.Sk, seed, s))) return st;
-    if ((st = launch_radix_sort(prof, L.Sk, L.tmp, S->n, L.rs_hist, L.rs_counts, L.rs_starts, s, 4))) return st;
-    if ((st = launch_runs(prof, TL, L.Sk, S->n, L.S, nullptr, s))) return st;
+    // per run of S the OR of T's sketches of its C values
     FmWArgs Fw;
     Fw.S = run_index(L.S); Fw.Sk = L.Sk; Fw.T = run_index(L.T); Fw.tsk = L.tsk; Fw.wsk = L.wsk;
     MJ_LAUNCH(prof, "k_fm_wsketch", k_fm_wsketch, dim3(grid_for(S->n, FM_THREADS, 16384)), dim3(FM_THREADS),
@@ -2261,16 +2295,13 @@ int mj_linear3_materialize(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const 
     }
     // the seed only groups equal keys; the output order does not depend on it
     const uint32_t seed = 0x2545F491u;
-    TriLayout TL{};                    // launch_runs only uses flags / ridx / partial
-    TL.flags = L.flags; TL.ridx = L.ridx; TL.partial = L.partial;
     // T grouped by C with its raw D values, S by B with its raw C values; the
     // sort is stable, so every run keeps its relation's order
-    if ((st = tri_keys(prof, *T, 0, L.Tk, seed, s, true))) return st;
-    if ((st = launch_radix_sort(prof, L.Tk, L.tmp, T->n, L.rs_hist, L.rs_counts, L.rs_starts, s, 4))) return st;
-    if ((st = launch_runs(prof, TL, L.Tk, T->n, L.T, L.td, s))) return st;
-    if ((st = tri_keys(prof, *S, 0, L.Sk, seed, s, true))) return st;
-    if ((st = launch_radix_sort(prof, L.Sk, L.tmp, S->n, L.rs_hist, L.rs_counts, L.rs_starts, s, 4))) return st;
-    if ((st = launch_runs(prof, TL, L.Sk, S->n, L.S, L.sc, s))) return st;
+    const SortSpec sort[2] = {{T, 0, true, L.Tk, L.tmp[0], L.rs_hist[0], L.rs_counts},
+                              {S, 0, true, L.Sk, L.tmp[1], L.rs_hist[1], L.rs_counts + 256}};
+    if ((st = launch_sorts(prof, sort, 2, seed, 4, s))) return st;
+    const RunSpec run[2] = {{L.Tk, T->n, L.T, L.td}, {L.Sk, S->n, L.S, L.sc}};
+    if ((st = launch_runs(prof, run, 2, s))) return st;
     EmitSArgs Es;
     Es.sc = L.sc; Es.ns = S->n; Es.T = run_index(L.T); Es.seed = seed; Es.tdeg = L.tdeg; Es.tst = L.tst;
     MJ_LAUNCH(prof, "k_emit_sdeg", k_emit_sdeg, dim3(grid_for((S->n + 3) / 4, 256, 16384)), dim3(256), 0, s, Es);
@@ -2471,12 +2502,14 @@ static int record_batch(mj_ctx* ctx, const mj_batch_item* items, int n, char* ba
             st = [&]() -> int {
                 TriLayout L = tri_layout(wsi, p);
                 unsigned long long* out = reinterpret_cast<unsigned long long*>(it.out);
-                MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, out, (uint64_t)1, 0ull);
-                if (it.R.n == 0 || it.S.n == 0 || it.T.n == 0) return MJ_OK;
+                if (it.R.n == 0 || it.S.n == 0 || it.T.n == 0) {
+                    MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, out, (uint64_t)1, 0ull);
+                    return MJ_OK;
+                }
                 int e;
-                if ((e = tri_prepare(prof, ctx->num_cu, it.R, it.S, it.T, p, L, out, s))) return e;
-                B.tri.push_back(tri_join_args(L, p, out, 0));
-                B.tri.push_back(tri_join_args(L, p, out, 1));
+                if ((e = tri_prepare(prof, it.R, it.S, it.T, p, L, 0, out, s))) return e;
+                B.tri.push_back(tri_join_args(L, p, 0, out, 0));
+                B.tri.push_back(tri_join_args(L, p, 0, out, 1));
                 return MJ_OK;
             }();
         }

@@ -125,6 +125,12 @@ __device__ __forceinline__ bool wave_fold_first(uint32_t key, bool act, T& v) {
 __device__ __forceinline__ void handoff_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
 __device__ __forceinline__ void handoff_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 
+// Orders a wave's own LDS accesses before and after it.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Read tuple component from a strided column.
 __device__ __forceinline__ uint32_t ld_col(const uint32_t* __restrict__ col, uint64_t i,
                                            int64_t stride) {

@@ -580,29 +580,37 @@ MJ_KERNEL_DECL(k_scan_one, ScanArgs);
 MJ_KERNEL_DECL(k_scan_one64, Scan64Args);
 
 // ------------------------------------------------------------- radix sort
-constexpr int RS_THREADS = 256;
+constexpr int RS_THREADS = 512;
 constexpr int RS_TILE = 4096;
-struct RsArgs {
-    const unsigned long long* in;
-    unsigned long long* out;
-    uint64_t n;
-    uint32_t shift;              // digit = (key >> shift) & 255
-    uint32_t ntiles;
-    uint32_t* hist;              // [256][ntiles]
-    const uint32_t* starts;      // [257] digit starts
-};
-MJ_KERNEL_DECL(k_rs_hist, RsArgs);
-MJ_KERNEL_DECL(k_rs_scatter, RsArgs);
-// small arrays: the whole sort in one workgroup, or one scan launch per pass
+constexpr int RS_MAX_JOBS = 4;
+constexpr uint32_t RS_SELF_TILES = 32;       // at most this many tiles: the scatter adds up the histogram rows
+// small arrays: the whole sort in one workgroup
 constexpr uint32_t RS_SMALL_BITS = 14;
 constexpr uint32_t RS_SMALL = 1u << RS_SMALL_BITS;   // keys sorted whole in LDS
 constexpr int RS_SMALL_THREADS = 1024;
-constexpr uint32_t RS_SCAN1_TILES = 32;              // tiles scanned by one workgroup
 static_assert(size_t(RS_SMALL) * 8 <= LDS_BYTES && RS_SMALL_BITS <= 16, "small sort shape");
-struct RsSmallArgs { unsigned long long* keys; uint32_t n; uint32_t shift; };
-struct RsScan1Args { RsArgs rs; uint32_t* starts; };
-MJ_KERNEL_DECL(k_rs_small, RsSmallArgs);
-MJ_KERNEL_DECL(k_rs_scan1, RsScan1Args);
+static_assert(RS_TILE % RS_THREADS == 0 && RS_THREADS >= 256, "a thread per digit");
+struct RsJob {
+    const uint32_t* key_col = nullptr;   // set: keys made from the columns (the first pass)
+    const uint32_t* val_col = nullptr;
+    int64_t stride = 0;
+    uint32_t seed = 0, raw_low = 0;      // raw_low: the low word is the other value itself, not its mix
+    const unsigned long long* in = nullptr;
+    unsigned long long* out = nullptr;
+    uint64_t n = 0;
+    uint32_t* hist = nullptr;            // [256][ntiles]
+    uint32_t* counts = nullptr;          // [256] digit totals (when the rows are scanned)
+    uint32_t ntiles = 0, tile_begin = 0;
+};
+struct RsLaunch {
+    RsJob job[RS_MAX_JOBS];
+    int njobs = 0;
+    uint32_t shift = 0;                  // digit = (key >> shift) & 255
+    uint32_t rows = 0;                   // the histogram rows hold prefixes over tiles, counts the totals
+};
+MJ_KERNEL_DECL(k_rs_hist, RsLaunch);
+MJ_KERNEL_DECL(k_rs_scatter, RsLaunch);
+MJ_KERNEL_DECL(k_rs_small, RsLaunch);
 
 // --------------------------------------------------------------- triangle
 constexpr int TRI_THREADS = 256;           // light kernel: one staged list per wave
@@ -619,7 +627,7 @@ constexpr uint32_t TRI_SHORT_LIST = 16;    // lists walked by one lane
 constexpr uint32_t TRI_LIGHT_PER_CU = 6;   // workgroups of the light kernel that fit a CU (LDS)
 constexpr uint32_t TRI_QUEUES = 32;        // queues of light items, their counters
 constexpr uint32_t TRI_QUEUE_PAD = 32;     // this many words apart (a cache line each)
-constexpr uint32_t TRI_CTR_WORDS = TRI_QUEUE_PAD * (1 + TRI_QUEUES);   // nlight, -, nheavy_groups, heavy_next; queues
+constexpr uint32_t TRI_CTR_WORDS = TRI_QUEUE_PAD * (1 + TRI_QUEUES);   // nlight, heavy_next, heavy (64 bits); queues
 
 struct RunIndex {                          // runs of equal high words of sorted keys
     const uint32_t* run_key;               // [nruns]
@@ -739,16 +747,6 @@ __global__ void k_fm_asketch(FmAArgs A);         // range mode: writes sketches 
 __global__ void k_fm_asketch_global(FmAArgs A);  // global mode: ORs into the zeroed output
 __global__ void k_fm_estimate(FmAArgs A);        // global mode: estimates
 
-struct TriKeyArgs {
-    const uint32_t* key_col;
-    const uint32_t* val_col;
-    int64_t stride;
-    uint64_t n;
-    uint32_t seed;
-    uint32_t raw_low;              // 1: the low word is the value itself, not its mix
-    unsigned long long* out;
-};
-
 // One pass of the cyclic join: the lists of the staged relation (R per B,
 // or T per C) are loaded into LDS one group at a time; the groups come from
 // S sorted by that same attribute; each s of a group whose iterated list
@@ -761,10 +759,13 @@ struct TriClassifyArgs {
     uint32_t share;
     uint32_t* nlight;
     uint2* light;                          // (group, run of its staged list)
-    uint32_t* nheavy_groups;
+    unsigned long long* heavy;             // heavy groups << HEAVY_SHIFT | their items
     uint32_t* heavy_group;
-    uint32_t* heavy_items;
+    unsigned long long* heavy_off;         // items before each heavy group
 };
+constexpr int HEAVY_SHIFT = 40;
+// both passes of a join in one launch: the first `per` workgroups take pass 0
+struct TriClassifyPair { TriClassifyArgs pass[2]; uint32_t per; };
 
 struct TriJoinArgs {
     RunIndex Stg, Grp, Itr;
@@ -775,13 +776,16 @@ struct TriJoinArgs {
     const uint32_t* nlight;
     const uint2* light;
     uint32_t* light_next;                  // [TRI_QUEUES] counters, TRI_QUEUE_PAD words apart
+    const unsigned long long* heavy;       // heavy groups << HEAVY_SHIFT | their items
     const uint32_t* heavy_group;
     const unsigned long long* heavy_off;
-    uint32_t n_heavy_cap;
     uint32_t* heavy_next;
     uint32_t share;
+    uint32_t low_bits;                     // lists are ordered by their words' bits from low_bits up (at most 16)
     unsigned long long* total;
 };
+static_assert(32 - TRI_LIGHT_DIR_BITS >= 16, "a light bucket is no finer than the order of the lists");
+struct TriJoinPair { TriJoinArgs pass[2]; };
 
 struct CasProbeTriArgs {
     const uint2* I;                   // (a, c) pairs of R |x| S
@@ -811,28 +815,39 @@ struct LinearBatchArgs {
 };
 __global__ void k_linear_cell_batch(LinearBatchArgs B);
 
-MJ_KERNEL_DECL(k_tri_keys, TriKeyArgs);
-// runs of equal high words of sorted keys: flags of run heads (and the low
-// words, when `low` is set), then each head's run start and key, then a
-// directory of the runs by the top `bits` bits of their keys
-struct RunFlagsArgs { const unsigned long long* keys; uint64_t n; uint32_t* flags; uint32_t* low; };
-struct RunCompactArgs {
-    const unsigned long long* keys;
-    uint64_t n;
-    const uint32_t* flags;
-    const unsigned long long* ridx;   // [n + 1] exclusive scan of flags
-    uint32_t* run_key;
-    uint32_t* run_start;
-    unsigned long long* nruns;
+// runs of equal high words of sorted keys (RunIndex), up to RUN_MAX_JOBS
+// arrays per launch: heads per tile, then each run's start and key, the low
+// words (when `low` is set) and the directory (when `dir` is set): dir[p] =
+// first run whose key prefix (top `bits` bits) is >= p, p in [0, 2^bits]
+constexpr int RUN_MAX_JOBS = 4;
+constexpr int RUN_THREADS = 256;
+constexpr uint32_t RUN_TILE = 4096;
+constexpr uint32_t RUN_SELF_TILES = 1024;    // at most this many tiles: each adds up the counts before it
+struct RunJob {
+    const unsigned long long* keys = nullptr;
+    uint64_t n = 0;
+    uint32_t* low = nullptr;
+    uint32_t* run_key = nullptr;
+    uint32_t* run_start = nullptr;
+    uint32_t* dir = nullptr;
+    uint32_t bits = 0;
+    unsigned long long* nruns = nullptr;
+    uint32_t* part = nullptr;                // [ntiles + 1] heads per tile, or the heads before it
+    uint32_t ntiles = 0, tile_begin = 0;     // ntiles >= 1 (n = 0: one empty tile)
 };
-// dir[p] = first run whose key prefix (top `bits` bits) is >= p, p in [0, 2^bits]
-struct RunDirArgs { const uint32_t* run_key; const unsigned long long* nruns; uint32_t bits; uint32_t* dir; };
-MJ_KERNEL_DECL(k_run_flags, RunFlagsArgs);
-MJ_KERNEL_DECL(k_run_compact, RunCompactArgs);
-MJ_KERNEL_DECL(k_run_dir, RunDirArgs);
-MJ_KERNEL_DECL(k_tri_classify, TriClassifyArgs);
-MJ_KERNEL_DECL(k_tri_light, TriJoinArgs);
-MJ_KERNEL_DECL(k_tri_heavy, TriJoinArgs);
+struct RunLaunch {
+    RunJob job[RUN_MAX_JOBS];
+    int njobs = 0;
+    uint32_t scanned = 0;                    // part holds the heads before each tile
+    uint32_t* clear = nullptr;               // words the first launch sets to 0 (the caller's counters)
+    uint32_t nclear = 0;
+    unsigned long long* zero = nullptr;      // one more word set to 0
+};
+MJ_KERNEL_DECL(k_run_count, RunLaunch);
+MJ_KERNEL_DECL(k_run_emit, RunLaunch);
+MJ_KERNEL_DECL(k_tri_classify, TriClassifyPair);
+MJ_KERNEL_DECL(k_tri_light, TriJoinPair);
+MJ_KERNEL_DECL(k_tri_heavy, TriJoinPair);
 
 // ------------------------------------------------ materialised linear join
 // The result tuples (a, b, c, d) of R |x| S |x| T written out in nested-loop

@@ -1,118 +1,165 @@
 // Stable LSD radix sort of 64-bit keys (8-bit digits), the repeated radix
 // partitioning that groups each relation of the cyclic join by its join key
-// (Fig. 3 partitions by radix digits of A, B and C).
+// (Fig. 3 partitions by radix digits of A, B and C).  Up to RS_MAX_JOBS
+// arrays are sorted by the same launches, and the first pass makes the keys
+// from the relations' columns, so no unsorted key array is written.
 //
 //   k_rs_hist    : per tile, digit histogram -> column `tile` of hist[d][tile]
-//   (k_part_rowscan / k_part_scan give every (digit, tile) its output start)
-//   k_rs_scatter : per tile, stable ranks: the tile is walked in rounds of
-//                  blockDim keys in input order; inside a round the rank of a
-//                  key among equal digits is its position among the wave's
-//                  matching lanes (found with eight ballots) plus the counts
-//                  of earlier waves and earlier rounds.
-//   k_rs_scan1   : with few tiles, one workgroup does both scans of a pass
+//   (k_part_rowscan: each digit's prefix over tiles and its total; with at
+//   most RS_SELF_TILES tiles the scatter adds up the rows itself)
+//   k_rs_scatter : per tile, stable ranks, the tile put in digit order in LDS
+//                  and written out, each digit's run consecutive
 //   k_rs_small   : arrays of at most RS_SMALL keys are sorted whole in one
-//                  workgroup's LDS, in one launch instead of four per pass.
+//                  workgroup's LDS, in one launch.
 #include "mj_kernels.h"
 
 namespace mj {
 
-MJ_KERNEL(k_rs_hist, RS_THREADS, RsArgs) {
+// key i of a job: (mix(key) << 32 | mix(other)), or the other value itself as
+// low word, from the columns on the first pass; the stored key afterwards
+__device__ __forceinline__ unsigned long long rs_key(const RsJob& J, uint64_t i) {
+    if (!J.key_col) return J.in[i];
+    const uint32_t hi = ld_col(J.key_col, i, J.stride);
+    const uint32_t lo = ld_col(J.val_col, i, J.stride);
+    return ((unsigned long long)mix32(hi, J.seed) << 32) | (J.raw_low ? lo : mix32(lo, J.seed));
+}
+
+__device__ __forceinline__ int rs_find_job(const RsLaunch& L, uint32_t tile) {
+    int j = 0;
+#pragma unroll
+    for (int q = 1; q < RS_MAX_JOBS; ++q)
+        if (q < L.njobs && tile >= L.job[q].tile_begin) j = q;
+    return j;
+}
+
+MJ_KERNEL(k_rs_hist, RS_THREADS, RsLaunch) {
     __shared__ uint32_t lh[256];
-    const uint32_t tile = xcd_remap(vg.bid, vg.nblk);
+    const uint32_t blk = xcd_remap(vg.bid, vg.nblk);
+    const RsJob& J = A.job[rs_find_job(A, blk)];
+    const uint32_t tile = blk - J.tile_begin;
     for (uint32_t d = threadIdx.x; d < 256; d += blockDim.x) lh[d] = 0;
     __syncthreads();
     const uint64_t beg = uint64_t(tile) * RS_TILE;
-    const uint64_t end = min<uint64_t>(beg + RS_TILE, A.n);
-    for (uint64_t i = beg + threadIdx.x; i < end; i += blockDim.x)
-        atomicAdd(&lh[(uint32_t)(A.in[i] >> A.shift) & 255u], 1u);
+    constexpr int ITEMS = RS_TILE / RS_THREADS;
+    unsigned long long key[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const uint64_t i = beg + k * RS_THREADS + threadIdx.x;
+        key[k] = i < J.n ? rs_key(J, i) : 0ull;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k)
+        if (beg + k * RS_THREADS + threadIdx.x < J.n) atomicAdd(&lh[(uint32_t)(key[k] >> A.shift) & 255u], 1u);
     __syncthreads();
-    for (uint32_t d = threadIdx.x; d < 256; d += blockDim.x)
-        A.hist[uint64_t(d) * A.ntiles + tile] = lh[d];
+    for (uint32_t d = threadIdx.x; d < 256; d += blockDim.x) J.hist[uint64_t(d) * J.ntiles + tile] = lh[d];
 }
 
-MJ_KERNEL(k_rs_scatter, RS_THREADS, RsArgs) {
-    __shared__ uint32_t running[256];
-    __shared__ uint32_t wcnt[RS_THREADS / WAVE][256];
-    // adjacent tiles write adjacent runs of every digit: keep them on one XCD
-    const uint32_t tile = xcd_remap(vg.bid, vg.nblk);
+// exclusive prefix over the first 256 threads' values (four waves; all
+// threads of the workgroup call it, the others' results are unused)
+__device__ __forceinline__ uint32_t rs_scan256(uint32_t v, uint32_t* wsum) {
     const int lane = lane_id();
-    const int w = threadIdx.x / WAVE;
-    constexpr int NW = RS_THREADS / WAVE;
-    for (uint32_t d = threadIdx.x; d < 256; d += blockDim.x) {
-        running[d] = A.starts[d] + A.hist[uint64_t(d) * A.ntiles + tile];
-        for (int q = 0; q < NW; ++q) wcnt[q][d] = 0;
+    const uint32_t w = threadIdx.x / WAVE, x = v;
+#pragma unroll
+    for (int off = 1; off < WAVE; off <<= 1) {
+        const uint32_t y = __shfl_up(v, off, WAVE);
+        if (lane >= off) v += y;
     }
+    if (lane == WAVE - 1) wsum[w] = v;
     __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t q = 0; q < w && q < 4; ++q) before += wsum[q];
+    __syncthreads();
+    return before + v - x;
+}
+
+// A tile's keys stay in registers: wave w holds the tile's w-th part in input
+// order, 64 keys a round.  The rank of a key among the wave's equal digits is
+// the count of earlier rounds (an LDS counter per wave and digit) plus its
+// position among the round's matching lanes (eight ballots), so the rounds
+// need no barrier; the waves' counters are then added up per digit.  Writing
+// from the LDS stage, a digit's run is consecutive (about 16 keys, 128 bytes):
+// stores straight from registers are one L2 request a key.  Bound by HBM
+// traffic for large arrays (2^26 keys: 478 -> 310 us a pass against
+// the unstaged form with five barriers per 256 keys) and by the launch for
+// arrays of up to about 10^6.
+MJ_KERNEL(k_rs_scatter, RS_THREADS, RsLaunch) {
+    constexpr int NW = RS_THREADS / WAVE, ROUNDS = RS_TILE / RS_THREADS;
+    __shared__ unsigned long long stage[RS_TILE];
+    __shared__ uint16_t wcnt[NW][256];
+    __shared__ uint32_t lstart[256], gbase[256];
+    __shared__ uint32_t wsum[NW];
+    // adjacent tiles write adjacent runs of every digit: keep them on one XCD
+    const uint32_t blk = xcd_remap(vg.bid, vg.nblk);
+    const RsJob& J = A.job[rs_find_job(A, blk)];
+    const uint32_t tile = blk - J.tile_begin;
+    const uint32_t lane = lane_id(), w = threadIdx.x / WAVE;
     const uint64_t beg = uint64_t(tile) * RS_TILE;
-    const uint64_t end = min<uint64_t>(beg + RS_TILE, A.n);
-    const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (uint64_t r0 = beg; r0 < end; r0 += RS_THREADS) {
-        const uint64_t i = r0 + threadIdx.x;
-        const bool live = i < end;
-        const unsigned long long key = live ? A.in[i] : 0ull;
-        const uint32_t d = (uint32_t)(key >> A.shift) & 255u;
-        // lanes of this wave holding the same digit
-        unsigned long long peers = __ballot(live);
+    const uint32_t cnt = (uint32_t)min<uint64_t>(RS_TILE, J.n - beg);
+    const uint32_t at = w * (RS_TILE / NW) + lane;
+    unsigned long long key[ROUNDS];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) key[k] = at + k * WAVE < cnt ? rs_key(J, beg + at + k * WAVE) : 0ull;
+    for (uint32_t d = lane; d < 256; d += WAVE) wcnt[w][d] = 0;
+    // digit totals before this tile, and over all tiles
+    uint32_t pre = 0, tot = 0;
+    if (threadIdx.x < 256) {
+        const uint32_t* row = J.hist + uint64_t(threadIdx.x) * J.ntiles;
+        if (A.rows) {
+            pre = row[tile];
+            tot = J.counts[threadIdx.x];
+        } else {
+            for (uint32_t t = 0; t < J.ntiles; ++t) {
+                const uint32_t c = row[t];
+                pre += t < tile ? c : 0u;
+                tot += c;
+            }
+        }
+    }
+    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    uint16_t rank[ROUNDS];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        wave_fence();
+        const bool live = at + k * WAVE < cnt;
+        const uint32_t d = (uint32_t)(key[k] >> A.shift) & 255u;
+        unsigned long long peers = __ballot(live);          // lanes holding the same digit
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
             const unsigned long long bal = __ballot(live && ((d >> bit) & 1u));
             peers &= ((d >> bit) & 1u) ? bal : ~bal;
         }
-        const uint32_t rank_w = __popcll(peers & lt_mask);
-        const bool leader = live && rank_w == 0;
-        if (leader) wcnt[w][d] = __popcll(peers);
-        __syncthreads();
-        if (live) {
-            uint32_t before = 0;
-            for (int q = 0; q < w; ++q) before += wcnt[q][d];
-            A.out[running[d] + before + rank_w] = key;
-        }
-        __syncthreads();
-        if (leader) {
-            // the last wave holding digit d in this round advances running[d]
-            bool last = true;
-            for (int q = w + 1; q < NW; ++q) last = last && wcnt[q][d] == 0;
-            if (last) {
-                uint32_t tot = 0;
-                for (int q = 0; q < NW; ++q) tot += wcnt[q][d];
-                running[d] += tot;
-            }
-        }
-        __syncthreads();
-        if (leader) wcnt[w][d] = 0;
-        __syncthreads();
-    }
-}
-
-// One workgroup, at most RS_SCAN1_TILES tiles: every digit's row of the
-// histogram becomes its exclusive prefix over tiles (in place), and the
-// digits' totals their exclusive prefix (starts, with starts[256] = n):
-// what k_part_rowscan and k_part_scan write, in one launch.
-MJ_KERNEL(k_rs_scan1, 256, RsScan1Args) {
-    (void)vg;
-    const RsArgs& R = A.rs;
-    uint32_t* starts = A.starts;
-    __shared__ uint32_t h[256 * RS_SCAN1_TILES];
-    __shared__ uint32_t tot[256];
-    __shared__ uint32_t wave_tmp[256 / WAVE + 1];
-    const uint32_t nt = R.ntiles, m = 256 * nt;
-    for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) h[i] = R.hist[i];
-    __syncthreads();
-    {
-        const uint32_t d = threadIdx.x;          // one digit per thread
-        uint32_t run = 0;
-        for (uint32_t t = 0; t < nt; ++t) {
-            const uint32_t c = h[d * nt + t];
-            h[d * nt + t] = run;
-            run += c;
-        }
-        tot[d] = run;
+        const uint32_t mine = __popcll(peers & lt_mask);
+        const uint32_t before = wcnt[w][d];
+        rank[k] = (uint16_t)(before + mine);
+        wave_fence();
+        if (live && mine == 0) wcnt[w][d] = (uint16_t)(before + __popcll(peers));
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) R.hist[i] = h[i];
-    const uint32_t total = block_exclusive_scan(tot, 256, wave_tmp);
-    starts[threadIdx.x] = tot[threadIdx.x];
-    if (threadIdx.x == 0) starts[256] = total;
+    uint32_t local = 0;
+    if (threadIdx.x < 256)
+        for (int q = 0; q < NW; ++q) {
+            const uint32_t c = wcnt[q][threadIdx.x];
+            wcnt[q][threadIdx.x] = (uint16_t)local;
+            local += c;
+        }
+    const uint32_t ls = rs_scan256(local, wsum);
+    const uint32_t gs = rs_scan256(tot, wsum);
+    if (threadIdx.x < 256) {
+        lstart[threadIdx.x] = ls;
+        gbase[threadIdx.x] = gs + pre - ls;                 // (modulo 2^32)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        if (at + k * WAVE >= cnt) continue;
+        const uint32_t d = (uint32_t)(key[k] >> A.shift) & 255u;
+        stage[lstart[d] + wcnt[w][d] + rank[k]] = key[k];
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < cnt; i += RS_THREADS) {
+        const unsigned long long v = stage[i];
+        J.out[(uint32_t)(gbase[(uint32_t)(v >> A.shift) & 255u] + i)] = v;
+    }
 }
 
 // The keys ordered on their bits from `shift` up, ties in input order: the
@@ -122,10 +169,11 @@ MJ_KERNEL(k_rs_scan1, 256, RsScan1Args) {
 // the composites are sorted, and each position takes the key its index names
 // (kept in LDS beside them).  A bitonic network over the next power of two,
 // padded with the largest value; pads sort after every real entry.
-MJ_KERNEL(k_rs_small, RS_SMALL_THREADS, RsSmallArgs) {
-    (void)vg;
-    unsigned long long* keys = A.keys;
-    const uint32_t n = A.n, shift = A.shift;
+// One workgroup per job.
+MJ_KERNEL(k_rs_small, RS_SMALL_THREADS, RsLaunch) {
+    const RsJob& J = A.job[vg.bid];
+    unsigned long long* keys = J.out;
+    const uint32_t n = (uint32_t)J.n, shift = A.shift;
     extern __shared__ unsigned long long rs_lds[];
     uint32_t P = 2;
     while (P < n) P <<= 1;
@@ -135,7 +183,8 @@ MJ_KERNEL(k_rs_small, RS_SMALL_THREADS, RsSmallArgs) {
     for (uint32_t i = threadIdx.x; i < P; i += blockDim.x) {
         unsigned long long x = ~0ull;
         if (i < n) {
-            const unsigned long long k = keys[i];
+            const unsigned long long k = rs_key(J, i);
+            if (shift && J.key_col) keys[i] = k;            // gathered again below
             x = shift ? (((k >> shift) << RS_SMALL_BITS) | i) : k;
         }
         v[i] = x;

@@ -29,53 +29,114 @@
 
 namespace mj {
 
-// --------------------------------------------------------------- key forms
-MJ_KERNEL(k_tri_keys, 256, TriKeyArgs) {
-    for (uint64_t i = vg.bid * (uint64_t)blockDim.x + threadIdx.x; i < A.n;
-         i += (uint64_t)vg.nblk * blockDim.x) {
-        const uint32_t hi = ld_col(A.key_col, i, A.stride);
-        const uint32_t lo = ld_col(A.val_col, i, A.stride);
-        A.out[i] = ((unsigned long long)mix32(hi, A.seed) << 32) | (A.raw_low ? lo : mix32(lo, A.seed));
-    }
-}
-
 // ------------------------------------------------------- runs of equal keys
-// (and, when `low` is given, the low words: the joins read only those once
-// the runs of the high words are indexed)
-MJ_KERNEL(k_run_flags, 256, RunFlagsArgs) {
-    for (uint64_t i = vg.bid * (uint64_t)blockDim.x + threadIdx.x; i < A.n;
-         i += (uint64_t)vg.nblk * blockDim.x) {
-        const unsigned long long k = A.keys[i];
-        A.flags[i] = (i == 0 || (k >> 32) != (A.keys[i - 1] >> 32)) ? 1u : 0u;
-        if (A.low) A.low[i] = (uint32_t)k;
+__device__ __forceinline__ int run_find_job(const RunLaunch& L, uint32_t tile) {
+    int j = 0;
+#pragma unroll
+    for (int q = 1; q < RUN_MAX_JOBS; ++q)
+        if (q < L.njobs && tile >= L.job[q].tile_begin) j = q;
+    return j;
+}
+
+// The tile's keys, wave w holding its w-th part, 64 keys a round, and the
+// ballots of the run heads.  Returns the wave's number of heads.
+constexpr int RUN_ROUNDS = RUN_TILE / RUN_THREADS;
+__device__ __forceinline__ uint32_t run_heads(const RunJob& J, uint64_t beg, unsigned long long (&key)[RUN_ROUNDS],
+                                              unsigned long long (&heads)[RUN_ROUNDS]) {
+    const uint32_t lane = lane_id();
+    const uint64_t at = beg + threadIdx.x / WAVE * (RUN_ROUNDS * WAVE) + lane;
+    unsigned long long prev[RUN_ROUNDS];
+#pragma unroll
+    for (int k = 0; k < RUN_ROUNDS; ++k) {
+        const uint64_t i = at + k * WAVE;
+        key[k] = i < J.n ? J.keys[i] : 0ull;
+        prev[k] = lane == 0 && i > 0 && i < J.n ? J.keys[i - 1] : 0ull;
+    }
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < RUN_ROUNDS; ++k) {
+        const uint64_t i = at + k * WAVE;
+        const uint32_t hi = (uint32_t)(key[k] >> 32);
+        const uint32_t up = __shfl_up(hi, 1, WAVE);
+        const uint32_t before = lane == 0 ? (uint32_t)(prev[k] >> 32) : up;
+        heads[k] = __ballot(i < J.n && (i == 0 || hi != before));
+        c += (uint32_t)__popcll(heads[k]);
+    }
+    return c;
+}
+
+MJ_KERNEL(k_run_count, RUN_THREADS, RunLaunch) {
+    __shared__ uint32_t wsum[RUN_THREADS / WAVE];
+    if (vg.bid == 0) {                               // before the launches that count into them
+        for (uint32_t w = threadIdx.x; w < A.nclear; w += blockDim.x) A.clear[w] = 0;
+        if (A.zero && threadIdx.x == 0) *A.zero = 0;
+    }
+    const RunJob& J = A.job[run_find_job(A, vg.bid)];
+    const uint32_t tile = vg.bid - J.tile_begin;
+    unsigned long long key[RUN_ROUNDS], heads[RUN_ROUNDS];
+    const uint32_t c = run_heads(J, uint64_t(tile) * RUN_TILE, key, heads);
+    if (lane_id() == 0) wsum[threadIdx.x / WAVE] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int q = 0; q < RUN_THREADS / WAVE; ++q) t += wsum[q];
+        J.part[tile] = t;
     }
 }
 
-// run r starts at element i for every head i (ridx = exclusive scan of flags)
-MJ_KERNEL(k_run_compact, 256, RunCompactArgs) {
-    for (uint64_t i = vg.bid * (uint64_t)blockDim.x + threadIdx.x; i < A.n;
-         i += (uint64_t)vg.nblk * blockDim.x) {
-        if (A.flags[i]) {
-            const uint64_t r = A.ridx[i];
-            A.run_key[r] = (uint32_t)(A.keys[i] >> 32);
-            A.run_start[r] = (uint32_t)i;
+// Every tile numbers its runs from the heads before it and writes each run's
+// key, start and directory entries: a head knows the run before it from the
+// key before it, so the directory needs no pass of its own.  (As separate
+// flag, scan, compact and directory passes the four arrays of a join of 10^6
+// tuples took 26 launches and 0.25 ms; two launches and 62 us now.)
+MJ_KERNEL(k_run_emit, RUN_THREADS, RunLaunch) {
+    __shared__ uint32_t wsum[RUN_THREADS / WAVE], wbefore[RUN_THREADS / WAVE];
+    const RunJob& J = A.job[run_find_job(A, vg.bid)];
+    const uint32_t tile = vg.bid - J.tile_begin, lane = lane_id(), w = threadIdx.x / WAVE;
+    const uint64_t beg = uint64_t(tile) * RUN_TILE;
+    unsigned long long key[RUN_ROUNDS], heads[RUN_ROUNDS];
+    const uint32_t c = run_heads(J, beg, key, heads);
+    uint32_t b = 0;
+    if (A.scanned) {
+        b = threadIdx.x == 0 ? J.part[tile] : 0u;
+    } else {
+        for (uint32_t t = threadIdx.x; t < tile; t += blockDim.x) b += J.part[t];
+    }
+    b = wave_sum_u32(b);
+    if (lane == 0) { wsum[w] = c; wbefore[w] = b; }
+    __syncthreads();
+    uint32_t r = 0, end = 0;                          // runs before this wave's part, and before the next tile
+    for (uint32_t q = 0; q < RUN_THREADS / WAVE; ++q) {
+        r += wbefore[q] + (q < w ? wsum[q] : 0u);
+        end += wbefore[q] + wsum[q];
+    }
+    const uint64_t at = beg + w * (RUN_ROUNDS * WAVE) + lane;
+    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int k = 0; k < RUN_ROUNDS; ++k) {
+        const uint64_t i = at + k * WAVE;
+        const uint32_t hi = (uint32_t)(key[k] >> 32);
+        if (i < J.n && J.low) J.low[i] = (uint32_t)key[k];
+        if ((heads[k] >> lane) & 1ull) {
+            const uint32_t run = r + (uint32_t)__popcll(heads[k] & lt_mask);
+            J.run_key[run] = hi;
+            J.run_start[run] = (uint32_t)i;
+            if (J.dir) {
+                const uint32_t p0 = i == 0 ? 0u : top_bits((uint32_t)(J.keys[i - 1] >> 32), J.bits) + 1u;
+                const uint32_t p1 = top_bits(hi, J.bits);
+                for (uint32_t p = p0; p <= p1; ++p) J.dir[p] = run;
+            }
         }
+        r += (uint32_t)__popcll(heads[k]);
     }
-    if (vg.bid == 0 && threadIdx.x == 0) {
-        A.run_start[A.ridx[A.n]] = (uint32_t)A.n;
-        *A.nruns = A.ridx[A.n];
+    if (tile != J.ntiles - 1) return;
+    if (threadIdx.x == 0) {
+        J.run_start[end] = (uint32_t)J.n;
+        *J.nruns = end;
     }
-}
-
-// dir[p] = first run whose key prefix (top `bits` bits) is >= p, p in [0, 2^bits]
-MJ_KERNEL(k_run_dir, 256, RunDirArgs) {
-    const uint64_t nruns = *A.nruns;
-    const uint64_t np = uint64_t(1) << A.bits;
-    for (uint64_t r = vg.bid * (uint64_t)blockDim.x + threadIdx.x; r <= nruns;
-         r += (uint64_t)vg.nblk * blockDim.x) {
-        const uint64_t lo = r == 0 ? 0 : uint64_t(top_bits(A.run_key[r - 1], A.bits)) + 1;
-        const uint64_t hi = r == nruns ? np : uint64_t(top_bits(A.run_key[r], A.bits));
-        for (uint64_t p = lo; p <= hi; ++p) A.dir[p] = (uint32_t)r;
+    if (J.dir) {                                      // the prefixes after the last run's
+        const uint32_t p0 = J.n == 0 ? 0u : top_bits((uint32_t)(J.keys[J.n - 1] >> 32), J.bits) + 1u;
+        for (uint32_t p = p0 + threadIdx.x; p <= (1u << J.bits); p += blockDim.x) J.dir[p] = end;
     }
 }
 
@@ -90,67 +151,87 @@ __device__ __forceinline__ void heavy_shape(uint32_t x, uint32_t gn, uint32_t sh
     nsr = (gn + TRI_HEAVY_S - 1) / TRI_HEAVY_S;
 }
 
-// Light groups are appended with one atomic per workgroup and round of 1024
-// groups (one per wave serialised on the counter's address: 370 us a pass at
-// scale 22); each entry carries its group's run and its staged list's run.
-MJ_KERNEL(k_tri_classify, 256, TriClassifyArgs) {
-    __shared__ uint32_t wsum[256 / WAVE];
-    __shared__ uint32_t sbase;
-    const uint64_t ng = *A.Grp.nruns;
+// Groups are appended with one atomic per workgroup and round of 1024 groups
+// (one per wave serialised on the counter's address: 370 us a pass at scale
+// 22).  A light entry carries its group's run and its staged list's run.
+// Heavy groups and their items are counted in one 64-bit word, so a heavy
+// group learns its place and the items before it from the same atomic.
+MJ_KERNEL(k_tri_classify, 256, TriClassifyPair) {
+    __shared__ uint32_t wl[256 / WAVE], lbase;
+    __shared__ unsigned long long wh[256 / WAVE], hbase;
+    const bool second = vg.bid >= A.per;
+    const TriClassifyArgs& C = A.pass[second ? 1 : 0];
+    const uint32_t bid = second ? vg.bid - A.per : vg.bid;
+    const uint64_t ng = *C.Grp.nruns;
     const int lane = lane_id(), w = threadIdx.x / WAVE;
-    for (uint64_t g0 = vg.bid * 1024ull; g0 < ng; g0 += vg.nblk * 1024ull) {   // uniform over the block
-        uint32_t key[4], run[4], nlight = 0;
+    for (uint64_t g0 = bid * 1024ull; g0 < ng; g0 += A.per * 1024ull) {      // uniform over the block
+        uint32_t key[4], run[4], items[4], nlight = 0;
+        unsigned long long nheavy = 0;
         bool live[4], light[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint64_t g = g0 + u * 256 + threadIdx.x;
             live[u] = g < ng;
-            key[u] = live[u] ? A.Grp.run_key[g] : 0u;
+            key[u] = live[u] ? C.Grp.run_key[g] : 0u;
         }
-        run_find4(A.Stg, key, live, run);
+        run_find4(C.Stg, key, live, run);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             light[u] = false;
+            items[u] = 0;
             if (run[u] == 0xFFFFFFFFu) continue;
             const uint64_t g = g0 + u * 256 + threadIdx.x;
-            const uint32_t x = A.Stg.run_start[run[u] + 1] - A.Stg.run_start[run[u]];
-            const uint32_t gn = A.Grp.run_start[g + 1] - A.Grp.run_start[g];
+            const uint32_t x = C.Stg.run_start[run[u] + 1] - C.Stg.run_start[run[u]];
+            const uint32_t gn = C.Grp.run_start[g + 1] - C.Grp.run_start[g];
             light[u] = x <= TRI_LIGHT_X && gn <= TRI_LIGHT_S;
             if (light[u]) {
                 ++nlight;
             } else {
                 uint32_t nsl, nsr;
-                heavy_shape(x, gn, A.share, nsl, nsr);
-                const uint32_t h = atomicAdd(A.nheavy_groups, 1u);
-                A.heavy_group[h] = (uint32_t)g;
-                A.heavy_items[h] = nsl * nsr;
+                heavy_shape(x, gn, C.share, nsl, nsr);
+                items[u] = nsl * nsr;
+                nheavy += (1ull << HEAVY_SHIFT) | items[u];
             }
         }
-        uint32_t v = nlight;                          // inclusive prefix over the wave
+        uint32_t vl = nlight;                         // inclusive prefixes over the wave
+        unsigned long long vh = nheavy;
 #pragma unroll
         for (int off = 1; off < WAVE; off <<= 1) {
-            const uint32_t y = __shfl_up(v, off, WAVE);
-            if (lane >= off) v += y;
+            const uint32_t yl = __shfl_up(vl, off, WAVE);
+            const unsigned long long yh = __shfl_up(vh, off, WAVE);
+            if (lane >= off) { vl += yl; vh += yh; }
         }
-        if (lane == WAVE - 1) wsum[w] = v;
+        if (lane == WAVE - 1) { wl[w] = vl; wh[w] = vh; }
         __syncthreads();
         if (threadIdx.x == 0) {
-            uint32_t t = 0;
-            for (int q = 0; q < 256 / WAVE; ++q) t += wsum[q];
-            sbase = t ? atomicAdd(A.nlight, t) : 0u;
+            uint32_t tl = 0;
+            unsigned long long th = 0;
+            for (int q = 0; q < 256 / WAVE; ++q) { tl += wl[q]; th += wh[q]; }
+            lbase = tl ? atomicAdd(C.nlight, tl) : 0u;
+            hbase = th ? atomicAdd(C.heavy, th) : 0ull;
         }
         __syncthreads();
-        uint32_t at = sbase + v - nlight;
-        for (int q = 0; q < w; ++q) at += wsum[q];
+        uint32_t at = lbase + vl - nlight;
+        unsigned long long hat = hbase + vh - nheavy;
+        for (int q = 0; q < w; ++q) { at += wl[q]; hat += wh[q]; }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (light[u]) A.light[at++] = make_uint2((uint32_t)(g0 + u * 256 + threadIdx.x), run[u]);
-        __syncthreads();                              // wsum and sbase are used again
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t g = (uint32_t)(g0 + u * 256 + threadIdx.x);
+            if (light[u]) C.light[at++] = make_uint2(g, run[u]);
+            if (items[u]) {
+                const uint32_t hg = (uint32_t)(hat >> HEAVY_SHIFT);
+                C.heavy_group[hg] = g;
+                C.heavy_off[hg] = hat & ((1ull << HEAVY_SHIFT) - 1ull);
+                hat += (1ull << HEAVY_SHIFT) | items[u];
+            }
+        }
+        __syncthreads();                              // the shared words are used again
     }
 }
 
 // ------------------------------------------------------------- staged lists
-// A staged list lies in LDS as it is, sorted by m(a), with a directory over
+// A staged list lies in LDS as it is, sorted by m(a) (at least by its top bits
+// from TriJoinArgs::low_bits up; a bucket is no finer), with a directory over
 // the range of its values: the values are hashes, so equal-width buckets
 // hold about the same number each.  dir[bucket] = first position | number of
 // entries << 16.  A lookup reads one directory word and then the bucket's
@@ -181,12 +262,17 @@ __device__ __forceinline__ bool listtab_index(const ListTab& T, uint32_t q) {
 }
 
 // run[q] of a run's first entry: the end of its run, by a binary search in
-// the rest of its bucket
-__device__ __forceinline__ void listtab_run(const ListTab& T, uint32_t q) {
+// the rest of its bucket (step by step where the bucket is not in order:
+// then a value may have several runs, each counted)
+__device__ __forceinline__ void listtab_run(const ListTab& T, uint32_t q, bool in_order) {
     const uint32_t v = T.val[q];
     if (q && T.val[q - 1] == v) return;
     const uint32_t d = T.dir[(v - T.base) >> T.shift];
     uint32_t lo = q + 1, hi = (d & 0xFFFFu) + (d >> 16);
+    if (!in_order) {
+        while (lo < hi && T.val[lo] == v) ++lo;
+        hi = lo;
+    }
     while (lo < hi) {
         const uint32_t m = (lo + hi) >> 1;
         if (T.val[m] == v) lo = m + 1; else hi = m;
@@ -246,11 +332,6 @@ __device__ __forceinline__ uint32_t count_low(const unsigned long long* keys, ui
     uint32_t l2 = l, h2 = hi;
     while (l2 < h2) { uint32_t m = (l2 + h2) >> 1; if ((uint32_t)keys[m] <= a) l2 = m + 1; else h2 = m; }
     return l2 - l;
-}
-
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // ------------------------------------------------------- streaming lists
@@ -356,7 +437,7 @@ __device__ unsigned long long tri_light_group(const TriJoinArgs& A, uint2 item, 
     T.dup = __ballot(dup) != 0;
     unsigned long long acc = 0;
     if (T.dup) {
-        for (uint32_t q = lane; q < x; q += WAVE) listtab_run(T, q);
+        for (uint32_t q = lane; q < x; q += WAVE) listtab_run(T, q, A.low_bits == 0);
         wave_fence();
         for (uint32_t c0 = gs; c0 < ge; c0 += WAVE)
             acc += stream_chunk<true>(A, c0 + lane, c0 + lane < ge, x, T, false);
@@ -422,19 +503,25 @@ __device__ __forceinline__ bool light_next_run(uint32_t* counters, unsigned long
     }
 }
 
-MJ_KERNEL(k_tri_light, TRI_THREADS, TriJoinArgs) {
+// Both passes in one launch: a wave that finds pass 0's queues empty goes on
+// with pass 1's.
+MJ_KERNEL(k_tri_light, TRI_THREADS, TriJoinPair) {
     TRI_LIGHT_SETUP
     (void)lane;
-    const uint32_t nitems = *A.nlight;
-    const uint32_t grab = light_grab(nitems, (unsigned long long)vg.nblk * (TRI_THREADS / WAVE));
-    unsigned long long acc = 0, it = 0, end = 0;
-    uint32_t q = vg.bid % TRI_QUEUES;
-    while (true) {
-        if (it >= end && !light_next_run(A.light_next, nitems, grab, q, it, end)) break;   // wave-uniform
-        acc += tri_light_group(A, A.light[it], T);
-        ++it;
+    unsigned long long acc = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        const TriJoinArgs& P = A.pass[pass];
+        const uint32_t nitems = *P.nlight;
+        const uint32_t grab = light_grab(nitems, (unsigned long long)vg.nblk * (TRI_THREADS / WAVE));
+        unsigned long long it = 0, end = 0;
+        uint32_t q = vg.bid % TRI_QUEUES;
+        while (true) {
+            if (it >= end && !light_next_run(P.light_next, nitems, grab, q, it, end)) break;   // wave-uniform
+            acc += tri_light_group(P, P.light[it], T);
+            ++it;
+        }
     }
-    block_add_u64(A.total, acc);
+    block_add_u64(A.pass[0].total, acc);
 }
 
 // ------------------------------------------------------------- heavy groups
@@ -470,7 +557,7 @@ __device__ __forceinline__ uint32_t wave_last_le(const unsigned long long* off, 
 __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long long it, const BlockTable& B) {
     const int lane = lane_id();
     // item -> (heavy group, slice of the staged list, range of the group)
-    const uint32_t lo = wave_last_le(A.heavy_off, A.n_heavy_cap, it);
+    const uint32_t lo = wave_last_le(A.heavy_off, (uint32_t)(*A.heavy >> HEAVY_SHIFT), it);
     const uint32_t g = A.heavy_group[lo];
     const uint32_t local = (uint32_t)(it - A.heavy_off[lo]);
     uint32_t rs = 0, x = 0;
@@ -484,10 +571,11 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
     const uint32_t s0 = gs + sb * TRI_HEAVY_S, s1 = min(gs + gn, s0 + TRI_HEAVY_S);
     if (r0 == r1) return 0;                           // uniform across the block
     const uint32_t len = r1 - r0;
-    ListTab T{B.dir, B.val, B.run, A.Stgl[r0], 0u, 0u, false};
-    T.top = A.Stgl[r1 - 1] - T.base;
+    const uint32_t low = (1u << A.low_bits) - 1u;      // the bits the lists are not ordered by
+    ListTab T{B.dir, B.val, B.run, A.Stgl[r0] & ~low, 0u, 0u, false};
+    T.top = (A.Stgl[r1 - 1] | low) - T.base;
     const uint32_t width = 32u - (uint32_t)__clz((int)(T.top | 1u));           // bits of the largest offset
-    T.shift = width > TRI_HEAVY_DIR_BITS ? width - TRI_HEAVY_DIR_BITS : 0u;
+    T.shift = max(A.low_bits, width > TRI_HEAVY_DIR_BITS ? width - TRI_HEAVY_DIR_BITS : 0u);
     for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) T.val[q] = A.Stgl[r0 + q];
     for (uint32_t q = threadIdx.x; q < (1u << TRI_HEAVY_DIR_BITS); q += blockDim.x) T.dir[q] = 0;
     __syncthreads();
@@ -497,7 +585,7 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
     __syncthreads();
     T.dup = *B.dup != 0;                              // uniform across the block
     if (T.dup) {
-        for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) listtab_run(T, q);
+        for (uint32_t q = threadIdx.x; q < len; q += blockDim.x) listtab_run(T, q, A.low_bits == 0);
         __syncthreads();
     }
     const bool sliced = nsl > 1;
@@ -523,21 +611,24 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
     __shared__ uint32_t hdup, hchunk;                                     \
     const BlockTable B{hdir, hval, hrun, &hdup, &hchunk};
 
-MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinArgs) {
+MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinPair) {
     (void)vg;
     TRI_HEAVY_SETUP
     __shared__ uint32_t s_item;
-    const uint32_t nitems = (uint32_t)A.heavy_off[A.n_heavy_cap];
     unsigned long long acc = 0;
-    while (true) {
-        __syncthreads();
-        if (threadIdx.x == 0) { s_item = atomicAdd(A.heavy_next, 1u); hchunk = 0; hdup = 0; }
-        __syncthreads();
-        const uint32_t it = s_item;
-        if (it >= nitems) break;
-        acc += tri_heavy_item(A, it, B);
+    for (int pass = 0; pass < 2; ++pass) {
+        const TriJoinArgs& P = A.pass[pass];
+        const unsigned long long nitems = *P.heavy & ((1ull << HEAVY_SHIFT) - 1ull);
+        while (nitems) {                              // uniform across the block
+            __syncthreads();
+            if (threadIdx.x == 0) { s_item = atomicAdd(P.heavy_next, 1u); hchunk = 0; hdup = 0; }
+            __syncthreads();
+            const uint32_t it = s_item;
+            if (it >= nitems) break;
+            acc += tri_heavy_item(P, it, B);
+        }
     }
-    block_add_u64(A.total, acc);
+    block_add_u64(A.pass[0].total, acc);
 }
 
 // ------------------------------------------------------------- batches
@@ -608,7 +699,7 @@ __global__ void __launch_bounds__(WAVE) k_tri_batch_prefix(TriBatchArgs Bt) {
     for (uint32_t j0 = 0; j0 < Bt.njoins; j0 += WAVE) {
         const uint32_t j = j0 + lane;
         const unsigned long long nl = j < Bt.njoins ? *Bt.joins[j].nlight : 0ull;
-        const unsigned long long nh = j < Bt.njoins ? Bt.joins[j].heavy_off[Bt.joins[j].n_heavy_cap] : 0ull;
+        const unsigned long long nh = j < Bt.njoins ? *Bt.joins[j].heavy & ((1ull << HEAVY_SHIFT) - 1ull) : 0ull;
         unsigned long long l = nl, h = nh;
 #pragma unroll
         for (int off = 1; off < WAVE; off <<= 1) {

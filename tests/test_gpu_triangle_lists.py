@@ -56,3 +56,24 @@ def test_staged_and_streamed_list_sizes(mj, x, y, g, bag):
         p = fixed_plan(mj, ctx, mj.TRIANGLE, Rd, Sd, Td, algo=mj.ALGO_3WAY, log2_share=share, seed=11 + share)
         assert int(mj.as_u64(ctx.triangle3_count(Rd, Sd, Td, plan=p))[0]) == want, share
     ctx.close()
+
+
+@pytest.mark.parametrize("nr,ns,nt", [
+    (1, 16384, 16385), (16385, 4097, 131073), (131073, 131072, 20479), (4096, 300000, 20481), (262145, 3, 16383)])
+def test_sorts_of_different_sizes_together(mj, nr, ns, nt):
+    """The four key arrays of one join, some sorted in one workgroup, some in
+    passes whose scatter adds up the histogram rows, some with scanned rows;
+    with the materialised join for the order inside equal keys (stability)."""
+    rng = np.random.default_rng(nr + ns + nt)
+    R, S, T = (rng.integers(0, 2500, size=(n, 2)).astype(np.uint32) for n in (nr, ns, nt))
+    R[0] = S[0] = T[0] = (0xFFFFFFFF, 0xFFFFFFFF)
+    ctx = mj.Context()
+    Rd, Sd, Td = dev(R), dev(S), dev(T)
+    p = fixed_plan(mj, ctx, mj.TRIANGLE, Rd, Sd, Td, algo=mj.ALGO_3WAY, seed=5)
+    assert int(mj.as_u64(ctx.triangle3_count(Rd, Sd, Td, plan=p))[0]) == oracle.triangle3_count(R, S, T)
+    import torch
+    out = torch.zeros((5000, 4), dtype=torch.int32, device="cuda")
+    got, total = ctx.linear3_materialize(Rd, Sd, Td, first=7, out=out)
+    want = np.asarray(oracle.linear3_materialize(R, S, T, 7, 5000)[0], dtype=np.uint32).reshape(-1, 4)
+    assert np.array_equal(got.cpu().numpy().view(np.uint32)[:want.shape[0]], want)
+    ctx.close()
