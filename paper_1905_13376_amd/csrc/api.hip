@@ -326,29 +326,40 @@ void take_part(Bump& B, RelPart& P, uint64_t n, uint32_t bits) {
     P.pairs = B.take<uint2>(std::max<uint64_t>(n, 1));
 }
 
-// Ranges of A for the per-A counts: about 32K R tuples per range, at most
-// 2^PART_MAX_BITS ranges of at most 2^ACELL_MAX_SHIFT values.  False when
-// a_domain needs more (the cells then add into the output with atomics).
-bool a_ranges(const mj_plan_t& p, uint32_t& bits, uint32_t& shift) {
-    if (p.a_domain == 0) return false;
-    const uint32_t L = ceil_log2(p.a_domain);
-    bits = std::min<uint32_t>({ceil_log2((p.n_r + 32767) / 32768), PART_MAX_BITS, L});
+// Ranges of a key domain [0, domain): about 32K of n tuples per range, but
+// 2^9 ranges (two workgroups a CU) as soon as each gets 1024 tuples -- 64
+// workgroups of 32K tuples took 46 us for the sums of a 2 x 10^6-tuple
+// relation, 15 us in 512 of 4K -- at most 2^PART_MAX_BITS ranges of at most
+// 2^ACELL_MAX_SHIFT values; false when the domain needs more.  In a batch the
+// other joins fill the chip, and workgroups of 2K tuples cost more to start
+// than they save: at least 8K there.
+bool key_ranges(uint64_t n, uint32_t domain, uint32_t& bits, uint32_t& shift, bool in_batch = false) {
+    if (domain == 0) return false;
+    const uint32_t L = ceil_log2(domain);
+    const uint64_t least = in_batch ? 8192 : 1024;
+    const uint32_t fill = std::min<uint32_t>(9, n >= 2 * least ? ceil_log2(n / least + 1) - 1 : 0);
+    bits = std::min<uint32_t>({std::max(fill, ceil_log2((n + 32767) / 32768)), PART_MAX_BITS, L});
     if (L - bits > ACELL_MAX_SHIFT) bits = L - ACELL_MAX_SHIFT;
     shift = L - bits;
     return bits <= PART_MAX_BITS;
 }
 
-// Ranges of a key domain [0, domain): about 32K of n tuples per range, at
-// most 2^PART_MAX_BITS ranges of at most 2^ACELL_MAX_SHIFT values; false
-// when the domain needs more.
-bool key_ranges(uint64_t n, uint32_t domain, uint32_t& bits, uint32_t& shift) {
-    if (domain == 0) return false;
-    const uint32_t L = ceil_log2(domain);
-    bits = std::min<uint32_t>({ceil_log2((n + 32767) / 32768), PART_MAX_BITS, L});
-    if (L - bits > ACELL_MAX_SHIFT) bits = L - ACELL_MAX_SHIFT;
-    shift = L - bits;
-    return bits <= PART_MAX_BITS;
+// Ranges of A for the per-A counts.  False when a_domain needs more than
+// there can be (the cells then add into the output with atomics).
+bool a_ranges(const mj_plan_t& p, uint32_t& bits, uint32_t& shift) {
+    return key_ranges(p.n_r, p.a_domain, bits, shift);
 }
+
+// Range pairs in 4 bytes: the key's place in its range beside the other value
+// (table_n stands for every value at or above it: those join nothing).  Half
+// the bytes of the partition's writes and of the sums' reads.
+bool pack_pairs(uint32_t shift, uint32_t table_n, uint32_t& bits) {
+    bits = ceil_log2(uint64_t(table_n) + 1);
+    return shift + bits <= 32;
+}
+
+// internal plan flag: the join runs as one of a batch
+constexpr uint32_t PLAN_IN_BATCH = 1u << 31;
 
 // dense keys: B and C below these bounds, and not much sparser than the tuples
 constexpr uint32_t DENSE_MAX_DOMAIN = 1u << 24;
@@ -378,15 +389,16 @@ bool dense_plan(const mj_plan_t& p) {
 DenseLayout dense_layout(void* ws, const mj_plan_t& p) {
     Bump B(ws);
     DenseLayout L{};
-    key_ranges(p.n_t, p.c_domain, L.c_bits, L.c_shift);
-    key_ranges(p.n_s, p.b_domain, L.b_bits, L.b_shift);
-    key_ranges(p.n_r, p.a_domain, L.a_bits, L.a_shift);
+    const bool in_batch = (p.flags & PLAN_IN_BATCH) != 0;
+    key_ranges(p.n_t, p.c_domain, L.c_bits, L.c_shift, in_batch);
+    key_ranges(p.n_s, p.b_domain, L.b_bits, L.b_shift, in_batch);
+    key_ranges(p.n_r, p.a_domain, L.a_bits, L.a_shift, in_batch);
     auto part = [&](RelPart& P, uint64_t n, uint32_t bits, bool pairs) {
         const uint32_t nb = 1u << bits;
         P.hist = B.take<uint32_t>(uint64_t(nb) * ntiles_of(n));
         P.counts = B.take<uint32_t>(nb);
         P.starts = B.take<uint32_t>(nb + 1);
-        P.pairs = pairs ? B.take<uint2>(std::max<uint64_t>(n, 1)) : nullptr;
+        P.pairs = pairs ? B.take<uint2>(std::max<uint64_t>(n, 4)) : nullptr;   // (packed: read four at a time)
     };
     part(L.T, p.n_t, L.c_bits, false);
     L.tkeys = B.take<uint32_t>(std::max<uint64_t>(p.n_t, 1));
@@ -573,10 +585,14 @@ PartJob make_job(const mj_rel& r, uint32_t* hist, uint32_t* counts, uint32_t* st
 
 // Partition up to MJ_PART_MAX_JOBS relations (four launches in all).
 int launch_partition(Prof* prof, const char* tag, PartLaunch& P, hipStream_t st) {
-    uint32_t tiles = 0, rows = 0, maxbits = 0;
+    uint32_t tiles = 0, rows = 0, maxbits = 0, most = 0;
     for (int q = 0; q < P.njobs; ++q) {
         const PartJob& J = P.job[q];
         // a one-column payload is re-bucketed from that column alone
+        if (J.out_packed) {
+            if (!J.range_on || J.out_pair || J.out_single || J.range_shift + J.pack_bits > 32) return MJ_ERR_INVALID_ARG;
+            continue;
+        }
         if (!J.out_pair && (J.bits1 != 0 || J.key0_col != J.single_col)) return MJ_ERR_INVALID_ARG;
         if ((J.out_pair != nullptr) == (J.out_single != nullptr)) return MJ_ERR_INVALID_ARG;
     }
@@ -586,7 +602,9 @@ int launch_partition(Prof* prof, const char* tag, PartLaunch& P, hipStream_t st)
         const uint32_t bits = P.job[q].bits0 + P.job[q].bits1;
         rows += 1u << bits;
         maxbits = std::max(maxbits, bits);
+        most = std::max(most, P.job[q].ntiles);
     }
+    P.fold_rows = most <= PART_FOLD_TILES ? 1u : 0u;
     const std::string t(tag);
     // k_part_hist clears the caller's words first
     if (tiles) {
@@ -595,8 +613,9 @@ int launch_partition(Prof* prof, const char* tag, PartLaunch& P, hipStream_t st)
     } else if (P.nclear) {
         MJ_LAUNCHM(prof, t + ":k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, st, P.clear, (uint64_t)P.nclear, 0u);
     }
-    MJ_LAUNCHM(prof, t + ":k_part_rowscan", k_part_rowscan, dim3(rows), dim3(PART_THREADS),
-              PART_SCAN_CHUNK * 4, st, P);
+    if (!P.fold_rows)
+        MJ_LAUNCHM(prof, t + ":k_part_rowscan", k_part_rowscan, dim3(rows), dim3(PART_THREADS),
+                  PART_SCAN_CHUNK * 4, st, P);
     MJ_LAUNCHM(prof, t + ":k_part_scan", k_part_scan, dim3(P.njobs), dim3(PART_THREADS),
               (size_t(1) << maxbits) * 4, st, P);
     if (tiles)
@@ -1078,6 +1097,7 @@ int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
 
 // ------------------------------------------------------------- star join
 static_assert(STAR_GROUPS == STAR_PLAN_MAX_R, "planner and kernels agree on the star limit");
+static_assert(SMALL_MAX == DENSE_SMALL_MAX, "planner and kernels agree on the small joins' limit");
 
 struct StarLayout {
     TableLayout Rt, Tt;               // one-bucket tables: R on B, T on C
@@ -1333,68 +1353,117 @@ int run_dense(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, con
     // S by range of B, R by range of A, T by range of C: each on its first
     // column.  A partition identical to an earlier one (same columns,
     // stride, size and ranges: R = S = T in a self-join) is not made again;
-    // its pairs and starts serve both (T then reads the keys of the pairs).
+    // it serves both (T then reads the keys of the pairs).
     auto same = [](const mj_rel& x, uint32_t xb, uint32_t xs, const mj_rel& y, uint32_t yb, uint32_t ys) {
         return same_rel(x, y) && xb == yb && xs == ys;
     };
+    const bool r_is_s = same(R, L.a_bits, L.a_shift, S, L.b_bits, L.b_shift);
+    const bool t_is_s = same(T, L.c_bits, L.c_shift, S, L.b_bits, L.b_shift);
+    const bool t_is_r = !t_is_s && same(T, L.c_bits, L.c_shift, R, L.a_bits, L.a_shift);
+    // a shared partition's keys are held to the least of their bounds, and
+    // its other values packed for the larger table (each reader checks its own)
+    const uint32_t s_dom = std::min({p.b_domain, r_is_s ? p.a_domain : p.b_domain, t_is_s ? p.c_domain : p.b_domain});
+    const uint32_t s_tab = std::max(p.c_domain, r_is_s ? p.b_domain : 0u);
+    const uint32_t r_dom = std::min(p.a_domain, t_is_r ? p.c_domain : p.a_domain);
+    uint32_t s_pack = 0, r_pack = 0;
+    const bool s_packed = pack_pairs(L.b_shift, s_tab, s_pack);
+    const bool r_packed = r_is_s ? s_packed : pack_pairs(L.a_shift, p.b_domain, r_pack);
+    if (r_is_s) r_pack = s_pack;
     PartLaunch P{};
     P.njobs = 0;
     P.clear = L.err; P.nclear = 3;                   // the flags, cleared by the first launch
-    P.job[P.njobs] = make_job(S, L.S.hist, L.S.counts, L.S.starts, 0, 0, L.b_bits, 0, 0, 0);
-    P.job[P.njobs].range_on = 1; P.job[P.njobs].range_shift = L.b_shift;
-    P.job[P.njobs].split = L.Ssplit;
-    P.job[P.njobs++].out_pair = L.S.pairs;
-    const bool r_is_s = same(R, L.a_bits, L.a_shift, S, L.b_bits, L.b_shift);
-    if (!r_is_s) {
-        P.job[P.njobs] = make_job(R, L.R.hist, L.R.counts, L.R.starts, 0, 0, L.a_bits, 0, 0, 0);
-        P.job[P.njobs].range_on = 1; P.job[P.njobs].range_shift = L.a_shift;
-        P.job[P.njobs].split = L.Rsplit;
-        P.job[P.njobs++].out_pair = L.R.pairs;
-    }
-    const bool t_is_s = same(T, L.c_bits, L.c_shift, S, L.b_bits, L.b_shift);
-    const bool t_is_r = !t_is_s && same(T, L.c_bits, L.c_shift, R, L.a_bits, L.a_shift);
+    auto add_pairs = [&](const mj_rel& rel, const RelPart& part, uint32_t bits, uint32_t shift, const BucketItems& split,
+                         bool packed, uint32_t pack, uint32_t tab, uint32_t dom) {
+        PartJob& J = P.job[P.njobs++];
+        J = make_job(rel, part.hist, part.counts, part.starts, 0, 0, bits, 0, 0, 0);
+        J.range_on = 1; J.range_shift = shift;
+        J.split = split;
+        if (!packed) { J.out_pair = part.pairs; return; }
+        J.out_packed = reinterpret_cast<uint32_t*>(part.pairs);
+        J.pack_bits = pack; J.pack_max = tab; J.pack_domain = dom; J.pack_err = L.err;
+    };
+    add_pairs(S, L.S, L.b_bits, L.b_shift, L.Ssplit, s_packed, s_pack, s_tab, s_dom);
+    if (!r_is_s) add_pairs(R, L.R, L.a_bits, L.a_shift, L.Rsplit, r_packed, r_pack, p.b_domain, r_dom);
     if (!t_is_s && !t_is_r) {
-        P.job[P.njobs] = make_job(T, L.T.hist, L.T.counts, L.T.starts, 0, 0, L.c_bits, 0, 0, 0);
-        P.job[P.njobs].range_on = 1; P.job[P.njobs].range_shift = L.c_shift;
-        P.job[P.njobs].split = L.Tsplit;
-        P.job[P.njobs].out_single = L.tkeys; P.job[P.njobs++].single_col = 0;
+        PartJob& J = P.job[P.njobs++];
+        J = make_job(T, L.T.hist, L.T.counts, L.T.starts, 0, 0, L.c_bits, 0, 0, 0);
+        J.range_on = 1; J.range_shift = L.c_shift;
+        J.split = L.Tsplit;
+        J.out_single = L.tkeys; J.single_col = 0;
     }
     int st = launch_partition(prof, "dense", P, s);
     if (st) return st;
     const RelPart& Rp = r_is_s ? L.S : L.R;
     const RelPart* Tp = t_is_s ? &L.S : (t_is_r ? &Rp : nullptr);
+    const bool t_packed = t_is_s ? s_packed : (t_is_r ? r_packed : false);
     // the work items of each sum: those of the partition it reads
     const BucketItems& Rsp = r_is_s ? L.Ssplit : L.Rsplit;
     const BucketItems& Tsp = t_is_s ? L.Ssplit : (t_is_r ? Rsp : L.Tsplit);
     const uint64_t n_rp = r_is_s ? S.n : R.n;
     const uint64_t n_tp = t_is_s ? S.n : (t_is_r ? n_rp : T.n);
-    RangeAccArgs<uint32_t, uint16_t, uint32_t, uint16_t> Ad{};
-    Ad.pairs = Tp ? Tp->pairs : nullptr; Ad.keys = Tp ? nullptr : L.tkeys;
-    Ad.starts = Tp ? Tp->starts : L.T.starts; Ad.shift = L.c_shift;
-    Ad.domain = p.c_domain; Ad.table = nullptr; Ad.table_n = 0; Ad.out = L.deg; Ad.err = L.err;
-    Ad.out_narrow = L.deg16; Ad.wide = L.err + 2; Ad.table_narrow = nullptr; Ad.use_wide = nullptr;
+    auto tuples = [](auto& A, const RelPart& part, bool packed, uint32_t pack) {
+        if (packed) { A.packed = reinterpret_cast<const uint32_t*>(part.pairs); A.pack_bits = pack; }
+        else A.pairs = part.pairs;
+        A.starts = part.starts;
+    };
+    RangeDegArgs Ad{};
+    if (Tp) tuples(Ad, *Tp, t_packed, t_is_s ? s_pack : r_pack);
+    else { Ad.keys = L.tkeys; Ad.starts = L.T.starts; }
+    Ad.shift = L.c_shift; Ad.domain = p.c_domain; Ad.out = L.deg; Ad.err = L.err;
+    Ad.out_narrow = L.deg16; Ad.wide = L.err + 2;
     Ad.split = Tsp; Ad.rows = L.rows; Ad.row_len = 1u << L.c_shift;
     MJ_LAUNCHM(prof, "k_range_deg", k_range_deg, dim3(split_grid(n_tp, L.c_bits)), dim3(RANGE_THREADS),
               size_t(4) << L.c_shift, s, Ad);
-    RangeAccArgs<uint32_t, uint16_t, unsigned long long, uint16_t> Aw{};
-    Aw.pairs = L.S.pairs; Aw.keys = nullptr; Aw.starts = L.S.starts; Aw.shift = L.b_shift;
-    Aw.domain = p.b_domain; Aw.table = L.deg; Aw.table_n = p.c_domain; Aw.out = L.w; Aw.err = L.err;
+    RangeWArgs Aw{};
+    tuples(Aw, L.S, s_packed, s_pack);
+    Aw.shift = L.b_shift; Aw.domain = p.b_domain; Aw.table = L.deg; Aw.table_n = p.c_domain; Aw.out = L.w; Aw.err = L.err;
     // deg's 2-byte copy unless some deg[c] needs more; W's saturating 2-byte copy
-    Aw.out_narrow = L.w16; Aw.wide = nullptr; Aw.table_narrow = L.deg16; Aw.use_wide = L.err + 2;
+    Aw.out_narrow = L.w16; Aw.table_narrow = L.deg16; Aw.use_wide = L.err + 2;
     Aw.split = L.Ssplit; Aw.rows = L.rows; Aw.row_len = 1u << L.b_shift;
     MJ_LAUNCHM(prof, "k_range_w", k_range_w, dim3(split_grid(S.n, L.b_bits)), dim3(RANGE_THREADS),
               size_t(8) << L.b_shift, s, Aw);
-    RangeAccArgs<unsigned long long, uint16_t, unsigned long long, uint32_t> Ac{};
-    Ac.pairs = Rp.pairs; Ac.keys = nullptr; Ac.starts = Rp.starts; Ac.shift = L.a_shift;
-    Ac.domain = p.a_domain; Ac.table = L.w; Ac.table_n = p.b_domain; Ac.out = count; Ac.err = L.err;
+    RangeCountArgs Ac{};
+    tuples(Ac, Rp, r_packed, r_pack);
+    Ac.shift = L.a_shift; Ac.domain = p.a_domain; Ac.table = L.w; Ac.table_n = p.b_domain; Ac.out = count; Ac.err = L.err;
     // W's saturating 2-byte copy; the full W where it reads 0xFFFF
-    Ac.out_narrow = nullptr; Ac.wide = nullptr; Ac.table_narrow = L.w16; Ac.use_wide = nullptr;
+    Ac.table_narrow = L.w16;
     Ac.split = Rsp; Ac.rows = L.rows; Ac.row_len = 1u << L.a_shift;
     MJ_LAUNCHM(prof, "k_range_count", k_range_count, dim3(split_grid(n_rp, L.a_bits)), dim3(RANGE_THREADS),
               size_t(8) << L.a_shift, s, Ac);
-    // a key beyond its certified bound: every count all ones
-    MJ_LAUNCHM(prof, "k_poison_u64", k_poison_u64, dim3(grid_for(p.a_domain, 256, 1024)), dim3(256), 0, s,
-              count, (uint64_t)p.a_domain, L.err);
+    // a key beyond its certified bound: every count all ones (with packed
+    // pairs of R no flag is raised after the partition, and the counts'
+    // kernel has written them)
+    if (!r_packed)
+        MJ_LAUNCHM(prof, "k_poison_u64", k_poison_u64, dim3(grid_for(p.a_domain, 256, 1024)), dim3(256), 0, s,
+                  count, (uint64_t)p.a_domain, L.err);
+    return MJ_OK;
+}
+
+// Small relations, dense keys: three launches, no partition.  The line lies
+// where reading a relation in every workgroup costs what its partition does
+// (SMALL_MAX tuples); the domains are within 2 n + 4096 of it.
+int run_small(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, const mj_plan_t& p,
+              unsigned long long* count, void* ws, hipStream_t s) {
+    const DenseLayout L = dense_layout(ws, p);
+    auto set = [](auto& A, const mj_rel& r, uint32_t domain) {
+        A.key_col = r.col0; A.val_col = r.col1; A.stride = r.stride; A.n = r.n;
+        A.packed = r.stride == 2 && r.col1 == r.col0 + 1 && (reinterpret_cast<uintptr_t>(r.col0) & 15) == 0 ? 1u : 0u;
+        A.domain = domain;
+        A.span = std::min<uint32_t>(SMALL_SPAN, (domain + SMALL_RANGES - 1) / SMALL_RANGES);
+        return dim3((domain + A.span - 1) / A.span);
+    };
+    SmallDegArgs D{};
+    const dim3 gd = set(D, T, p.c_domain);
+    D.out = L.deg; D.err = L.err;
+    MJ_LAUNCHM(prof, "k_small_deg", k_small_deg, gd, dim3(SMALL_THREADS), 0, s, D);
+    SmallWArgs W{};
+    const dim3 gw = set(W, S, p.b_domain);
+    W.table = L.deg; W.table_n = p.c_domain; W.out = L.w; W.err = L.err + 1;
+    MJ_LAUNCHM(prof, "k_small_w", k_small_w, gw, dim3(SMALL_THREADS), 0, s, W);
+    SmallCountArgs C{};
+    const dim3 gc = set(C, R, p.a_domain);
+    C.table = L.w; C.table_n = p.b_domain; C.out = count; C.err_in = L.err; C.n_err_in = 2;
+    MJ_LAUNCHM(prof, "k_small_count", k_small_count, gc, dim3(SMALL_THREADS), 0, s, C);
     return MJ_OK;
 }
 
@@ -1942,6 +2011,7 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
                       cnt, (uint64_t)a_domain, 0ull);
             return MJ_OK;
         }
+        if (std::max({R->n, S->n, T->n}) <= SMALL_MAX) return run_small(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
         return run_dense(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
     }
     LinearLayout L = linear_layout(nullptr, p);
@@ -2435,9 +2505,16 @@ int mj_ctx_set_planner(mj_ctx* ctx, const void* params) {
 // plan's cells are left out of its chain and run for all joins in one
 // launch at the end.
 
+static mj_plan_t batch_plan(const mj_batch_item& it) {
+    mj_plan_t p = it.plan;
+    p.flags |= PLAN_IN_BATCH;
+    return p;
+}
+
 static size_t batch_item_bytes(const mj_batch_item& it) {
     if (it.plan.algo != MJ_ALGO_3WAY) return it.plan.workspace_bytes;
-    if (it.kind == MJ_LINEAR) return linear_layout(nullptr, it.plan).bytes;
+    if (it.kind == MJ_LINEAR)
+        return dense_plan(it.plan) ? dense_layout(nullptr, batch_plan(it)).bytes : linear_layout(nullptr, it.plan).bytes;
     return tri_layout(nullptr, it.plan).bytes;
 }
 
@@ -2470,8 +2547,10 @@ static int record_batch(mj_ctx* ctx, const mj_batch_item* items, int n, char* ba
         const size_t bytes = batch_item_bytes(it);
         off += align256(bytes);
         prof->rec = &B.chains[(size_t)i];
-        if (p.algo != MJ_ALGO_3WAY) {        // cascades, star and oriented plans run their own path
-            st = run_plan(ctx, it.kind, &it.R, &it.S, &it.T, it.a_domain, it.out, p, wsi, bytes, s);
+        // cascades, star and oriented plans, and direct-indexed tables, run
+        // their own path
+        if (p.algo != MJ_ALGO_3WAY || (it.kind == MJ_LINEAR && dense_plan(p))) {
+            st = run_plan(ctx, it.kind, &it.R, &it.S, &it.T, it.a_domain, it.out, batch_plan(it), wsi, bytes, s);
         } else if (it.kind == MJ_LINEAR) {
             st = [&]() -> int {
                 LinearLayout L = linear_layout(wsi, p);

@@ -821,6 +821,41 @@ __device__ __forceinline__ void range_accumulate(const RangeAccArgs<TW, TWN, TO,
     const uint32_t q1 = s0 + (uint32_t)(uint64_t(len) * (piece + 1) / pcs);
     // a split range is a heavy one: equal keys of a wave are folded first
     const bool heavy = pcs > 1;
+    if (A.packed) {
+        // four consecutive tuples per thread and load (16 bytes, aligned)
+        const uint32_t vmask = (1u << A.pack_bits) - 1u;
+        for (uint32_t qb = q0 & ~3u; qb < q1; qb += 4 * nthr) {     // every lane runs every round
+            const uint32_t q = qb + 4 * threadIdx.x;
+            u32x4 p = {0u, 0u, 0u, 0u};
+            if (q < q1) p = *reinterpret_cast<const u32x4*>(A.packed + q);
+            TO w[4];
+            bool live[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                live[u] = q + u >= q0 && q + u < q1;
+                const uint32_t v = p[u] & vmask;
+                if (A.table) {
+                    const bool in = live[u] && v < A.table_n;
+                    if constexpr (SAT_IN) {
+                        const TWN x = in ? A.table_narrow[v] : TWN(0);
+                        w[u] = x == TWN(~TWN(0)) ? (TO)A.table[v] : (TO)x;
+                    } else {
+                        w[u] = !in ? (TO)0 : (narrow ? (TO)A.table_narrow[v] : (TO)A.table[v]);
+                    }
+                } else {
+                    w[u] = 1;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                TO v = w[u];
+                const uint32_t off = p[u] >> A.pack_bits;
+                bool act = live[u] && v != 0 && off < span;          // (a key past the domain was reported)
+                if (heavy && wave_fold_first(off, act, v)) act = false;
+                if (act) atomicAdd(&acc[off], v);
+            }
+        }
+    } else
     for (uint32_t qb = q0; qb < q1; qb += 4 * nthr) {               // every lane runs every round
         const uint32_t q = qb + threadIdx.x;
         uint32_t key[4];
@@ -865,8 +900,11 @@ __device__ __forceinline__ void range_accumulate(const RangeAccArgs<TW, TWN, TO,
     if (pcs > 1 && !split_merge(A.split, k, piece, pcs, reinterpret_cast<TO*>(A.rows), A.row_len, acc, span))
         return;                                                     // another piece writes the range
     bool big = false;
+    // packed tuples: every key past its bound was found by the partition, so
+    // the counts can be set to all ones here
+    const bool poison = SAT_IN && A.packed && *A.err != 0;
     for (uint32_t j = threadIdx.x; j < span; j += nthr) {
-        const TO v = acc[j];
+        const TO v = poison ? ~TO(0) : acc[j];
         A.out[base + j] = v;
         if (A.out_narrow) {
             constexpr uint64_t top = uint64_t(TON(~TON(0)));
@@ -894,6 +932,85 @@ MJ_KERNEL(k_range_w, RANGE_THREADS, RangeWArgs) {
 MJ_KERNEL(k_range_count, RANGE_THREADS, RangeCountArgs) {
     extern __shared__ unsigned long long acc64c[];
     range_accumulate<true, false>(A, acc64c, vg);
+}
+
+// ------------------------------------------------------------ small joins
+// The same three sums with no partition: one workgroup per range of keys
+// reads every tuple and keeps those of its range.  At these sizes a launch
+// costs more than reading the relation from L2 in every workgroup, so a join
+// is three launches instead of seven: 34.8 -> 18.4 us at 16,384 tuples a
+// relation, 34.2 -> 22.8 us at 32,768; at 65,536 (38.7 us) the partition is
+// the faster way (35.1 us).  Bound by the range test of every tuple in every
+// workgroup's vector units.
+template <bool LAST, class TW, class TO>
+__device__ __forceinline__ void small_accumulate(const SmallAccArgs<TW, TO>& A, TO* acc, VGrid vg) {
+    __shared__ uint32_t s_bad;
+    const uint64_t base64 = uint64_t(vg.bid) * A.span;
+    const uint32_t base = (uint32_t)base64, span = (uint32_t)min<uint64_t>(A.span, A.domain - base64);
+    const uint32_t nthr = blockDim.x, n = (uint32_t)A.n;
+    for (uint32_t j = threadIdx.x; j < span; j += nthr) acc[j] = 0;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
+    uint32_t top = 0;                                                // the largest key seen
+    constexpr uint32_t U = 8;                                        // tuples per thread and round
+    auto add = [&](uint32_t key, uint32_t v) {
+        TO w = 1;
+        if (A.table) w = v < A.table_n ? (TO)A.table[v] : TO(0);
+        if (w) atomicAdd(&acc[key - base], w);
+    };
+    uint32_t q0 = 0;
+    for (; q0 + U * nthr <= n; q0 += U * nthr) {                     // whole rounds
+        uint32_t key[U], v[U];
+        if (A.packed) {
+#pragma unroll
+            for (uint32_t u = 0; u < U; u += 2) {                    // two tuples per 16-byte load
+                const u32x4 p = reinterpret_cast<const u32x4*>(A.key_col)[((q0 + u * nthr) >> 1) + threadIdx.x];
+                key[u] = p[0]; v[u] = p[1]; key[u + 1] = p[2]; v[u + 1] = p[3];
+            }
+        } else {
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) key[u] = A.key_col[(q0 + u * nthr + threadIdx.x) * A.stride];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            top = max(top, key[u]);
+            if (key[u] - base >= span) continue;
+            if (!A.packed) v[u] = A.table ? A.val_col[(q0 + u * nthr + threadIdx.x) * A.stride] : 0u;
+            add(key[u], v[u]);
+        }
+    }
+    for (uint32_t i = q0 + threadIdx.x; i < n; i += nthr) {          // the rest
+        const uint32_t key = A.key_col[i * A.stride];
+        top = max(top, key);
+        if (key - base < span) add(key, A.table ? A.val_col[i * A.stride] : 0u);
+    }
+    const bool bad = n > 0 && top >= A.domain;
+    if (bad) s_bad = 1;
+    __syncthreads();
+    const bool any = s_bad != 0;                                     // the same in every workgroup
+    bool poison = false;
+    if constexpr (LAST) {
+        poison = any;
+        for (uint32_t e = 0; e < A.n_err_in; ++e) poison = poison || A.err_in[e] != 0;
+    } else if (vg.bid == 0 && threadIdx.x == 0) {
+        *A.err = any ? 1u : 0u;
+    }
+    for (uint32_t j = threadIdx.x; j < span; j += nthr) A.out[base + j] = poison ? ~TO(0) : acc[j];
+}
+
+MJ_KERNEL(k_small_deg, SMALL_THREADS, SmallDegArgs) {
+    __shared__ uint32_t acc[SMALL_SPAN];
+    small_accumulate<false>(A, acc, vg);
+}
+
+MJ_KERNEL(k_small_w, SMALL_THREADS, SmallWArgs) {
+    __shared__ unsigned long long acc[SMALL_SPAN];
+    small_accumulate<false>(A, acc, vg);
+}
+
+MJ_KERNEL(k_small_count, SMALL_THREADS, SmallCountArgs) {
+    __shared__ unsigned long long acc[SMALL_SPAN];
+    small_accumulate<true>(A, acc, vg);
 }
 
 MJ_KERNEL(k_check_size, 64, CheckSizeArgs) {

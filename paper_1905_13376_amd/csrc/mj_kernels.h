@@ -25,6 +25,7 @@ constexpr int PART_SCATTER_THREADS = MJ_PART_SCATTER_THREADS;   // scatter: more
 constexpr int PART_TILE = MJ_PART_TILE;  // tuples per block (<= 2^16)
 constexpr int PART_SCAN_CHUNK = 4096;    // row-scan chunk (LDS entries)
 constexpr int MJ_PART_MAX_JOBS = 4;
+constexpr uint32_t PART_FOLD_TILES = 16; // at most this many tiles: k_part_scan does the row scans too
 constexpr uint32_t PART_MAX_BITS = 12;   // at most 4096 buckets per pass
 constexpr size_t LDS_BYTES = 160 * 1024; // per workgroup on gfx950
 // the scatter's dynamic LDS (two words per bucket, a staged tile of pairs)
@@ -73,6 +74,12 @@ struct PartJob {
     uint32_t range_on;   // bucket = min(key0 >> range_shift, 2^bits0 - 1) (no hash; pairs only)
     uint32_t range_shift;
     uint32_t swap_out;   // pairs written as (col1, col0)
+    // packed range pairs (set with range_on, instead of out_pair and
+    // out_single): (col0 - first key of its range) << pack_bits |
+    // min(col1, pack_max), 4 bytes a tuple; a col0 >= pack_domain sets *pack_err
+    uint32_t* out_packed;
+    uint32_t pack_bits, pack_max, pack_domain;
+    uint32_t* pack_err;
     uint32_t tile_begin; // first block of this job in the grid
     uint32_t ntiles;
     BucketItems split;   // optional work items of the buckets (k_part_scan)
@@ -81,6 +88,7 @@ struct PartJob {
 struct PartLaunch {
     PartJob job[MJ_PART_MAX_JOBS];
     int njobs;
+    uint32_t fold_rows = 0;      // k_part_scan sums the histogram's rows itself (no k_part_rowscan)
     uint32_t* clear = nullptr;   // words k_part_hist sets to 0 first (flags of the caller's kernels)
     uint32_t nclear = 0;
 };
@@ -302,8 +310,10 @@ constexpr int RANGE_THREADS = 1024;         // range sums: one workgroup per ran
 // else table[v] (0 for v >= table_n).  A key outside [0, domain) sets err.
 template <class TW, class TWN, class TO, class TON>
 struct RangeAccArgs {
-    const uint2* pairs;          // (key, v) by range of key; null: keys only
-    const uint32_t* keys;        // keys by range (when pairs is null)
+    const uint2* pairs;          // (key, v) by range of key; null: keys only, or
+    const uint32_t* keys;        // keys by range (when pairs is null), or
+    const uint32_t* packed = nullptr;  // (key - first of its range) << pack_bits | v, 16-byte aligned (pairs, keys null)
+    uint32_t pack_bits = 0;
     const uint32_t* starts;      // [ranges + 1]
     uint32_t shift;              // range k holds keys [k << shift, (k + 1) << shift)
     uint32_t domain;
@@ -336,6 +346,33 @@ MJ_KERNEL_DECL(k_range_w, RangeWArgs);
 // count[a] += W[r.b] (reads W's saturating copy)
 typedef RangeAccArgs<unsigned long long, uint16_t, unsigned long long, uint32_t> RangeCountArgs;
 MJ_KERNEL_DECL(k_range_count, RangeCountArgs);
+// Small joins: the three sums without a partition, each a launch of one
+// workgroup per range of keys that reads the whole relation.
+constexpr int SMALL_THREADS = 1024;
+constexpr uint32_t SMALL_MAX = 49152;        // tuples per relation
+constexpr uint32_t SMALL_RANGES = 64;        // workgroups (more when the domain needs them)
+constexpr uint32_t SMALL_SPAN = 4096;        // keys per workgroup at most (32 KB of sums)
+template <class TW, class TO>
+struct SmallAccArgs {
+    const uint32_t* key_col;
+    const uint32_t* val_col;     // unused without a table
+    int64_t stride;
+    uint64_t n;
+    uint32_t packed;             // rows of 8 bytes (key first), 16-byte aligned
+    uint32_t span, domain;       // range k holds keys [k * span, (k + 1) * span)
+    const TW* table;             // null: weight 1
+    uint32_t table_n;
+    TO* out;                     // [domain]
+    uint32_t* err;               // this launch's flag: set to 1 or 0 (a key >= domain)
+    const uint32_t* err_in;      // earlier launches' flags: when one is set, or err would be,
+    uint32_t n_err_in;           // every entry of out is all ones
+};
+typedef SmallAccArgs<uint32_t, uint32_t> SmallDegArgs;
+typedef SmallAccArgs<uint32_t, unsigned long long> SmallWArgs;
+typedef SmallAccArgs<unsigned long long, unsigned long long> SmallCountArgs;
+MJ_KERNEL_DECL(k_small_deg, SmallDegArgs);
+MJ_KERNEL_DECL(k_small_w, SmallWArgs);
+MJ_KERNEL_DECL(k_small_count, SmallCountArgs);
 // every entry of out set to all ones when *err is set (a certified key bound broken)
 struct PoisonArgs { unsigned long long* out; uint64_t n; const uint32_t* err; };   // out[0..n) = ~0 when *err
 MJ_KERNEL_DECL(k_poison_u64, PoisonArgs);

@@ -27,6 +27,10 @@ inline bool star_plan_fits(const mj_plan_t& p) {
     return p.n_r <= STAR_PLAN_MAX_R && p.n_t <= STAR_PLAN_MAX_T;
 }
 
+// dense keys and at most this many tuples per relation: the sums run without
+// a partition (the kernels' SMALL_MAX)
+constexpr uint64_t DENSE_SMALL_MAX = 49152;
+
 // the degree-oriented cyclic join pays for its orientation pass (about
 // 0.4 ms of extra launches) when the relation is large and its wedges dense:
 // |R |x| S| = sum of squared degrees at least ORIENT_MIN_WEDGES per tuple

@@ -6,7 +6,8 @@
 //   k_part_hist    : per tile, an LDS histogram of bucket ids, stored as
 //                    column `tile` of a bucket-major matrix hist[d][tile]
 //   k_part_rowscan : per bucket, the exclusive prefix of its row over tiles
-//                    (in place) and the row total
+//                    (in place) and the row total (left to k_part_scan when
+//                    every relation has at most PART_FOLD_TILES tiles)
 //   k_part_scan    : per relation, the exclusive prefix of the bucket totals
 //                    (bucket starts)
 //   k_part_scatter : per tile, tuples are grouped by bucket in LDS (local
@@ -162,10 +163,24 @@ MJ_KERNEL(k_part_rowscan, PART_THREADS, PartLaunch) {
 // first the pieces of the split buckets (so the longest work starts first;
 // piece p of bucket d is item and scratch row hrow[d] + p), then the other
 // buckets in bucket order.  All threads of the block call it.
-__device__ void part_scan_job(const PartJob& J, uint32_t* lds, uint32_t* wave_tmp) {
+__device__ void part_scan_job(const PartJob& J, bool fold, uint32_t* lds, uint32_t* wave_tmp) {
     const uint32_t* counts = J.counts;
     const uint32_t nb = 1u << (J.bits0 + J.bits1);
-    for (uint32_t d = threadIdx.x; d < nb; d += blockDim.x) lds[d] = counts[d];
+    for (uint32_t d = threadIdx.x; d < nb; d += blockDim.x) {
+        if (!fold) { lds[d] = counts[d]; continue; }
+        // the row scan of a bucket of few tiles: a launch less (about 5 us)
+        uint32_t* row = J.hist + uint64_t(d) * J.ntiles;
+        uint32_t c[PART_FOLD_TILES], run = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < PART_FOLD_TILES; ++t) c[t] = t < J.ntiles ? row[t] : 0u;
+#pragma unroll
+        for (uint32_t t = 0; t < PART_FOLD_TILES; ++t) {
+            if (t < J.ntiles) row[t] = run;
+            run += c[t];
+        }
+        J.counts[d] = run;
+        lds[d] = run;
+    }
     __syncthreads();
     uint32_t total = block_exclusive_scan(lds, nb, wave_tmp);
     for (uint32_t d = threadIdx.x; d < nb; d += blockDim.x) J.starts[d] = lds[d];
@@ -199,7 +214,7 @@ __device__ void part_scan_job(const PartJob& J, uint32_t* lds, uint32_t* wave_tm
 MJ_KERNEL(k_part_scan, PART_THREADS, PartLaunch) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t wave_tmp[PART_THREADS / WAVE + 1];
-    part_scan_job(A.job[vg.bid], lds, wave_tmp);
+    part_scan_job(A.job[vg.bid], A.fold_rows != 0, lds, wave_tmp);
 }
 
 MJ_KERNEL(k_part_scatter, PART_SCATTER_THREADS, PartLaunch) {
@@ -235,6 +250,29 @@ MJ_KERNEL(k_part_scatter, PART_SCATTER_THREADS, PartLaunch) {
         gbase[d] = J.starts[d] + J.hist[uint64_t(d) * J.ntiles + tile];
     block_exclusive_scan(lcount, nb, wave_tmp);
     const bool pair = J.out_pair != nullptr;
+    if (J.out_packed) {
+        // 4 bytes a tuple, and beside it in LDS the tuple's range (the packed
+        // word no longer tells it)
+        uint16_t* range = reinterpret_cast<uint16_t*>(stage + PART_TILE);
+        bool bad = false;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (idx[k] >= cnt) continue;
+            const uint32_t d = rk[k] >> 16;
+            const uint32_t p = lcount[d] + (rk[k] & 0xFFFFu);
+            bad = bad || x0[k] >= J.pack_domain;
+            const uint32_t local = x0[k] & ((1u << J.range_shift) - 1u);
+            stage[p] = (local << J.pack_bits) | min(x1[k], J.pack_max);
+            range[p] = (uint16_t)d;
+        }
+        if (bad) atomicExch(J.pack_err, 1u);
+        __syncthreads();
+        for (uint32_t p = threadIdx.x; p < cnt; p += blockDim.x) {
+            const uint32_t d = range[p];
+            part_store(stage[p], J.out_packed + gbase[d] + (p - lcount[d]));
+        }
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         if (idx[k] < cnt) {
