@@ -250,23 +250,28 @@ struct Bump {
 #ifndef MJ_SPLIT_PCT
 #define MJ_SPLIT_PCT 200
 #endif
-uint32_t split_chunk(uint64_t n, uint32_t bits) {
+uint32_t split_chunk(uint64_t n, uint32_t bits, uint32_t pct = MJ_SPLIT_PCT) {
     const uint64_t mean = (n + (uint64_t(1) << bits) - 1) >> bits;
-    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(SPLIT_MIN_CHUNK, mean * MJ_SPLIT_PCT / 100),
-                                        uint64_t(1) << 31);
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(SPLIT_MIN_CHUNK, mean * pct / 100), uint64_t(1) << 31);
 }
+// The hashed tables' counts split at the mean: a skewed relation of 6 x 10^6
+// tuples 105 -> 72 us against twice the mean.  (The direct-indexed sums and
+// the table builds lose by it: 297 -> 362 us for the power-law join.)
+constexpr uint32_t COUNT_SPLIT_PCT = 100;
 uint32_t split_grid(uint64_t n, uint32_t bits) { return (1u << bits) + (uint32_t)(n / split_chunk(n, bits)) + 1; }
 // the work items of n tuples under a given split (its chunk may come from a
 // larger relation's layout: then they are fewer)
 uint32_t items_grid(const BucketItems& I, uint64_t n, uint32_t bits) {
     return (1u << bits) + (uint32_t)(n / I.chunk) + 1;
 }
-uint64_t split_rows(uint64_t n, uint32_t bits) { return 2 * (n / split_chunk(n, bits)) + 1; }
-BucketItems take_items(Bump& B, uint64_t n, uint32_t bits) {
+uint64_t split_rows(uint64_t n, uint32_t bits, uint32_t pct = MJ_SPLIT_PCT) {
+    return 2 * (n / split_chunk(n, bits, pct)) + 1;
+}
+BucketItems take_items(Bump& B, uint64_t n, uint32_t bits, uint32_t pct = MJ_SPLIT_PCT) {
     BucketItems I{};
     const uint32_t nb = 1u << bits;
-    I.chunk = split_chunk(n, bits);
-    I.items = B.take<uint32_t>(split_grid(n, bits));
+    I.chunk = split_chunk(n, bits, pct);
+    I.items = B.take<uint32_t>(items_grid(I, n, bits));
     I.nitems = B.take<uint32_t>(1);
     I.hrow = B.take<uint32_t>(nb);
     I.done = B.take<uint32_t>(nb);
@@ -286,6 +291,9 @@ struct TableLayout {                 // bucketed multiplicity tables of one colu
     BucketItems split;               // heavy buckets in pieces: their items,
     uint2* rows;                     // the pieces' (key, count) tables
     uint32_t* row_special;
+    uint32_t* row_n;
+    uint32_t* npool;                 // the tables' narrow form, or null
+    uint32_t* ndir;
 };
 
 uint32_t ntiles_of(uint64_t n) { return (uint32_t)((n + PART_TILE - 1) / PART_TILE); }
@@ -294,14 +302,16 @@ uint64_t pool_slots_for(uint64_t n, uint32_t nbkt) {
     return 4 * n + uint64_t(DB_MIN_CAP) * nbkt + DB_MIN_CAP;
 }
 
-void take_table(Bump& B, TableLayout& L, uint64_t n, uint32_t bits) {
+// `narrow`: with the tables' narrow form, for lookups of random keys
+void take_table(Bump& B, TableLayout& L, uint64_t n, uint32_t bits, bool narrow = false) {
     const uint32_t nb = 1u << bits;
     L.hist = B.take<uint32_t>(uint64_t(nb) * ntiles_of(n));
     L.counts = B.take<uint32_t>(nb);
     L.starts = B.take<uint32_t>(nb + 1);
     L.keys = B.take<uint32_t>(std::max<uint64_t>(n, 1));
     L.dir = B.take<DirEntry>(nb);
-    L.pool_slots = pool_slots_for(n, nb);
+    narrow = narrow && nt_bits_ok(bits);
+    L.pool_slots = pool_slots_for(n, nb) + (narrow ? NT_MIN_SLOTS : 0u);
     L.pool = B.take<uint2>(L.pool_slots);
     L.pool_cursor = B.take<unsigned long long>(1);
     L.err = B.take<uint32_t>(1);
@@ -309,6 +319,9 @@ void take_table(Bump& B, TableLayout& L, uint64_t n, uint32_t bits) {
     const uint64_t nrows = split_rows(n, bits);
     L.rows = B.take<uint2>(nrows * DB_CAP);
     L.row_special = B.take<uint32_t>(nrows);
+    L.row_n = B.take<uint32_t>(nrows);
+    L.npool = narrow ? B.take<uint32_t>(L.pool_slots) : nullptr;
+    L.ndir = narrow ? B.take<uint32_t>(nb) : nullptr;
 }
 
 struct RelPart {                     // one relation partitioned into 2^bits buckets
@@ -426,6 +439,8 @@ struct LinearLayout {
     TableLayout T;
     WDirEntry* wdir;                  // W tables per bucket of B
     WSlot* wpool;
+    uint32_t* npool;                  // the W tables' narrow form, or null
+    uint32_t* ndir;
     unsigned long long* wcursor;
     uint64_t wslots;
     uint32_t a_bits, a_shift;
@@ -435,6 +450,7 @@ struct LinearLayout {
     BucketItems Ssplit;               // skew split of the buckets of S (W build)
     WSlot* wrows;                     // the pieces' W tables
     unsigned long long* wrow_special;
+    uint32_t* wrow_n;
     // S-largest plans: R's B values as tables per part of R, a sum per slot
     TableLayout Rk;
     unsigned long long* wval;
@@ -461,19 +477,19 @@ LinearLayout linear_layout(void* ws, const mj_plan_t& p) {
     LinearLayout L;
     take_part(B, L.R, p.n_r, p.log2_nb);
     take_part(B, L.S, p.n_s, s_part_bits(p));
-    take_table(B, L.T, p.n_t, p.log2_nc);
+    take_table(B, L.T, p.n_t, p.log2_nc, p.algo != MJ_ALGO_SLARGE);
     L.by_range = a_ranges(p, L.a_bits, L.a_shift);
-    L.wdir = nullptr; L.wpool = nullptr; L.wcursor = nullptr; L.wslots = 0;
+    L.wdir = nullptr; L.wpool = nullptr; L.npool = nullptr; L.ndir = nullptr; L.wcursor = nullptr; L.wslots = 0;
     L.Rasplit = BucketItems{}; L.rows = nullptr;
-    L.Ssplit = BucketItems{}; L.wrows = nullptr; L.wrow_special = nullptr;
+    L.Ssplit = BucketItems{}; L.wrows = nullptr; L.wrow_special = nullptr; L.wrow_n = nullptr;
     L.Ra = L.R;
     if (L.by_range) {
         const uint32_t na = 1u << L.a_bits;
         L.Ra.hist = B.take<uint32_t>(uint64_t(na) * ntiles_of(p.n_r));
         L.Ra.counts = B.take<uint32_t>(na);
         L.Ra.starts = B.take<uint32_t>(na + 1);
-        L.Rasplit = take_items(B, p.n_r, L.a_bits);
-        L.rows = B.take<unsigned long long>(split_rows(p.n_r, L.a_bits) << L.a_shift);
+        L.Rasplit = take_items(B, p.n_r, L.a_bits, COUNT_SPLIT_PCT);
+        L.rows = B.take<unsigned long long>(split_rows(p.n_r, L.a_bits, COUNT_SPLIT_PCT) << L.a_shift);
         const uint32_t nb = 1u << p.log2_nb;
         L.wdir = B.take<WDirEntry>(nb);
         if (p.algo == MJ_ALGO_SLARGE) {
@@ -486,11 +502,16 @@ LinearLayout linear_layout(void* ws, const mj_plan_t& p) {
             // a bucket's table holds at most 4 slots per S tuple (a power of
             // two >= twice its keys), plus the minimum per bucket and the
             // empty head
-            L.wslots = 4 * p.n_s + uint64_t(W_MIN_CAP) * (nb + 1);
+            L.wslots = 4 * p.n_s + uint64_t(W_MIN_CAP) * (nb + 1) + (nt_bits_ok(p.log2_nb) ? NT_MIN_SLOTS : 0u);
             L.Ssplit = take_items(B, p.n_s, p.log2_nb);
             const uint64_t nrows = split_rows(p.n_s, p.log2_nb);
             L.wrows = B.take<WSlot>(nrows * CELL_CAP);
             L.wrow_special = B.take<unsigned long long>(nrows);
+            L.wrow_n = B.take<uint32_t>(nrows);
+            if (nt_bits_ok(p.log2_nb)) {
+                L.npool = B.take<uint32_t>(L.wslots);
+                L.ndir = B.take<uint32_t>(nb);
+            }
         }
         L.wpool = B.take<WSlot>(L.wslots);
         L.wcursor = B.take<unsigned long long>(1);
@@ -541,7 +562,7 @@ CascadeLayout cascade_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
         L.deg16 = B.take<uint16_t>(std::max<uint32_t>(p.c_domain, 1));
         L.dflags = B.take<uint32_t>(3);
     } else {
-        take_table(B, L.T, p.n_t, p.log2_nc);
+        take_table(B, L.T, p.n_t, p.log2_nc, true);
     }
     // join 1 groups S's C values by B and probes with R's tuples
     L.Rgrp = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
@@ -647,7 +668,8 @@ int launch_tables(Prof* prof, const TableLayout& L, const mj_rel& rel, int col, 
     D.keys = L.keys; D.starts = L.starts; D.nbkt = nb; D.slot_seed = sseed;
     D.dir = L.dir; D.pool = L.pool; D.pool_cursor = L.pool_cursor; D.pool_cap = L.pool_slots;
     D.err = L.err;
-    D.split = L.split; D.rows = L.rows; D.row_special = L.row_special;
+    D.split = L.split; D.rows = L.rows; D.row_special = L.row_special; D.row_n = L.row_n;
+    D.npool = L.npool; D.ndir = L.ndir; D.bkt_bits = bits; D.bkt_seed = bseed;
     MJ_LAUNCHM(prof, "tab:k_dbuild", k_dbuild, dim3(items_grid(L.split, rel.n, bits)), dim3(DB_THREADS), 0, st, D);
     return MJ_OK;
 }
@@ -2077,7 +2099,9 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
             Wb.c_seed = seed_c(p); Wb.c_bits = p.log2_nc; Wb.slot_seed = seed_slot(p); Wb.w_seed = seed_w(p);
             Wb.wdir = L.wdir; Wb.wpool = L.wpool; Wb.wcursor = L.wcursor; Wb.wcap = L.wslots;
             Wb.err = L.T.err;
-            Wb.split = L.Ssplit; Wb.rows = L.wrows; Wb.row_special = L.wrow_special;
+            Wb.split = L.Ssplit; Wb.rows = L.wrows; Wb.row_special = L.wrow_special; Wb.row_n = L.wrow_n;
+            Wb.dnpool = L.T.npool; Wb.dndir = L.T.ndir; Wb.npool = L.npool; Wb.ndir = L.ndir;
+            Wb.b_bits = p.log2_nb; Wb.b_seed = seed_b(p);
             MJ_LAUNCH(&ctx->prof, "k_wbuild", k_wbuild, dim3(split_grid(S->n, p.log2_nb)), dim3(CELL_THREADS), 0, s, Wb);
         }
         // per range of A: count[a] = sum of W[r.b], written once
@@ -2088,7 +2112,8 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
         Cn.count = reinterpret_cast<unsigned long long*>(count);
         Cn.err = L.T.err;
         Cn.split = L.Rasplit; Cn.rows = L.rows;
-        MJ_LAUNCH(&ctx->prof, "k_count", k_count, dim3(split_grid(R->n, L.a_bits)), dim3(COUNT_THREADS),
+        Cn.npool = L.npool; Cn.ndir = L.ndir;
+        MJ_LAUNCH(&ctx->prof, "k_count", k_count, dim3(items_grid(L.Rasplit, R->n, L.a_bits)), dim3(COUNT_THREADS),
                   (size_t(8) << L.a_shift), s, Cn);
         // an A value out of range or a table overflow: every count all ones
         MJ_LAUNCHM(&ctx->prof, "k_poison_u64", k_poison_u64, dim3(grid_for(a_domain, 256, 1024)), dim3(256), 0, s,
@@ -2253,6 +2278,7 @@ int mj_cascade2_count(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, c
         Q.c_seed = seed_c(p); Q.c_bits = p.log2_nc; Q.slot_seed = seed_slot(p);
         Q.count = count; Q.a_domain = a_domain; Q.err = dense ? L.dflags : L.T.err;
         Q.deg = L.deg; Q.deg16 = L.deg16; Q.c_domain = p.c_domain; Q.use_wide = dense ? L.dflags + 2 : nullptr;
+        if (!dense) { Q.npool = L.T.npool; Q.ndir = L.T.ndir; }
         MJ_LAUNCHM(prof, "k_cas_probe", k_cas_probe, dim3(grid_for(hi - lo, 1024, 8192)), dim3(256), 0, s, Q);
     }
     // a key beyond its certified bound, an A value out of range, a table

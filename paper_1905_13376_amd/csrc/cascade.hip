@@ -324,6 +324,11 @@ MJ_KERNEL(k_cas_expand, EXP_THREADS, CasExpandArgs) {
 
 // ------------------------------------------------------------- second join
 MJ_KERNEL(k_cas_probe, 256, CasProbeArgs) {
+    __shared__ uint32_t ldir[1u << NT_MAX_BITS];           // T's narrow directory
+    if (A.npool) {                                         // uniform over the launch
+        for (uint32_t j = threadIdx.x; j < (1u << A.c_bits); j += blockDim.x) ldir[j] = A.ndir[j];
+        __syncthreads();
+    }
     const int lane = lane_id();
     const bool wide = A.deg && *A.use_wide != 0;           // uniform over the launch
     const uint64_t stride = uint64_t(vg.nblk) * blockDim.x * 4;
@@ -345,6 +350,9 @@ MJ_KERNEL(k_cas_probe, 256, CasProbeArgs) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 w[u] = (live[u] && c[u] < A.c_domain) ? (wide ? A.deg[c[u]] : (uint32_t)A.deg16[c[u]]) : 0u;
+        } else if (A.npool) {
+            nt_lookup4(ldir, A.npool, c, live, A.c_seed, A.c_bits, w);
+            dtab_wide4(A.ddir, A.dpool, c, A.c_seed, A.c_bits, A.slot_seed, w);
         } else {
             dtab_lookup4(A.ddir, A.dpool, c, live, A.c_seed, A.c_bits, A.slot_seed, w);
         }

@@ -135,13 +135,54 @@ __device__ __forceinline__ void db_count(const uint32_t* keys, uint32_t beg, uin
     }
 }
 
+// A piece's table goes to its scratch row without the empty slots (a row of
+// a few hundred entries instead of 64 KB); returns through *n how many.  All
+// threads of the workgroup call it; `put` stores entry `slot` at place `at`.
+template <class F>
+__device__ __forceinline__ void row_compact(const uint32_t* keys, uint32_t cap, uint32_t* n, F&& put) {
+    const unsigned long long lane_lt = lane_id() == 0 ? 0ull : (~0ull >> (64 - lane_id()));
+    for (uint32_t s = threadIdx.x; s < cap; s += blockDim.x) {       // cap: a multiple of the workgroup
+        const unsigned long long occ = __ballot(keys[s] != EMPTY_KEY);
+        uint32_t base = 0;
+        if (lane_id() == 0 && occ) base = atomicAdd(n, (uint32_t)__popcll(occ));
+        base = __shfl(base, 0, WAVE);
+        if (keys[s] != EMPTY_KEY) put(s, base + (uint32_t)__popcll(occ & lane_lt));
+    }
+}
+
+// The entries of `pcs` compacted rows, eight rows' reads in flight per thread
+// (one slot at a time, each waits for another XCD's lines: adding up a hub's
+// nine rows took 0.1 ms).  Stops once *over is set.
+template <class E, class F>
+__device__ __forceinline__ void rows_for_each(const E* rows, const uint32_t* row_n, uint32_t row_cap, uint32_t pcs,
+                                              const uint32_t* over, F&& add) {
+    constexpr uint32_t ROWS = 8;
+    for (uint32_t r0 = 0; r0 < pcs; r0 += ROWS) {
+        uint32_t n[ROWS], most = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < ROWS; ++u) n[u] = r0 + u < pcs ? row_n[r0 + u] : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < ROWS; ++u) most = max(most, n[u]);
+        for (uint32_t i = threadIdx.x; i < most; i += blockDim.x) {
+            if (*(volatile const uint32_t*)over) return;
+            E e[ROWS];
+#pragma unroll
+            for (uint32_t u = 0; u < ROWS; ++u)
+                if (i < n[u]) e[u] = rows[uint64_t(r0 + u) * row_cap + i];
+#pragma unroll
+            for (uint32_t u = 0; u < ROWS; ++u)
+                if (i < n[u]) add(e[u]);
+        }
+    }
+}
+
 // One workgroup per bucket: the (key, count) table in LDS, then one table
 // per bucket in the pool.  A bucket crowded by heavy keys runs as pieces,
 // one workgroup each, and the last piece to finish adds up their tables.
 MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
     __shared__ uint32_t tkeys[DB_CAP];
     __shared__ uint32_t tvals[DB_CAP];
-    __shared__ uint32_t s_special, s_distinct, s_over, s_log2, s_last;
+    __shared__ uint32_t s_special, s_distinct, s_over, s_log2, s_last, s_rown;
     __shared__ unsigned long long s_base;
     uint32_t j = vg.bid, piece = 0, pcs = 1;
     if (A.split.items) {                                         // uniform over the block
@@ -155,7 +196,7 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
     const uint32_t n = end - beg;
 
     for (uint32_t s = threadIdx.x; s < DB_CAP; s += blockDim.x) { tkeys[s] = EMPTY_KEY; tvals[s] = 0; }
-    if (threadIdx.x == 0) { s_special = 0; s_distinct = 0; s_over = 0; }
+    if (threadIdx.x == 0) { s_special = 0; s_distinct = 0; s_over = 0; s_rown = 0; }
     __syncthreads();
     if (pcs == 1) {
         db_count(A.keys, beg, end, tkeys, tvals, &s_special, &s_distinct, &s_over, A.slot_seed);
@@ -170,19 +211,11 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
         const uint64_t r = uint64_t(A.split.hrow[j]) + piece;
         if (!ovf) {
             uint2* row = A.rows + r * DB_CAP;
-            for (uint32_t s = threadIdx.x; s < DB_CAP; s += blockDim.x) row[s] = make_uint2(tkeys[s], tvals[s]);
-            if (threadIdx.x == 0) A.row_special[r] = s_special;
+            row_compact(tkeys, DB_CAP, &s_rown, [&](uint32_t s, uint32_t at) { row[at] = make_uint2(tkeys[s], tvals[s]); });
+            __syncthreads();
+            if (threadIdx.x == 0) { A.row_special[r] = s_special; A.row_n[r] = s_rown; }
         }
-        handoff_release();
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (ovf) atomicOr(&A.split.done[j], 0x80000000u);
-            const uint32_t old = atomicAdd(&A.split.done[j], 1u);
-            s_last = (old & 0x7FFFFFFFu) == pcs - 1 ? 1u : 0u;
-        }
-        __syncthreads();
-        if (!s_last) return;                                     // uniform over the block
-        handoff_acquire();
+        if (!handoff_last(&A.split.done[j], pcs, ovf)) return;   // uniform over the block
         const bool merged = (atomicAdd(&A.split.done[j], 0u) & 0x80000000u) == 0;
         for (uint32_t s = threadIdx.x; s < DB_CAP; s += blockDim.x) { tkeys[s] = EMPTY_KEY; tvals[s] = 0; }
         __syncthreads();
@@ -190,12 +223,9 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
         __syncthreads();
         if (merged) {                     // the pieces' tables added up (an overflow here spills too)
             const uint2* first = A.rows + uint64_t(A.split.hrow[j]) * DB_CAP;
-            for (uint32_t p = 0; p < pcs; ++p)
-                for (uint32_t s = threadIdx.x; s < DB_CAP; s += blockDim.x) {
-                    if (*(volatile uint32_t*)&s_over) break;
-                    const uint2 e = first[uint64_t(p) * DB_CAP + s];
-                    if (e.x != EMPTY_KEY && e.y) db_add(tkeys, tvals, &s_distinct, &s_over, e.x, e.y, A.slot_seed);
-                }
+            rows_for_each(first, A.row_n + A.split.hrow[j], DB_CAP, pcs, &s_over, [&](const uint2& e) {
+                db_add(tkeys, tvals, &s_distinct, &s_over, e.x, e.y, A.slot_seed);
+            });
             if (threadIdx.x == 0) {
                 uint32_t sp = 0;
                 for (uint32_t p = 0; p < pcs; ++p) sp += A.row_special[A.split.hrow[j] + p];
@@ -210,7 +240,7 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
     const bool local = !spill && 2u * s_distinct <= DB_CAP;
     if (threadIdx.x == 0) {
         const uint32_t want = spill ? (n > (1u << 30) ? (1u << 31) : 2u * n) : 2u * s_distinct;
-        uint32_t cap = max(DB_MIN_CAP, next_pow2_u32(want));
+        uint32_t cap = max(A.npool ? NT_MIN_SLOTS >> A.bkt_bits : DB_MIN_CAP, next_pow2_u32(want));
         unsigned long long base = atomicAdd(A.pool_cursor, (unsigned long long)cap);
         if (base + cap > A.pool_cap) {       // cannot happen with a planned workspace
             atomicExch(A.err, 1u);
@@ -225,6 +255,7 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
     const unsigned long long base = s_base;
     const uint32_t cap = 1u << s_log2;
     uint2* region = A.pool + base;
+    bool narrow = false;
     if (base != 0 && local) {
         // take the entries out, clear, reinsert with mask cap - 1 (the
         // lookup's probe sequence), then copy slots [0, cap) out coalesced
@@ -249,6 +280,21 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
         }
         __syncthreads();
         for (uint32_t s = threadIdx.x; s < cap; s += blockDim.x) region[s] = make_uint2(tkeys[s], tvals[s]);
+        if (A.npool) {
+            // the narrow form, in the same place of its own pool
+            __syncthreads();
+            for (uint32_t s = threadIdx.x; s < cap; s += blockDim.x) tkeys[s] = 0;
+            if (threadIdx.x == 0) s_last = 1;
+            __syncthreads();
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (ek[u] != EMPTY_KEY) ok = nt_insert(tkeys, s_log2, ek[u], ev[u], A.bkt_seed, A.bkt_bits) && ok;
+            if (!ok) s_last = 0;
+            __syncthreads();
+            for (uint32_t s = threadIdx.x; s < cap; s += blockDim.x) A.npool[base + s] = tkeys[s];
+            narrow = s_last != 0;
+        }
     } else if (base != 0) {
         for (uint32_t s = threadIdx.x; s < cap; s += blockDim.x) region[s] = make_uint2(EMPTY_KEY, 0u);
         __threadfence();
@@ -273,6 +319,7 @@ MJ_KERNEL(k_dbuild, DB_THREADS, DBuildArgs) {
         e.log2cap = s_log2;
         e.special = s_special;
         A.dir[j] = e;
+        if (A.ndir) A.ndir[j] = narrow && base >> 4 < (1u << 27) ? (uint32_t)(base >> 4) << 5 | s_log2 : 0u;
     }
 }
 
@@ -340,7 +387,7 @@ __device__ __forceinline__ void w_table_add(const WTable& T, uint32_t b, unsigne
 __device__ void w_accumulate(const uint2* S, uint32_t s0, uint32_t s1, const DirEntry* ddir,
                              const uint2* dpool, uint32_t c_seed, uint32_t c_bits,
                              uint32_t slot_seed, uint32_t w_seed, uint32_t level, uint32_t pass,
-                             const WTable& T) {
+                             const WTable& T, const uint32_t* ldir = nullptr, const uint32_t* npool = nullptr) {
     const int nthr = blockDim.x;
     for (uint32_t q = s0 + threadIdx.x; q < s1; q += 4 * nthr) {
         if (*(volatile uint32_t*)T.over) break;
@@ -354,7 +401,12 @@ __device__ void w_accumulate(const uint2* S, uint32_t s0, uint32_t s1, const Dir
             live[u] = idx < s1 && (level == 0 || pass_of(sv[u].x, w_seed, level) == pass);
             cc[u] = sv[u].y;
         }
-        dtab_lookup4(ddir, dpool, cc, live, c_seed, c_bits, slot_seed, w);
+        if (npool) {
+            nt_lookup4(ldir, npool, cc, live, c_seed, c_bits, w);
+            dtab_wide4(ddir, dpool, cc, c_seed, c_bits, slot_seed, w);
+        } else {
+            dtab_lookup4(ddir, dpool, cc, live, c_seed, c_bits, slot_seed, w);
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const unsigned long long v = w[u];
@@ -368,16 +420,11 @@ __device__ void w_accumulate(const uint2* S, uint32_t s0, uint32_t s1, const Dir
 
 // The pieces' W tables of a split bucket added into the LDS table (and
 // their sums for b = 0xFFFFFFFF into T.special); sets *over as above.
-__device__ void w_merge_rows(const WSlot* rows, const unsigned long long* rspecial, uint32_t pcs,
-                             uint32_t w_seed, const WTable& T) {
-    for (uint32_t r = 0; r < pcs; ++r) {
-        const WSlot* row = rows + uint64_t(r) * CELL_CAP;
-        for (uint32_t t = threadIdx.x; t < CELL_CAP; t += blockDim.x) {
-            if (*(volatile uint32_t*)T.over) break;
-            const WSlot e = row[t];
-            if (e.key != EMPTY_KEY && e.w) w_table_add(T, e.key, e.w, w_seed);
-        }
-    }
+__device__ void w_merge_rows(const WSlot* rows, const uint32_t* row_n, const unsigned long long* rspecial,
+                             uint32_t pcs, uint32_t w_seed, const WTable& T) {
+    rows_for_each(rows, row_n, CELL_CAP, pcs, T.over, [&](const WSlot& e) {
+        if (e.w) w_table_add(T, e.key, e.w, w_seed);
+    });
     if (threadIdx.x == 0) {
         unsigned long long sp = 0;
         for (uint32_t r = 0; r < pcs; ++r) sp += rspecial[r];
@@ -485,8 +532,12 @@ k_wbuild(WBuildArgs A) {
     __shared__ uint32_t s_distinct, s_over, s_log2, s_global;
     __shared__ uint32_t st_level[64], st_pass[64];
     __shared__ int s_sp;
-    __shared__ uint32_t s_last;
+    __shared__ uint32_t s_narrow, s_rown;
+    __shared__ uint32_t ldir[1u << NT_MAX_BITS];       // T's narrow directory
     const WTable T{wkeys, wvals, &w_special, &s_distinct, &s_over};
+    if (A.dnpool)
+        for (uint32_t j = threadIdx.x; j < (1u << A.c_bits); j += blockDim.x) ldir[j] = A.dndir[j];
+    if (threadIdx.x == 0) s_narrow = 0;                // (ordered by the barriers before both are read)
     // the block's work item: a bucket, or a piece of a split bucket (heavy
     // keys; listed first so that they start first)
     uint32_t i = blockIdx.x, piece = 0, pcs = 1;
@@ -508,31 +559,23 @@ k_wbuild(WBuildArgs A) {
         const uint32_t q0 = s0 + (uint32_t)(uint64_t(len) * piece / pcs);
         const uint32_t q1 = s0 + (uint32_t)(uint64_t(len) * (piece + 1) / pcs);
         for (uint32_t s = threadIdx.x; s < CELL_CAP; s += nthr) { wkeys[s] = EMPTY_KEY; wvals[s] = 0; }
-        if (threadIdx.x == 0) { w_special = 0; s_distinct = 0; s_over = 0; }
+        if (threadIdx.x == 0) { w_special = 0; s_distinct = 0; s_over = 0; s_rown = 0; }
         __syncthreads();
-        w_accumulate(A.S, q0, q1, A.ddir, A.dpool, A.c_seed, A.c_bits, A.slot_seed, A.w_seed, 0, 0, T);
+        w_accumulate(A.S, q0, q1, A.ddir, A.dpool, A.c_seed, A.c_bits, A.slot_seed, A.w_seed, 0, 0, T, ldir, A.dnpool);
         __syncthreads();
         const bool ovf = s_over != 0;
         const uint64_t r = uint64_t(A.split.hrow[i]) + piece;
         if (!ovf) {
             WSlot* row = A.rows + r * CELL_CAP;
-            for (uint32_t s = threadIdx.x; s < CELL_CAP; s += nthr) {
+            row_compact(wkeys, CELL_CAP, &s_rown, [&](uint32_t s, uint32_t at) {
                 WSlot v;
                 v.key = wkeys[s]; v.pad = 0; v.w = wvals[s];
-                row[s] = v;
-            }
-            if (threadIdx.x == 0) A.row_special[r] = w_special;
+                row[at] = v;
+            });
+            __syncthreads();
+            if (threadIdx.x == 0) { A.row_special[r] = w_special; A.row_n[r] = s_rown; }
         }
-        handoff_release();
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (ovf) atomicOr(&A.split.done[i], 0x80000000u);
-            const uint32_t old = atomicAdd(&A.split.done[i], 1u);
-            s_last = (old & 0x7FFFFFFFu) == pcs - 1 ? 1u : 0u;
-        }
-        __syncthreads();
-        if (!s_last) return;                                     // uniform over the block
-        handoff_acquire();
+        if (!handoff_last(&A.split.done[i], pcs, ovf)) return;   // uniform over the block
         merged = (atomicAdd(&A.split.done[i], 0u) & 0x80000000u) == 0;
         __syncthreads();
     }
@@ -541,6 +584,7 @@ k_wbuild(WBuildArgs A) {
             WDirEntry e;
             e.offset = 0; e.special = 0; e.log2cap = 31 - __clz(W_MIN_CAP); e.pad = 0;
             A.wdir[i] = e;
+            if (A.ndir) A.ndir[i] = 0;
         }
         return;
     }
@@ -562,7 +606,7 @@ k_wbuild(WBuildArgs A) {
         __syncthreads();
         if (merged) {
             const uint64_t r0 = A.split.hrow[i];
-            w_merge_rows(A.rows + r0 * CELL_CAP, A.row_special + r0, pcs, A.w_seed, T);
+            w_merge_rows(A.rows + r0 * CELL_CAP, A.row_n + r0, A.row_special + r0, pcs, A.w_seed, T);
             __syncthreads();
             if (s_over) {                    // the union overflows: redo this pass from the tuples
                 merged = false;
@@ -571,7 +615,7 @@ k_wbuild(WBuildArgs A) {
             }
         } else {
             w_accumulate(A.S, s0, s1, A.ddir, A.dpool, A.c_seed, A.c_bits, A.slot_seed, A.w_seed,
-                         level, pass, T);
+                         level, pass, T, ldir, A.dnpool);
         }
         __syncthreads();
         if (s_over) {
@@ -591,7 +635,7 @@ k_wbuild(WBuildArgs A) {
                 // a whole table keeps load <= 1/2 when it can be halved, else
                 // it leaves LDS as it is (CELL_CAP slots, load < 7/8)
                 const uint64_t want = whole ? min<uint64_t>(2ull * s_distinct, CELL_CAP) : 2ull * (s1 - s0);
-                uint32_t cap = max(W_MIN_CAP, (uint32_t)min<uint64_t>(uint64_t(1) << 31,
+                uint32_t cap = max(A.npool ? NT_MIN_SLOTS >> A.b_bits : W_MIN_CAP, (uint32_t)min<uint64_t>(uint64_t(1) << 31,
                                                                       next_pow2_u32((uint32_t)min<uint64_t>(want, 1ull << 31))));
                 unsigned long long base = atomicAdd(A.wcursor, (unsigned long long)cap);
                 if (base + cap > A.wcap) {   // cannot happen with a planned workspace
@@ -609,8 +653,9 @@ k_wbuild(WBuildArgs A) {
         const uint32_t cap = 1u << s_log2;
         WSlot* region = A.wpool + base;
         if (base == 0) continue;             // pool exhausted: reported above
-        if (whole && cap < CELL_CAP) {
-            // rehash in place at mask cap - 1, then copy slots [0, cap) out
+        if (whole) {
+            // rehashed in place at mask cap - 1 (unless that is the table's
+            // own), then slots [0, cap) copied out
             constexpr int PER = CELL_CAP / CELL_THREADS;
             uint32_t ek[PER];
             unsigned long long ev[PER];
@@ -620,28 +665,38 @@ k_wbuild(WBuildArgs A) {
                 ek[u] = wkeys[s];
                 ev[u] = wvals[s];
             }
-            __syncthreads();
-            for (uint32_t s = threadIdx.x; s < cap; s += nthr) { wkeys[s] = EMPTY_KEY; wvals[s] = 0; }
-            __syncthreads();
-            const uint32_t cmask = cap - 1;
+            if (cap < CELL_CAP) {
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < cap; s += nthr) { wkeys[s] = EMPTY_KEY; wvals[s] = 0; }
+                __syncthreads();
+                const uint32_t cmask = cap - 1;
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                if (ek[u] == EMPTY_KEY) continue;
-                uint32_t s = slot_hash(ek[u], A.w_seed) & cmask;
-                while (atomicCAS(&wkeys[s], EMPTY_KEY, ek[u]) != EMPTY_KEY) s = (s + 1u) & cmask;
-                wvals[s] = ev[u];
+                for (int u = 0; u < PER; ++u) {
+                    if (ek[u] == EMPTY_KEY) continue;
+                    uint32_t s = slot_hash(ek[u], A.w_seed) & cmask;
+                    while (atomicCAS(&wkeys[s], EMPTY_KEY, ek[u]) != EMPTY_KEY) s = (s + 1u) & cmask;
+                    wvals[s] = ev[u];
+                }
+                __syncthreads();
             }
-            __syncthreads();
             for (uint32_t s = threadIdx.x; s < cap; s += nthr) {
                 WSlot v;
                 v.key = wkeys[s]; v.pad = 0; v.w = wvals[s];
                 region[s] = v;
             }
-        } else if (whole) {                  // same mask: the LDS table as it is
-            for (uint32_t s = threadIdx.x; s < CELL_CAP; s += nthr) {
-                WSlot v;
-                v.key = wkeys[s]; v.pad = 0; v.w = wvals[s];
-                region[s] = v;
+            if (A.npool) {
+                // the narrow form, in the same place of its own pool
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < cap; s += nthr) wkeys[s] = 0;
+                if (threadIdx.x == 0) s_narrow = 1;
+                __syncthreads();
+                bool ok = true;
+#pragma unroll
+                for (int u = 0; u < PER; ++u)
+                    if (ek[u] != EMPTY_KEY && ev[u]) ok = nt_insert(wkeys, s_log2, ek[u], ev[u], A.b_seed, A.b_bits) && ok;
+                if (!ok) s_narrow = 0;
+                __syncthreads();
+                for (uint32_t s = threadIdx.x; s < cap; s += nthr) A.npool[base + s] = wkeys[s];
             }
         } else {
             if (need_region) {
@@ -668,6 +723,7 @@ k_wbuild(WBuildArgs A) {
         WDirEntry e;
         e.offset = s_base; e.special = s_special_tot; e.log2cap = s_log2; e.pad = 0;
         A.wdir[i] = e;
+        if (A.ndir) A.ndir[i] = s_narrow && s_base >> 4 < (1u << 27) ? (uint32_t)(s_base >> 4) << 5 | s_log2 : 0u;
     }
 }
 
@@ -716,19 +772,14 @@ __device__ __forceinline__ void wtab_lookup4(const WDirEntry* __restrict__ dir,
 template <class TO>
 __device__ __forceinline__ bool split_merge(const BucketItems& B, uint32_t k, uint32_t piece, uint32_t pcs,
                                             TO* rows, uint32_t row_len, TO* acc, uint32_t span) {
-    __shared__ uint32_t s_last;
     TO* mine = rows + (uint64_t(B.hrow[k]) + piece) * row_len;
     for (uint32_t j = threadIdx.x; j < span; j += blockDim.x) mine[j] = acc[j];
-    handoff_release();
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&B.done[k], 1u) == pcs - 1 ? 1u : 0u;
-    __syncthreads();
-    if (!s_last) return false;                                      // uniform over the block
-    handoff_acquire();
+    if (!handoff_last(&B.done[k], pcs)) return false;               // uniform over the block
     const TO* first = rows + uint64_t(B.hrow[k]) * row_len;
     for (uint32_t j = threadIdx.x; j < span; j += blockDim.x) {
         TO v = 0;
-        for (uint32_t r = 0; r < pcs; ++r) v += *(const volatile TO*)&first[uint64_t(r) * row_len + j];
+#pragma unroll 4
+        for (uint32_t r = 0; r < pcs; ++r) v += first[uint64_t(r) * row_len + j];
         acc[j] = v;
     }
     if (threadIdx.x == 0) B.done[k] = 0;                            // for the next kernel over these items
@@ -742,7 +793,10 @@ __device__ __forceinline__ bool split_merge(const BucketItems& B, uint32_t k, ui
 __global__ void __launch_bounds__(COUNT_THREADS)
 k_count(CountArgs A) {
     extern __shared__ unsigned long long cnt[];          // [1 << a_shift]
+    __shared__ uint32_t ldir[1u << NT_MAX_BITS];          // the W tables' narrow directory
     uint32_t k = blockIdx.x, piece = 0;
+    if (A.npool)
+        for (uint32_t j = threadIdx.x; j < (1u << A.b_bits); j += blockDim.x) ldir[j] = A.ndir[j];
     if (A.split.items) {                                  // uniform over the block
         if (blockIdx.x >= *A.split.nitems) return;
         const uint32_t it = A.split.items[blockIdx.x];
@@ -774,7 +828,21 @@ k_count(CountArgs A) {
             rv[u] = live[u] ? A.R[idx] : make_uint2(0u, 0u);
             bb[u] = rv[u].y;
         }
-        wtab_lookup4(A.wdir, A.wpool, bb, live, A.b_seed, A.b_bits, A.w_seed, w);
+        if (A.npool) {
+            uint32_t x[4];
+            nt_lookup4(ldir, A.npool, bb, live, A.b_seed, A.b_bits, x);
+            bool open[4], any = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { open[u] = x[u] == NT_WIDE; any = any || open[u]; w[u] = x[u]; }
+            if (any) {
+                unsigned long long y[4];
+                wtab_lookup4(A.wdir, A.wpool, bb, open, A.b_seed, A.b_bits, A.w_seed, y);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) if (open[u]) w[u] = y[u];
+            }
+        } else {
+            wtab_lookup4(A.wdir, A.wpool, bb, live, A.b_seed, A.b_bits, A.w_seed, w);
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             unsigned long long v = w[u];

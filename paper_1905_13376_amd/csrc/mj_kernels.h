@@ -128,14 +128,111 @@ struct DBuildArgs {
     unsigned long long pool_cap;
     uint32_t* err;               // set to 1 if the pool is exhausted
     // optional (heavy keys): buckets split into pieces, one workgroup each;
-    // each piece's counts (DB_CAP slots of (key, count)) and its count of
-    // key 0xFFFFFFFF by scratch row; split.done[bucket] counts finished
+    // each piece's counts (at most DB_CAP (key, count) entries) and its count
+    // of key 0xFFFFFFFF by scratch row; split.done[bucket] counts finished
     // pieces, its top bit set when a piece's table overflowed
     BucketItems split;
     uint2* rows = nullptr;
     uint32_t* row_special = nullptr;
+    uint32_t* row_n = nullptr;           // entries of each row
+    // optional: the narrow form of each table (below), bits of the bucket
+    // number and the seed of its hash
+    uint32_t* npool = nullptr;
+    uint32_t* ndir = nullptr;
+    uint32_t bkt_bits = 0, bkt_seed = 0;
 };
 MJ_KERNEL_DECL(k_dbuild, DBuildArgs);
+
+// ------------------------------------------------------- narrow tables
+// A second form of a bucketed (key, value) table for lookups of random keys:
+// 4-byte slots, in aligned groups of four read by one 16-byte load, so that
+// the tables of 10^6 keys fit an XCD's L2 (8- or 16-byte slots fetch a line
+// of the last-level cache per lookup).  A slot is meta << NT_VALUE_BITS |
+// min(value, NT_SAT); 0 is an empty slot (values are at least 1).  The
+// bucket hash is a bijection of the keys: of its bits below the bucket number
+// the low ones give the home group and the rest, the tag, with the number of
+// groups the entry was moved on (at most NT_MAX_MOVE), make up the meta, so
+// a match is exact.  ndir[bucket] = (offset / 16) << 5 | log2 of the slots,
+// or 0 where the table has no narrow form (tag or move too large, key
+// 0xFFFFFFFF apart): the lookup then takes the wide table, as it does for a
+// value of NT_SAT.
+constexpr uint32_t NT_VALUE_BITS = 14, NT_SAT = (1u << NT_VALUE_BITS) - 1u;
+constexpr uint32_t NT_MOVE_BITS = 3, NT_MAX_MOVE = (1u << NT_MOVE_BITS) - 1u;
+constexpr uint32_t NT_TAG_BITS = 32 - NT_VALUE_BITS - NT_MOVE_BITS;
+constexpr uint32_t NT_MAX_BITS = 10;         // bucket bits of a directory copied to LDS
+constexpr uint32_t NT_MIN_BITS = 9;          // fewer: too many tag bits for the slots of a bucket built in LDS
+constexpr uint32_t NT_MIN_SLOTS = 1u << (32 - NT_TAG_BITS + 2);   // least slots of all buckets together
+constexpr uint32_t NT_WIDE = 0xFFFFFFFFu;    // lookup result: ask the wide table
+
+__host__ __device__ __forceinline__ bool nt_bits_ok(uint32_t bkt_bits) {
+    return bkt_bits >= NT_MIN_BITS && bkt_bits <= NT_MAX_BITS;
+}
+
+// The entry's slot value without its move, and its home group.
+__device__ __forceinline__ uint32_t nt_home(uint32_t key, uint32_t bkt_seed, uint32_t bkt_bits, uint32_t log2cap,
+                                            uint32_t& tag) {
+    const uint32_t r = bkt_bits ? mix32(key, bkt_seed) & ((1u << (32 - bkt_bits)) - 1u) : mix32(key, bkt_seed);
+    const uint32_t gb = log2cap - 2;
+    tag = r >> gb;
+    return r & ((1u << gb) - 1u);
+}
+
+// Put an entry into a table of 1 << log2cap slots in LDS; false when it would
+// move too far.
+__device__ __forceinline__ bool nt_insert(uint32_t* tab, uint32_t log2cap, uint32_t key, unsigned long long value,
+                                          uint32_t bkt_seed, uint32_t bkt_bits) {
+    uint32_t tag;
+    uint32_t g = nt_home(key, bkt_seed, bkt_bits, log2cap, tag);
+    const uint32_t gmask = (1u << (log2cap - 2)) - 1u;
+    const uint32_t v = value < NT_SAT ? (uint32_t)value : NT_SAT;
+    for (uint32_t m = 0; m <= NT_MAX_MOVE; ++m, g = (g + 1u) & gmask) {
+        const uint32_t e = ((tag << NT_MOVE_BITS | m) << NT_VALUE_BITS) | v;
+        for (uint32_t s = 0; s < 4; ++s)
+            if (tab[4 * g + s] == 0 && atomicCAS(&tab[4 * g + s], 0u, e) == 0u) return true;
+    }
+    return false;
+}
+
+// The rest of a lookup whose home group has been read: 0 when absent.
+// (Insertions fill a group before they move on, so a group with an empty
+// slot ends the walk.)
+__device__ __forceinline__ uint32_t nt_walk(const uint32_t* __restrict__ tab, uint32_t gmask, uint32_t g, uint32_t tag,
+                                            u32x4 q) {
+    uint32_t want = tag << NT_MOVE_BITS;
+    for (uint32_t m = 0;; ++m) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (q[s] && (q[s] >> NT_VALUE_BITS) == want) return (q[s] & NT_SAT) == NT_SAT ? NT_WIDE : q[s] & NT_SAT;
+        if (m == NT_MAX_MOVE || !q[0] || !q[1] || !q[2] || !q[3]) return 0u;
+        ++want;
+        g = (g + 1u) & gmask;
+        q = *reinterpret_cast<const u32x4*>(tab + 4 * g);
+    }
+}
+
+// Four independent lookups (home groups in flight together); NT_WIDE where
+// the wide table has to be asked.
+__device__ __forceinline__ void nt_lookup4(const uint32_t* ldir, const uint32_t* __restrict__ npool,
+                                           const uint32_t (&key)[4], const bool (&live)[4], uint32_t bkt_seed,
+                                           uint32_t bkt_bits, uint32_t (&out)[4]) {
+    u32x4 q[4];
+    uint32_t g[4], tag[4], e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        e[u] = live[u] && key[u] != EMPTY_KEY ? ldir[top_bits(mix32(key[u], bkt_seed), bkt_bits)] : 0u;
+        g[u] = tag[u] = 0;
+        q[u] = u32x4{0u, 0u, 0u, 0u};
+        if (e[u]) {
+            g[u] = nt_home(key[u], bkt_seed, bkt_bits, e[u] & 31u, tag[u]);
+            q[u] = *reinterpret_cast<const u32x4*>(npool + (uint64_t(e[u] >> 5) << 4) + 4 * g[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (!e[u]) { out[u] = live[u] ? NT_WIDE : 0u; continue; }
+        out[u] = nt_walk(npool + (uint64_t(e[u] >> 5) << 4), (1u << ((e[u] & 31u) - 2u)) - 1u, g[u], tag[u], q[u]);
+    }
+}
 
 // Lookup in a bucketed multiplicity table; 0 when absent.
 __device__ __forceinline__ uint32_t dtab_lookup(const DirEntry* __restrict__ dir,
@@ -198,6 +295,21 @@ __device__ __forceinline__ void dtab_lookup4(const DirEntry* __restrict__ dir,
     }
 }
 
+// The lookups the narrow form left open (NT_WIDE), together.
+__device__ __forceinline__ void dtab_wide4(const DirEntry* __restrict__ dir, const uint2* __restrict__ pool,
+                                           const uint32_t (&key)[4], uint32_t bkt_seed, uint32_t bkt_bits,
+                                           uint32_t slot_seed, uint32_t (&out)[4]) {
+    bool open[4];
+    bool any = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { open[u] = out[u] == NT_WIDE; any = any || open[u]; }
+    if (!any) return;
+    uint32_t x[4];
+    dtab_lookup4(dir, pool, key, open, bkt_seed, bkt_bits, slot_seed, x);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) if (open[u]) out[u] = x[u];
+}
+
 // --------------------------------------------------------- linear cells
 constexpr int CELL_THREADS = MJ_CELL_THREADS;
 constexpr uint32_t CELL_CAP = 4096;                      // W-table slots (LDS)
@@ -250,13 +362,20 @@ struct WBuildArgs {
     unsigned long long wcap;
     uint32_t* err;               // set to 1 if the pool is exhausted
     // optional (heavy keys): buckets of S split into pieces, one workgroup
-    // each; each piece's W table (CELL_CAP slots) and its sum for
+    // each; each piece's W table (at most CELL_CAP entries) and its sum for
     // b = 0xFFFFFFFF by scratch row; split.done[bucket] counts finished
     // pieces, its top bit set when a piece's table overflowed (the last
     // piece then builds the bucket from its tuples)
     BucketItems split;
     WSlot* rows = nullptr;
     unsigned long long* row_special = nullptr;
+    uint32_t* row_n = nullptr;           // entries of each row
+    // optional narrow forms: T's tables (read) and the W tables (written)
+    const uint32_t* dnpool = nullptr;
+    const uint32_t* dndir = nullptr;
+    uint32_t* npool = nullptr;
+    uint32_t* ndir = nullptr;
+    uint32_t b_bits = 0, b_seed = 0;
 };
 __global__ void k_wbuild(WBuildArgs A);
 
@@ -393,6 +512,8 @@ struct CountArgs {
     uint32_t* err;               // set to 1 for an a >= a_domain
     BucketItems split;           // optional: ranges split into pieces
     unsigned long long* rows = nullptr;  // scratch rows of 2^a_shift entries
+    const uint32_t* npool = nullptr;     // optional: the W tables' narrow form
+    const uint32_t* ndir = nullptr;
 };
 __global__ void k_count(CountArgs A);
 
@@ -589,6 +710,8 @@ struct CasProbeArgs {
     const uint16_t* deg16;
     uint32_t c_domain;
     const uint32_t* use_wide;
+    const uint32_t* npool = nullptr;  // optional: T's tables' narrow form
+    const uint32_t* ndir = nullptr;
 };
 MJ_KERNEL_DECL(k_cas_probe, CasProbeArgs);
 

@@ -171,10 +171,13 @@ int analytic_plan(int kind, mj_plan_t& p, int num_cu, const DeviceModel& m) {
     const double R = (double)p.n_r, S = (double)p.n_s, T = (double)p.n_t;
     const double I = (double)p.join2_size;
     if (kind == MJ_LINEAR) {
-        // b-buckets: about 16K S tuples per W table; c-buckets: about 32K T
-        // tuples per multiplicity table (at most 2^10 of either)
-        p.log2_nb = std::min<uint32_t>(10, ceil_log2((p.n_s + 16383) / 16384));
-        p.log2_nc = std::min<uint32_t>(10, ceil_log2((p.n_t + 32767) / 32768));
+        // about 4K S tuples per W table and 4K T tuples per multiplicity table
+        // (at most 2^10 of either): at least two workgroups a CU from 2^21
+        // tuples, and tables small enough beside their number for the narrow
+        // form (with 16K and 32K: 128 workgroups built the tables of 4 x 10^6
+        // T tuples in 135 us, 66 us now)
+        p.log2_nb = std::min<uint32_t>(10, ceil_log2((p.n_s + 4095) / 4096));
+        p.log2_nc = std::min<uint32_t>(10, ceil_log2((p.n_t + 4095) / 4096));
         p.est_ms_3way = model_linear_3way_ms(m, R, S, T);
         // small relations with dense keys: three launches and no partition
         // (run_small; 18 us at 16,384 tuples where the star plan takes 95)
@@ -194,8 +197,8 @@ int analytic_plan(int kind, mj_plan_t& p, int num_cu, const DeviceModel& m) {
             if (t < best) { best = t; best_k = k; }
         }
         p.log2_share = best_k;
-        p.log2_nb = std::min<uint32_t>(10, ceil_log2((p.n_s + 32767) / 32768));
-        p.log2_nc = std::min<uint32_t>(10, ceil_log2((p.n_t + 32767) / 32768));
+        p.log2_nb = std::min<uint32_t>(10, ceil_log2((p.n_s + 4095) / 4096));
+        p.log2_nc = std::min<uint32_t>(10, ceil_log2((p.n_t + 4095) / 4096));
         p.est_ms_3way = best;
         p.est_ms_cascade = model_cyclic_cascade_ms(m, R, S, T, I);
     }
