@@ -287,9 +287,11 @@ MJ_KERNEL(k_star_reduce, STAR_REDUCE_THREADS, StarReduceArgs) {
     __shared__ unsigned long long part[STAR_REDUCE_THREADS / 64][64];
     uint32_t ngroups;
     if (A.by_b) {
+        // k_star_group_b's rule: otherwise its sums are in A.out already
+        const uint32_t k = (uint32_t)A.rid[A.pool_slots + 1];
         const bool lds = (1u << A.rdir[0].log2cap) <= STAR_LDS_SLOTS &&
-                         (1u << A.tdir[0].log2cap) <= STAR_LDS_SLOTS;
-        ngroups = lds ? (uint32_t)A.rid[A.pool_slots + 1] : 0u;
+                         (1u << A.tdir[0].log2cap) <= STAR_LDS_SLOTS && k <= STAR_LDS_SLOTS / 2;
+        ngroups = lds ? k : 0u;
     } else {
         ngroups = A.ngroups_max <= STAR_GROUPS ? A.ngroups_max : 0u;
     }
