@@ -381,7 +381,7 @@ def star_path(mj, ctx):
         kern = {k: v[0] / max(v[1], 1) for k, v in kp.items()}          # ms per launch
         ent = {"ms": round(ms, 4), "tuples_per_s": n_in / (ms * 1e-3), "sum_equals_closed_form": ok,
                "kernels_us": {k: round(v * 1e3, 1) for k, v in sorted(kern.items(), key=lambda kv: -kv[1])[:6]}}
-        kg = next((k for k in ("k_star_group_b", "k_star_group_a") if k in kern), None)
+        kg = next((k for k in ("k_star_stream", "k_star_group_b", "k_star_group_a") if k in kern), None)
         if name == "star" and kg:
             us = kern[kg] * 1e3
             nbytes = 8 * S.shape[0]                      # the fact relation, read once

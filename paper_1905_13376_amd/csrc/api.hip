@@ -1239,10 +1239,25 @@ int run_star3(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel* T, ui
     L = star_layout(ws, p, false);
     Prof* prof = &ctx->prof;
     unsigned long long* count = reinterpret_cast<unsigned long long*>(count_out);
+    const bool some = R->n && S->n && T->n && a_domain;
+    if (some && R->n <= STAR_SMALL && T->n <= STAR_SMALL) {
+        StarStreamArgs A;
+        A.r0 = R->col0; A.r1 = R->col1; A.r_stride = R->stride; A.n_r = (uint32_t)R->n;
+        A.s0 = S->col0; A.s1 = S->col1; A.s_stride = S->stride; A.n_s = S->n;
+        A.t0 = T->col0; A.t_stride = T->stride; A.n_t = (uint32_t)T->n;
+        A.partial = L.partial; A.rep = L.occ; A.count = count; A.a_domain = a_domain;
+        const uint32_t grid = star_grid_cu(S->n, ctx->num_cu);
+        MJ_LAUNCHM(prof, "k_star_stream", k_star_stream, dim3(grid), dim3(STAR_THREADS), 0, s, A);
+        StarFinishArgs F;
+        F.r0 = R->col0; F.r_stride = R->stride; F.n_r = A.n_r;
+        F.partial = L.partial; F.nblocks = grid; F.rep = L.occ; F.count = count; F.a_domain = a_domain;
+        MJ_LAUNCHM(prof, "k_star_finish", k_star_finish, dim3((A.n_r + 63) / 64), dim3(STAR_REDUCE_THREADS), 0, s, F);
+        return MJ_OK;
+    }
     if (a_domain)
         MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(grid_for(a_domain, 256, 4096)), dim3(256), 0, s,
                   count, (uint64_t)a_domain, 0ull);
-    if (R->n == 0 || S->n == 0 || T->n == 0 || a_domain == 0) return MJ_OK;
+    if (!some) return MJ_OK;
     int st;
     if ((st = star_prepare(prof, *R, *T, p, L, s))) return st;
     // W[id(b)] = sum of mult_T(c) over S, one pass over the fact relation

@@ -549,6 +549,37 @@ constexpr uint32_t STAR_GRID = 1024;       // most workgroups of a launch
 constexpr uint64_t STAR_ROWS_PER_BLOCK = 16384;
 static_assert(STAR_GROUPS < STAR_STRIDE, "the cascade's sums fit a workgroup's stride");
 
+// R and T of at most STAR_SMALL tuples each (what the planner takes for a
+// star): every workgroup builds its own tables from the tuples in LDS, two
+// launches in all.  With 2^26 tuples in S and 4096-tuple dimensions 167 us
+// a join, 437 us through the tables in memory and their 26 launches; with
+// 2^22 tuples 59 us, 170 us.  Larger R or T do not fit a workgroup's LDS
+// with the sums and take the general path.
+constexpr uint32_t STAR_SMALL = 4096;
+constexpr uint32_t STAR_BKTS = 2048;       // displacement buckets of a table
+constexpr uint32_t STAR_PAIRS = 4;         // pairs of rows per thread per step (2: 7 % longer)
+
+struct StarStreamArgs {
+    const uint32_t* r0; const uint32_t* r1; int64_t r_stride; uint32_t n_r;   // R(A, B)
+    const uint32_t* s0; const uint32_t* s1; int64_t s_stride; uint64_t n_s;   // S(B, C)
+    const uint32_t* t0; int64_t t_stride; uint32_t n_t;                       // T's C column
+    unsigned long long* partial;   // [gridDim][STAR_STRIDE] sums per first R tuple of a B value
+    uint32_t* rep;                 // [n_r + 2] first R tuple with the same B; the finish's ticket, its flag
+    unsigned long long* count;     // zeroed here
+    uint32_t a_domain;
+};
+MJ_KERNEL_DECL(k_star_stream, StarStreamArgs);
+
+struct StarFinishArgs {
+    const uint32_t* r0; int64_t r_stride; uint32_t n_r;
+    const unsigned long long* partial;
+    uint32_t nblocks;
+    uint32_t* rep;
+    unsigned long long* count;
+    uint32_t a_domain;
+};
+MJ_KERNEL_DECL(k_star_finish, StarFinishArgs);
+
 struct StarTable {                 // a one-bucket table of (key, multiplicity) slots
     const DirEntry* dir;           // [1]
     const uint2* pool;
