@@ -85,8 +85,11 @@ MJ_KERNEL(k_run_count, RUN_THREADS, RunLaunch) {
 }
 
 // Every tile numbers its runs from the heads before it and writes each run's
-// key, start and directory entries: a head knows the run before it from the
-// key before it, so the directory needs no pass of its own.  (As separate
+// key, start and directory entries: a round of 64 keys knows the prefix before
+// it from the key before it, so the directory needs no pass of its own, and
+// its lanes write the entries side by side (two arrays of 2^22 keys: 87 us for
+// 4000 runs each and 50 us for 2^18; each head filling its own gap 632 and
+// 80 us).  (As separate
 // flag, scan, compact and directory passes the four arrays of a join of 10^6
 // tuples took 26 launches and 0.25 ms; two launches and 62 us now.)
 MJ_KERNEL(k_run_emit, RUN_THREADS, RunLaunch) {
@@ -112,20 +115,32 @@ MJ_KERNEL(k_run_emit, RUN_THREADS, RunLaunch) {
     }
     const uint64_t at = beg + w * (RUN_ROUNDS * WAVE) + lane;
     const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    uint32_t d0 = 0;                                  // the first directory entry not written before this round
+    if (J.dir && at - lane > 0 && at - lane < J.n) d0 = top_bits((uint32_t)(J.keys[at - lane - 1] >> 32), J.bits) + 1u;
 #pragma unroll
     for (int k = 0; k < RUN_ROUNDS; ++k) {
         const uint64_t i = at + k * WAVE;
         const uint32_t hi = (uint32_t)(key[k] >> 32);
+        if (J.dir && i - lane < J.n) {                // uniform over the wave
+            // entries d0 up to the last key's prefix, one a lane: the first of
+            // these keys with that prefix or a greater one is a head
+            const uint32_t pk = i < J.n ? top_bits(hi, J.bits) : 0xFFFFFFFFu;
+            const uint32_t last = wave_read(pk, (int)min<uint64_t>(J.n - (i - lane), WAVE) - 1);
+            for (; d0 <= last; d0 += WAVE) {
+                const uint32_t p = d0 + lane;
+                int j = 0;
+#pragma unroll
+                for (int step = WAVE / 2; step > 0; step /= 2)
+                    if ((uint32_t)__shfl((int)pk, j + step - 1, WAVE) < p) j += step;
+                if (p <= last) J.dir[p] = r + (uint32_t)__popcll(heads[k] & ((1ull << j) - 1ull));
+            }
+            d0 = last + 1u;
+        }
         if (i < J.n && J.low) J.low[i] = (uint32_t)key[k];
         if ((heads[k] >> lane) & 1ull) {
             const uint32_t run = r + (uint32_t)__popcll(heads[k] & lt_mask);
             J.run_key[run] = hi;
             J.run_start[run] = (uint32_t)i;
-            if (J.dir) {
-                const uint32_t p0 = i == 0 ? 0u : top_bits((uint32_t)(J.keys[i - 1] >> 32), J.bits) + 1u;
-                const uint32_t p1 = top_bits(hi, J.bits);
-                for (uint32_t p = p0; p <= p1; ++p) J.dir[p] = run;
-            }
         }
         r += (uint32_t)__popcll(heads[k]);
     }
