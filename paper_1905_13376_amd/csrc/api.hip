@@ -1339,18 +1339,21 @@ struct FmLayout {
     uint32_t* tsk;                    // [T runs][FM_WORDS]
     uint32_t* wsk;                    // [S runs][FM_WORDS]
     RelPart Ra;                       // R by range of A
+    BucketItems Rsplit;
     uint32_t* err;
     uint32_t a_bits, a_shift;
     bool by_range;
     size_t bytes;
 };
 
-// ranges of A of at most 2^FM_RANGE_MAX_SHIFT values, about 32K R tuples
-// each, at most 2^PART_MAX_BITS of them; beyond that the sketches are ORed
-// straight into the output
+// ranges of A of at most 2^FM_RANGE_MAX_SHIFT values, at most 2^PART_MAX_BITS
+// of them; beyond that the sketches are ORed straight into the output.  Up to
+// 1024 ranges from 2048 R tuples each (four workgroups a CU; 256 ranges of
+// 16K tuples left a CU with four waves), more for larger A domains or R
 void fm_ranges(uint64_t n_r, uint32_t a_domain, uint32_t& bits, uint32_t& shift, bool& by_range) {
     const uint32_t L = ceil_log2(std::max<uint32_t>(a_domain, 1));
-    const uint32_t want = ceil_log2((n_r + 32767) / 32768);
+    const uint32_t fill = std::min<uint32_t>(10, n_r >= 4096 ? ceil_log2(n_r / 2048 + 1) - 1 : 0);
+    const uint32_t want = std::max(fill, ceil_log2((n_r + 32767) / 32768));
     bits = std::max<uint32_t>(std::min<uint32_t>(want, L), L > FM_RANGE_MAX_SHIFT ? L - FM_RANGE_MAX_SHIFT : 0);
     shift = L - bits;
     by_range = bits <= PART_MAX_BITS;
@@ -1374,6 +1377,7 @@ FmLayout fm_layout(void* ws, uint64_t nr, uint64_t ns, uint64_t nt, uint32_t a_d
     L.wsk = B.take<uint32_t>(std::max<uint64_t>(ns, 1) * FM_WORDS);
     fm_ranges(nr, a_domain, L.a_bits, L.a_shift, L.by_range);
     take_part(B, L.Ra, nr, L.a_bits);
+    if (L.by_range) L.Rsplit = take_items(B, nr, L.a_bits);
     L.err = B.take<uint32_t>(1);
     L.bytes = B.off + 256;
     return L;
@@ -2340,24 +2344,27 @@ int mj_linear3_distinct(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_
     }
     // T grouped by C as (mix(c), mix(d)) and S by B as (mix(b), mix(c)): only
     // the grouping by the high word matters to an OR of sketches
+    // (one and the same array when S and T are one relation, as in a self-join)
+    const int arrays = same_rel(*S, *T) ? 1 : 2;
+    if (arrays == 1) { L.Sk = L.Tk; L.S = L.T; }
     const SortSpec sort[2] = {{T, 0, false, L.Tk, L.tmp[0], L.rs_hist[0], L.rs_counts},
                               {S, 0, false, L.Sk, L.tmp[1], L.rs_hist[1], L.rs_counts + 256}};
-    if ((st = launch_sorts(prof, sort, 2, seed, 4, s))) return st;
+    if ((st = launch_sorts(prof, sort, arrays, seed, 4, s))) return st;
     const RunSpec run[2] = {{L.Tk, T->n, L.T, nullptr}, {L.Sk, S->n, L.S, nullptr}};
-    if ((st = launch_runs(prof, run, 2, s))) return st;
+    if ((st = launch_runs(prof, run, arrays, s))) return st;
     // per run of T the OR of bit(mix(d))
     FmTArgs Ft;
     Ft.T = run_index(L.T); Ft.Tk = L.Tk; Ft.tsk = L.tsk;
     MJ_LAUNCH(prof, "k_fm_tsketch", k_fm_tsketch, dim3(grid_for(T->n, FM_THREADS, 16384)), dim3(FM_THREADS),
               0, s, Ft);
-    MJ_LAUNCH(prof, "k_fm_tsketch_long", k_fm_tsketch_long, dim3(grid_for(T->n, FM_THREADS, 4096)),
+    MJ_LAUNCH(prof, "k_fm_tsketch_long", k_fm_tsketch_long, dim3(grid_for((T->n + FM_TILE - 1) / FM_TILE, FM_THREADS / WAVE, 4096)),
               dim3(FM_THREADS), 0, s, Ft);
     // per run of S the OR of T's sketches of its C values
     FmWArgs Fw;
     Fw.S = run_index(L.S); Fw.Sk = L.Sk; Fw.T = run_index(L.T); Fw.tsk = L.tsk; Fw.wsk = L.wsk;
     MJ_LAUNCH(prof, "k_fm_wsketch", k_fm_wsketch, dim3(grid_for(S->n, FM_THREADS, 16384)), dim3(FM_THREADS),
               0, s, Fw);
-    MJ_LAUNCH(prof, "k_fm_wsketch_long", k_fm_wsketch_long, dim3(grid_for(S->n, FM_THREADS, 4096)),
+    MJ_LAUNCH(prof, "k_fm_wsketch_long", k_fm_wsketch_long, dim3(grid_for((S->n + FM_TILE - 1) / FM_TILE, FM_THREADS / WAVE, 4096)),
               dim3(FM_THREADS), 0, s, Fw);
     // R by range of A (or as one bucket in the global mode): per a the OR of
     // the sketches of its B values
@@ -2367,13 +2374,21 @@ int mj_linear3_distinct(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_
     P.job[0].range_on = 1;
     P.job[0].range_shift = L.a_shift;
     P.job[0].out_pair = L.Ra.pairs;
+    P.job[0].split = L.Rsplit;
     if ((st = launch_partition(prof, "r", P, s))) return st;
     FmAArgs Fa;
+    Fa.split = L.Rsplit;
     Fa.R = L.Ra.pairs; Fa.rstarts = L.Ra.starts; Fa.n = R->n; Fa.a_shift = L.a_shift; Fa.a_domain = a_domain;
     Fa.seed = seed; Fa.S = run_index(L.S); Fa.wsk = L.wsk; Fa.sketch = sketch; Fa.est = est;
     Fa.err = L.err;
     if (L.by_range) {
-        MJ_LAUNCH(prof, "k_fm_asketch", k_fm_asketch, dim3(1u << L.a_bits), dim3(FM_THREADS), 0, s, Fa);
+        const uint32_t items = items_grid(L.Rsplit, R->n, L.a_bits);
+        if (R->n > L.Rsplit.chunk)
+            MJ_LAUNCH(prof, "k_fm_clear", k_fm_clear, dim3(1u << L.a_bits), dim3(FM_A_THREADS), 0, s, Fa);
+        if (L.a_shift <= FM_RANGE_SHIFT)
+            MJ_LAUNCH(prof, "k_fm_asketch", k_fm_asketch, dim3(items), dim3(FM_A_THREADS), 0, s, Fa);
+        else
+            MJ_LAUNCH(prof, "k_fm_asketch_wide", k_fm_asketch_wide, dim3(items), dim3(FM_A_THREADS), 0, s, Fa);
     } else {
         MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(grid_for(words, 256, 4096)), dim3(256), 0, s,
                   sketch, words, 0u);
@@ -2407,12 +2422,15 @@ int mj_linear3_materialize(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const 
     // the seed only groups equal keys; the output order does not depend on it
     const uint32_t seed = 0x2545F491u;
     // T grouped by C with its raw D values, S by B with its raw C values; the
-    // sort is stable, so every run keeps its relation's order
+    // sort is stable, so every run keeps its relation's order (one and the
+    // same array when S and T are one relation)
+    const int arrays = same_rel(*S, *T) ? 1 : 2;
+    if (arrays == 1) { L.Sk = L.Tk; L.S = L.T; L.sc = L.td; }
     const SortSpec sort[2] = {{T, 0, true, L.Tk, L.tmp[0], L.rs_hist[0], L.rs_counts},
                               {S, 0, true, L.Sk, L.tmp[1], L.rs_hist[1], L.rs_counts + 256}};
-    if ((st = launch_sorts(prof, sort, 2, seed, 4, s))) return st;
+    if ((st = launch_sorts(prof, sort, arrays, seed, 4, s))) return st;
     const RunSpec run[2] = {{L.Tk, T->n, L.T, L.td}, {L.Sk, S->n, L.S, L.sc}};
-    if ((st = launch_runs(prof, run, 2, s))) return st;
+    if ((st = launch_runs(prof, run, arrays, s))) return st;
     EmitSArgs Es;
     Es.sc = L.sc; Es.ns = S->n; Es.T = run_index(L.T); Es.seed = seed; Es.tdeg = L.tdeg; Es.tst = L.tst;
     MJ_LAUNCH(prof, "k_emit_sdeg", k_emit_sdeg, dim3(grid_for((S->n + 3) / 4, 256, 16384)), dim3(256), 0, s, Es);

@@ -899,17 +899,20 @@ __device__ __forceinline__ void run_find4(const RunIndex& X, const uint32_t (&ke
 // seed, are the sketch's hash values.
 constexpr int FM_WORDS = 16;
 constexpr int FM_THREADS = 256;
-constexpr uint32_t FM_RANGE_MAX_SHIFT = 10;   // A values per LDS range (64 KB of sketches)
+constexpr int FM_A_THREADS = 512;
+constexpr uint32_t FM_RANGE_SHIFT = 8;        // A values per LDS range (16 KB of sketches, 4 workgroups a CU)
+constexpr uint32_t FM_RANGE_MAX_SHIFT = 10;   // ... for A domains that need it (64 KB)
+constexpr uint32_t FM_TILE = 512;            // elements per wave of the long runs
 constexpr uint32_t FM_NONE = 0xFFFFFFFFu;
-constexpr uint32_t FM_SHORT = 64;             // runs up to this length: one thread; longer: one wave
+constexpr uint32_t FM_SHORT = 64;             // runs up to this length: 16 lanes; longer: shared by waves
 
 struct FmTArgs {                   // per run of T by C: OR of the bits of its D values
     RunIndex T;
     const unsigned long long* Tk;  // (mix(c) << 32 | mix(d)), sorted
     uint32_t* tsk;                 // [runs][FM_WORDS]
 };
-__global__ void k_fm_tsketch(FmTArgs A);        // runs of at most FM_SHORT elements, one thread each
-__global__ void k_fm_tsketch_long(FmTArgs A);   // longer runs, one wave each
+__global__ void k_fm_tsketch(FmTArgs A);        // runs of at most FM_SHORT elements; clears longer ones
+__global__ void k_fm_tsketch_long(FmTArgs A);   // longer runs
 
 struct FmWArgs {                   // per run of S by B: OR of T's sketches of its C values
     RunIndex S;
@@ -918,8 +921,8 @@ struct FmWArgs {                   // per run of S by B: OR of T's sketches of i
     const uint32_t* tsk;
     uint32_t* wsk;                 // [runs][FM_WORDS]
 };
-__global__ void k_fm_wsketch(FmWArgs A);        // runs of at most FM_SHORT elements, one thread each
-__global__ void k_fm_wsketch_long(FmWArgs A);   // longer runs, one wave each
+__global__ void k_fm_wsketch(FmWArgs A);        // runs of at most FM_SHORT elements; clears longer ones
+__global__ void k_fm_wsketch_long(FmWArgs A);   // longer runs
 
 struct FmAArgs {                   // per A value: OR of the sketches of its B values
     const uint2* R;                // (a, b): by range of a (range mode), or as given (global mode)
@@ -932,9 +935,12 @@ struct FmAArgs {                   // per A value: OR of the sketches of its B v
     const uint32_t* wsk;
     uint32_t* sketch;              // [a_domain][FM_WORDS]
     double* est;                   // [a_domain] or null
+    BucketItems split;             // range mode: the ranges' pieces
     uint32_t* err;                 // set for an a >= a_domain
 };
+__global__ void k_fm_clear(FmAArgs A);           // range mode: clears the sketches of split ranges
 __global__ void k_fm_asketch(FmAArgs A);         // range mode: writes sketches and estimates
+__global__ void k_fm_asketch_wide(FmAArgs A);    // ... with ranges of more than 2^FM_RANGE_SHIFT A values
 __global__ void k_fm_asketch_global(FmAArgs A);  // global mode: ORs into the zeroed output
 __global__ void k_fm_estimate(FmAArgs A);        // global mode: estimates
 
