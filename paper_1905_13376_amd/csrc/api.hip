@@ -645,33 +645,49 @@ int launch_partition(Prof* prof, const char* tag, PartLaunch& P, hipStream_t st)
     return MJ_OK;
 }
 
-// Partition T.c (or any single column) by bucket and build its tables.
-int launch_tables(Prof* prof, const TableLayout& L, const mj_rel& rel, int col, uint32_t bits,
-                  uint32_t bseed, uint32_t sseed, hipStream_t st) {
-    const uint32_t nb = 1u << bits;
-    MJ_LAUNCHM(prof, "tab:k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.pool),
-                       (uint64_t)(2 * DB_MIN_CAP), EMPTY_KEY);
-    // pool[0..DB_MIN_CAP) stays empty (keys EMPTY); cursor = DB_MIN_CAP; err = 0
-    MJ_LAUNCHM(prof, "tab:k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, st, L.pool_cursor, (uint64_t)1,
-                       (unsigned long long)DB_MIN_CAP);
-    MJ_LAUNCHM(prof, "tab:k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, st, L.err, (uint64_t)1, 0u);
+void add_fill(PartLaunch& P, void* p, uint32_t words, uint32_t v) {
+    P.fill[P.nfill++] = PartFill{static_cast<uint32_t*>(p), words, v};
+}
+void add_fill_u64(PartLaunch& P, unsigned long long* p, uint32_t v) {
+    add_fill(P, p, 1, v);
+    add_fill(P, reinterpret_cast<uint32_t*>(p) + 1, 1, 0);
+}
 
-    PartLaunch P{};
-    P.njobs = 1;
-    P.job[0] = make_job(rel, L.hist, L.counts, L.starts, col, bseed, bits, 0, 0, 0);
-    P.job[0].out_single = L.keys;
-    P.job[0].single_col = col;
-    P.job[0].split = L.split;                    // heavy buckets in pieces
-    int st2 = launch_partition(prof, "tab", P, st);
-    if (st2) return st2;
+// T.c (or any single column) by bucket, as one more job of a partition, and
+// the state its table build starts from: pool[0..DB_MIN_CAP) stays empty
+// (keys EMPTY); cursor = DB_MIN_CAP; err = 0.
+void add_table(PartLaunch& P, const TableLayout& L, const mj_rel& rel, int col, uint32_t bits, uint32_t bseed) {
+    PartJob& J = P.job[P.njobs++];
+    J = make_job(rel, L.hist, L.counts, L.starts, col, bseed, bits, 0, 0, 0);
+    J.out_single = L.keys;
+    J.single_col = col;
+    J.split = L.split;                           // heavy buckets in pieces
+    add_fill(P, L.pool, 2 * DB_MIN_CAP, EMPTY_KEY);
+    add_fill_u64(P, L.pool_cursor, DB_MIN_CAP);
+    add_fill(P, L.err, 1, 0);
+}
+
+// The tables of a partitioned column.
+int launch_dbuild(Prof* prof, const TableLayout& L, const mj_rel& rel, uint32_t bits, uint32_t bseed, uint32_t sseed,
+                  hipStream_t st) {
     DBuildArgs D{};
-    D.keys = L.keys; D.starts = L.starts; D.nbkt = nb; D.slot_seed = sseed;
+    D.keys = L.keys; D.starts = L.starts; D.nbkt = 1u << bits; D.slot_seed = sseed;
     D.dir = L.dir; D.pool = L.pool; D.pool_cursor = L.pool_cursor; D.pool_cap = L.pool_slots;
     D.err = L.err;
     D.split = L.split; D.rows = L.rows; D.row_special = L.row_special; D.row_n = L.row_n;
     D.npool = L.npool; D.ndir = L.ndir; D.bkt_bits = bits; D.bkt_seed = bseed;
     MJ_LAUNCHM(prof, "tab:k_dbuild", k_dbuild, dim3(items_grid(L.split, rel.n, bits)), dim3(DB_THREADS), 0, st, D);
     return MJ_OK;
+}
+
+// A column's partition and tables by themselves.
+int launch_tables(Prof* prof, const TableLayout& L, const mj_rel& rel, int col, uint32_t bits,
+                  uint32_t bseed, uint32_t sseed, hipStream_t st) {
+    PartLaunch P{};
+    add_table(P, L, rel, col, bits, bseed);
+    int e = launch_partition(prof, "tab", P, st);
+    if (e) return e;
+    return launch_dbuild(prof, L, rel, bits, bseed, sseed, st);
 }
 
 struct RunBuf {
@@ -2068,11 +2084,9 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
     if (empty || a_domain == 0) return MJ_OK;
 
     const uint32_t nb = 1u << p.log2_nb;
-    // T: partition by g(C) and reduce each bucket to C -> multiplicity
-    st = launch_tables(&ctx->prof, L.T, *T, 0, p.log2_nc, seed_c(p), seed_slot(p), s);
-    if (st) return st;
     if (L.by_range) {
-        // S by bucket of B, R by range of A (one group of launches)
+        // S by bucket of B, R by range of A, T by bucket of C (one group of
+        // launches), then each of T's buckets reduced to C -> multiplicity
         PartLaunch P{};
         P.njobs = 2;
         // S by bucket of B -- and, for the S-largest form, by bucket of C
@@ -2087,17 +2101,24 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
         P.job[1].range_shift = L.a_shift;
         P.job[1].split = L.Rasplit;
         P.job[1].out_pair = L.Ra.pairs;
-        if ((st = launch_partition(&ctx->prof, "rs", P, s))) return st;
+        add_table(P, L.T, *T, 0, p.log2_nc, seed_c(p));
+        if (slarge) {
+            add_table(P, L.Rk, *R, 1, p.log2_nb, seed_b(p));
+            add_fill(P, L.wspecial, 2 * nb, 0);
+        } else {
+            // the pool of W[b]: slots [0, W_MIN_CAP) stay empty
+            add_fill(P, L.wpool, 4 * W_MIN_CAP, EMPTY_KEY);
+            add_fill_u64(P, L.wcursor, W_MIN_CAP);
+        }
+        if ((st = launch_partition(&ctx->prof, "rst", P, s))) return st;
+        if ((st = launch_dbuild(&ctx->prof, L.T, *T, p.log2_nc, seed_c(p), seed_slot(p), s))) return st;
         if (slarge) {
             // R's B values as tables per part of R (slots hashed as the W
             // tables are), a zero sum beside each slot; then every (R_i, T_j)
             // pair meets S_ij; then the tables become the W tables
-            st = launch_tables(&ctx->prof, L.Rk, *R, 1, p.log2_nb, seed_b(p), seed_w(p), s);
-            if (st) return st;
+            if ((st = launch_dbuild(&ctx->prof, L.Rk, *R, p.log2_nb, seed_b(p), seed_w(p), s))) return st;
             MJ_LAUNCHM(&ctx->prof, "k_fill_u64", k_fill_u64, dim3(grid_for(L.Rk.pool_slots, 256, 4096)), dim3(256), 0, s,
                       L.wval, (uint64_t)L.Rk.pool_slots, 0ull);
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u64", k_fill_u64, dim3(grid_for(nb, 256, 64)), dim3(256), 0, s,
-                      L.wspecial, (uint64_t)nb, 0ull);
             SlCellArgs Sc;
             Sc.S = L.S.pairs; Sc.sstarts = L.S.starts; Sc.r_bits = p.log2_nb; Sc.t_bits = p.log2_nc;
             Sc.pieces = sl_pieces(p);
@@ -2108,11 +2129,7 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
             MJ_LAUNCH(&ctx->prof, "k_sl_wtables", k_sl_wtables, dim3(nb), dim3(256), 0, s, L.Rk.dir, L.Rk.pool,
                       L.wval, L.wspecial, L.wdir, L.wpool);
         } else {
-            // W[b] per bucket of B into the pool (slots [0, W_MIN_CAP) stay empty)
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s,
-                      reinterpret_cast<uint32_t*>(L.wpool), (uint64_t)(4 * W_MIN_CAP), EMPTY_KEY);
-            MJ_LAUNCHM(&ctx->prof, "k_fill_u64", k_fill_u64, dim3(1), dim3(64), 0, s, L.wcursor, (uint64_t)1,
-                      (unsigned long long)W_MIN_CAP);
+            // W[b] per bucket of B into the pool
             WBuildArgs Wb{};
             Wb.S = L.S.pairs; Wb.sstarts = L.S.starts; Wb.ddir = L.T.dir; Wb.dpool = L.T.pool;
             Wb.c_seed = seed_c(p); Wb.c_bits = p.log2_nc; Wb.slot_seed = seed_slot(p); Wb.w_seed = seed_w(p);
@@ -2139,15 +2156,17 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
                   Cn.count, (uint64_t)a_domain, L.T.err);
         return MJ_OK;
     }
-    // R and S: partition by the bucket of B (one group of launches for both)
+    // R and S by the bucket of B, T by the bucket of C (one group of launches)
     PartLaunch P{};
     P.njobs = 2;
     P.job[0] = make_job(*R, L.R.hist, L.R.counts, L.R.starts, 1, seed_b(p), p.log2_nb, 0, 0, 0);
     P.job[0].out_pair = L.R.pairs;
     P.job[1] = make_job(*S, L.S.hist, L.S.counts, L.S.starts, 0, seed_b(p), p.log2_nb, 0, 0, 0);
     P.job[1].out_pair = L.S.pairs;
-    st = launch_partition(&ctx->prof, "rs", P, s);
+    add_table(P, L.T, *T, 0, p.log2_nc, seed_c(p));
+    st = launch_partition(&ctx->prof, "rst", P, s);
     if (st) return st;
+    if ((st = launch_dbuild(&ctx->prof, L.T, *T, p.log2_nc, seed_c(p), seed_slot(p), s))) return st;
     // cells: one workgroup per b-bucket
     LinearCellArgs C;
     C.R = L.R.pairs; C.rstarts = L.R.starts; C.S = L.S.pairs; C.sstarts = L.S.starts;
@@ -2239,29 +2258,12 @@ int mj_cascade2_count(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, c
     // join 2's build side: T partitioned by C, one multiplicity table per
     // bucket -- or, for dense keys, T by range of C and deg[c] directly
     const bool dense = L.deg != nullptr;
-    if (dense) {
-        MJ_LAUNCHM(prof, "k_fill_u32", k_fill_u32, dim3(1), dim3(64), 0, s, L.dflags, (uint64_t)3, 0u);
-        PartLaunch PT{};
-        PT.njobs = 1;
-        PT.job[0] = make_job(*T, L.Tr.hist, L.Tr.counts, L.Tr.starts, 0, 0, L.c_bits, 0, 0, 0);
-        PT.job[0].range_on = 1; PT.job[0].range_shift = L.c_shift;
-        PT.job[0].out_single = L.tkeys; PT.job[0].single_col = 0;
-        if ((st = launch_partition(prof, "tab", PT, s))) return st;
-        RangeAccArgs<uint32_t, uint16_t, uint32_t, uint16_t> Ad{};
-        Ad.pairs = nullptr; Ad.keys = L.tkeys; Ad.starts = L.Tr.starts; Ad.shift = L.c_shift;
-        Ad.domain = p.c_domain; Ad.table = nullptr; Ad.table_n = 0; Ad.out = L.deg; Ad.err = L.dflags;
-        Ad.out_narrow = L.deg16; Ad.wide = L.dflags + 2; Ad.table_narrow = nullptr; Ad.use_wide = nullptr;
-        MJ_LAUNCHM(prof, "k_range_deg", k_range_deg, dim3(1u << L.c_bits), dim3(RANGE_THREADS),
-                  size_t(4) << L.c_shift, s, Ad);
-    } else {
-        st = launch_tables(prof, L.T, *T, 0, p.log2_nc, seed_c(p), seed_slot(p), s);
-        if (st) return st;
-    }
     // join 1: R and S partitioned by B.  S is the build side (its C values
     // grouped by B) and R the probe side, so the pairs of I come R tuple by R
     // tuple and the second join can sum a run of one A value before its
     // atomic.  The partitions store S as (c, b) and R as (b, a), the layout
-    // the grouping kernel reads (value, key) and (key, value) in.
+    // the grouping kernel reads (value, key) and (key, value) in.  T's
+    // partition is one more job of the group.
     const uint32_t nb = 1u << p.log2_nb;
     PartLaunch P{};
     P.njobs = 2;
@@ -2271,8 +2273,26 @@ int mj_cascade2_count(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, c
     P.job[1] = make_job(*R, L.R.hist, L.R.counts, L.R.starts, 1, seed_b(p), p.log2_nb, 0, 0, 0);
     P.job[1].out_pair = L.R.pairs;
     P.job[1].swap_out = 1;
-    st = launch_partition(prof, "rs", P, s);
-    if (st) return st;
+    if (dense) {
+        add_fill(P, L.dflags, 3, 0);
+        PartJob& J = P.job[P.njobs++];
+        J = make_job(*T, L.Tr.hist, L.Tr.counts, L.Tr.starts, 0, 0, L.c_bits, 0, 0, 0);
+        J.range_on = 1; J.range_shift = L.c_shift;
+        J.out_single = L.tkeys; J.single_col = 0;
+    } else {
+        add_table(P, L.T, *T, 0, p.log2_nc, seed_c(p));
+    }
+    if ((st = launch_partition(prof, "rst", P, s))) return st;
+    if (dense) {
+        RangeAccArgs<uint32_t, uint16_t, uint32_t, uint16_t> Ad{};
+        Ad.pairs = nullptr; Ad.keys = L.tkeys; Ad.starts = L.Tr.starts; Ad.shift = L.c_shift;
+        Ad.domain = p.c_domain; Ad.table = nullptr; Ad.table_n = 0; Ad.out = L.deg; Ad.err = L.dflags;
+        Ad.out_narrow = L.deg16; Ad.wide = L.dflags + 2; Ad.table_narrow = nullptr; Ad.use_wide = nullptr;
+        MJ_LAUNCHM(prof, "k_range_deg", k_range_deg, dim3(1u << L.c_bits), dim3(RANGE_THREADS),
+                  size_t(4) << L.c_shift, s, Ad);
+    } else {
+        if ((st = launch_dbuild(prof, L.T, *T, p.log2_nc, seed_c(p), seed_slot(p), s))) return st;
+    }
     CasIndexArgs X;
     X.R = L.S.pairs; X.rstarts = L.S.starts; X.S = L.R.pairs; X.sstarts = L.R.starts;
     X.Rgrp = L.Rgrp; X.ecnt = L.ecnt; X.elist = L.elist; X.seed = seed_w(p);
@@ -2619,14 +2639,15 @@ static int record_batch(mj_ctx* ctx, const mj_batch_item* items, int n, char* ba
                                count, (uint64_t)it.a_domain, 0ull);
                 if (it.R.n == 0 || it.S.n == 0 || it.T.n == 0) return MJ_OK;
                 int e;
-                if ((e = launch_tables(prof, L.T, it.T, 0, p.log2_nc, seed_c(p), seed_slot(p), s))) return e;
                 PartLaunch P{};
                 P.njobs = 2;
                 P.job[0] = make_job(it.R, L.R.hist, L.R.counts, L.R.starts, 1, seed_b(p), p.log2_nb, 0, 0, 0);
                 P.job[0].out_pair = L.R.pairs;
                 P.job[1] = make_job(it.S, L.S.hist, L.S.counts, L.S.starts, 0, seed_b(p), p.log2_nb, 0, 0, 0);
                 P.job[1].out_pair = L.S.pairs;
-                if ((e = launch_partition(prof, "rs", P, s))) return e;
+                add_table(P, L.T, it.T, 0, p.log2_nc, seed_c(p));
+                if ((e = launch_partition(prof, "rst", P, s))) return e;
+                if ((e = launch_dbuild(prof, L.T, it.T, p.log2_nc, seed_c(p), seed_slot(p), s))) return e;
                 LinearCellArgs C;
                 C.R = L.R.pairs; C.rstarts = L.R.starts; C.S = L.S.pairs; C.sstarts = L.S.starts;
                 C.ddir = L.T.dir; C.dpool = L.T.pool;

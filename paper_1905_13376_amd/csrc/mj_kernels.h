@@ -85,8 +85,16 @@ struct PartJob {
     BucketItems split;   // optional work items of the buckets (k_part_scan)
 };
 
+// Words that k_part_scan sets for the kernels after the partition: a few
+// flags, cursors and empty slots (a launch each would take as long as one of
+// the partition's own).
+struct PartFill { uint32_t* p; uint32_t n, v; };
+constexpr int PART_MAX_FILLS = 12;
+
 struct PartLaunch {
     PartJob job[MJ_PART_MAX_JOBS];
+    PartFill fill[PART_MAX_FILLS] = {};
+    int nfill = 0;
     int njobs;
     uint32_t fold_rows = 0;      // k_part_scan sums the histogram's rows itself (no k_part_rowscan)
     uint32_t* clear = nullptr;   // words k_part_hist sets to 0 first (flags of the caller's kernels)

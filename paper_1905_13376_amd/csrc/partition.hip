@@ -214,6 +214,9 @@ __device__ void part_scan_job(const PartJob& J, bool fold, uint32_t* lds, uint32
 MJ_KERNEL(k_part_scan, PART_THREADS, PartLaunch) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t wave_tmp[PART_THREADS / WAVE + 1];
+    if (vg.bid == 0)
+        for (int f = 0; f < A.nfill; ++f)
+            for (uint32_t w = threadIdx.x; w < A.fill[f].n; w += blockDim.x) A.fill[f].p[w] = A.fill[f].v;
     part_scan_job(A.job[vg.bid], A.fold_rows != 0, lds, wave_tmp);
 }
 
