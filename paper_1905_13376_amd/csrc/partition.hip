@@ -67,36 +67,44 @@ __device__ __forceinline__ int find_job(const PartLaunch& L, uint32_t blk) {
 
 // Load the tile's tuples into registers: item k of thread t is tuple
 // beg + t*2 + (k&1) + (k>>1)*2*blockDim for packed inputs (two tuples per
-// 16-byte load), beg + t + k*blockDim otherwise.
+// 16-byte load), beg + t + k*blockDim otherwise.  No load depends on a bound
+// (past the tile's end the last tuple is read again), so a thread's loads are
+// all in flight together; under a condition each they were waited for one by
+// one.
 template <int ITEMS>
 __device__ __forceinline__ void load_tile(const PartJob& J, uint64_t beg, uint32_t cnt,
                                           uint32_t (&x0)[ITEMS], uint32_t (&x1)[ITEMS],
                                           uint32_t (&idx)[ITEMS]) {
     const uint32_t t = threadIdx.x, B = blockDim.x;
     if (J.packed) {
-        const u32x4* src = reinterpret_cast<const u32x4*>(J.col0 + 2 * beg);
+        const uint32_t* col = J.col0 + 2 * beg;
 #pragma unroll
         for (int k = 0; k < ITEMS; k += 2) {
-            const uint32_t i = 2 * t + (k >> 1) * 2 * B;   // first of two tuples
-            idx[k] = i;
-            idx[k + 1] = i + 1;
-            if (i + 1 < cnt) {
-                u32x4 v = __builtin_nontemporal_load(src + (i >> 1));
+            idx[k] = 2 * t + (k >> 1) * 2 * B;             // first of two tuples
+            idx[k + 1] = idx[k] + 1;
+        }
+        if (cnt == ITEMS * B) {
+#pragma unroll
+            for (int k = 0; k < ITEMS; k += 2) {
+                const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(col) + (idx[k] >> 1));
                 x0[k] = v.x; x1[k] = v.y; x0[k + 1] = v.z; x1[k + 1] = v.w;
-            } else if (i < cnt) {
-                x0[k] = J.col0[2 * (beg + i)];
-                x1[k] = J.col0[2 * (beg + i) + 1];
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                const u32x2 v = reinterpret_cast<const u32x2*>(col)[min(idx[k], cnt - 1)];
+                x0[k] = v.x; x1[k] = v.y;
             }
         }
     } else {
+        const uint32_t *c0 = J.col0, *c1 = J.col1;
+        const int64_t stride = J.stride;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const uint32_t i = t + k * B;
-            idx[k] = i;
-            if (i < cnt) {
-                x0[k] = ld_col(J.col0, beg + i, J.stride);
-                x1[k] = ld_col(J.col1, beg + i, J.stride);
-            }
+            idx[k] = t + k * B;
+            const uint64_t i = beg + min(idx[k], cnt - 1);
+            x0[k] = ld_col(c0, i, stride);
+            x1[k] = ld_col(c1, i, stride);
         }
     }
 }
