@@ -867,6 +867,40 @@ k_count(CountArgs A) {
 // its weights in LDS and writes the range once; the weight of a tuple is one
 // read of the previous array.
 // SAT_IN: table_narrow is a saturating copy; SAT_OUT: out_narrow is one.
+// The weights of four tuples: w[u] = table[v[u]], 0 for a v at or past table_n
+// or a tuple that is not live.  The four reads have no condition (entry 0
+// stands in), so they are in flight together; what a saturated copy leaves
+// open is read afterwards.
+template <bool SAT_IN, class TW, class TWN, class TO, class TON>
+__device__ __forceinline__ void range_weights(const RangeAccArgs<TW, TWN, TO, TON>& A, bool narrow,
+                                              const uint32_t (&v)[4], const bool (&live)[4], TO (&w)[4]) {
+    uint32_t at[4];
+    bool in[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { in[u] = live[u] && v[u] < A.table_n; at[u] = in[u] ? v[u] : 0u; }
+    if (SAT_IN || narrow) {
+        const TWN* t = A.table_narrow;
+        TWN x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = t[at[u]];
+        bool open = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { w[u] = in[u] ? (TO)x[u] : (TO)0; open = open || (in[u] && x[u] == TWN(~TWN(0))); }
+        if (SAT_IN && open) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (in[u] && x[u] == TWN(~TWN(0))) w[u] = (TO)A.table[at[u]];
+        }
+    } else {
+        const TW* t = A.table;
+        TW x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = t[at[u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = in[u] ? (TO)x[u] : (TO)0;
+    }
+}
+
 template <bool SAT_IN, bool SAT_OUT, class TW, class TWN, class TO, class TON>
 __device__ __forceinline__ void range_accumulate(const RangeAccArgs<TW, TWN, TO, TON>& A, TO* acc, VGrid vg) {
     uint32_t k = vg.bid, piece = 0;
@@ -892,28 +926,23 @@ __device__ __forceinline__ void range_accumulate(const RangeAccArgs<TW, TWN, TO,
     if (A.packed) {
         // four consecutive tuples per thread and load (16 bytes, aligned)
         const uint32_t vmask = (1u << A.pack_bits) - 1u;
-        for (uint32_t qb = q0 & ~3u; qb < q1; qb += 4 * nthr) {     // every lane runs every round
+        const uint32_t qa = q0 & ~3u, ql = q1 ? (q1 - 1) & ~3u : 0u;    // first and last group of four
+        u32x4 next = {0u, 0u, 0u, 0u};
+        if (qa < q1) next = *reinterpret_cast<const u32x4*>(A.packed + min(qa + 4 * threadIdx.x, ql));
+        for (uint32_t qb = qa; qb < q1; qb += 4 * nthr) {           // every lane runs every round
             const uint32_t q = qb + 4 * threadIdx.x;
-            u32x4 p = {0u, 0u, 0u, 0u};
-            if (q < q1) p = *reinterpret_cast<const u32x4*>(A.packed + q);
+            const u32x4 p = next;
+            next = *reinterpret_cast<const u32x4*>(A.packed + min(q + 4 * nthr, ql));
             TO w[4];
+            uint32_t v[4];
             bool live[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 live[u] = q + u >= q0 && q + u < q1;
-                const uint32_t v = p[u] & vmask;
-                if (A.table) {
-                    const bool in = live[u] && v < A.table_n;
-                    if constexpr (SAT_IN) {
-                        const TWN x = in ? A.table_narrow[v] : TWN(0);
-                        w[u] = x == TWN(~TWN(0)) ? (TO)A.table[v] : (TO)x;
-                    } else {
-                        w[u] = !in ? (TO)0 : (narrow ? (TO)A.table_narrow[v] : (TO)A.table[v]);
-                    }
-                } else {
-                    w[u] = 1;
-                }
+                v[u] = p[u] & vmask;
+                w[u] = 1;
             }
+            if (A.table) range_weights<SAT_IN>(A, narrow, v, live, w);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 TO v = w[u];
@@ -926,33 +955,23 @@ __device__ __forceinline__ void range_accumulate(const RangeAccArgs<TW, TWN, TO,
     } else
     for (uint32_t qb = q0; qb < q1; qb += 4 * nthr) {               // every lane runs every round
         const uint32_t q = qb + threadIdx.x;
-        uint32_t key[4];
+        uint32_t key[4], v[4];
         TO w[4];
         bool live[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t idx = q + u * nthr;
-            live[u] = idx < q1;
-            uint32_t v = 0;
-            if (A.pairs) {
-                const uint2 pv = live[u] ? A.pairs[idx] : make_uint2(0u, 0u);
+        for (int u = 0; u < 4; ++u) { live[u] = q + u * nthr < q1; w[u] = 1; }
+        if (A.pairs) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint2 pv = A.pairs[min(q + u * nthr, q1 - 1)];
                 key[u] = pv.x;
-                v = pv.y;
-            } else {
-                key[u] = live[u] ? A.keys[idx] : 0u;
+                v[u] = pv.y;
             }
-            if (A.table) {                                           // the reads in flight together
-                const bool in = live[u] && v < A.table_n;
-                if constexpr (SAT_IN) {
-                    const TWN x = in ? A.table_narrow[v] : TWN(0);
-                    w[u] = x == TWN(~TWN(0)) ? (TO)A.table[v] : (TO)x;
-                } else {
-                    w[u] = !in ? (TO)0 : (narrow ? (TO)A.table_narrow[v] : (TO)A.table[v]);
-                }
-            } else {
-                w[u] = 1;
-            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { key[u] = A.keys[min(q + u * nthr, q1 - 1)]; v[u] = 0; }
         }
+        if (A.table) range_weights<SAT_IN>(A, narrow, v, live, w);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             TO v = w[u];
@@ -1123,9 +1142,14 @@ k_sl_cell(SlCellArgs A) {
         for (int u = 0; u < 4; ++u) {
             const uint32_t idx = q + u * nthr;
             live[u] = idx < q1;
-            sv[u] = live[u] ? A.S[idx] : make_uint2(0u, 0u);
-            sl[u] = slot_hash(sv[u].y, A.slot_seed) & tmask;
-            kv[u] = live[u] && sv[u].y != EMPTY_KEY ? tab[sl[u]] : make_uint2(EMPTY_KEY, 0u);
+            sv[u] = A.S[min(idx, q1 - 1)];                 // (no condition: the four in flight together)
+        }
+        if (tl) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { sl[u] = slot_hash(sv[u].y, A.slot_seed) & tmask; kv[u] = ttab[sl[u]]; }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { sl[u] = slot_hash(sv[u].y, A.slot_seed) & tmask; kv[u] = tg[sl[u]]; }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
