@@ -1126,7 +1126,7 @@ int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
                   dim3(EXP_THREADS), 0, s, E);
         CasProbeTriArgs Q;
         Q.I = L.I; Q.n = hi - lo; Q.T = run_index(L.Trun); Q.Tk = L.Tk; Q.seed = p.seed; Q.total = total;
-        MJ_LAUNCHM(prof, "k_cas_probe_tri", k_cas_probe_tri, dim3(grid_for(hi - lo, 256, 2048)), dim3(256), 0, s, Q);
+        MJ_LAUNCHM(prof, "k_cas_probe_tri", k_cas_probe_tri, dim3(grid_for((hi - lo + 3) / 4, 256, 2048)), dim3(256), 0, s, Q);
     }
     // an intermediate of another size than the plan's: the total is all ones
     MJ_LAUNCHM(prof, "k_poison_u64", k_poison_u64, dim3(1), dim3(64), 0, s, total, (uint64_t)1, L.err);

@@ -339,16 +339,6 @@ __device__ __forceinline__ uint32_t listtab_count4(const ListTab& T, const uint3
     return acc;
 }
 
-// number of entries of sorted low words keys[lo, hi) equal to a
-__device__ __forceinline__ uint32_t count_low(const unsigned long long* keys, uint32_t lo,
-                                              uint32_t hi, uint32_t a) {
-    uint32_t l = lo, h = hi;
-    while (l < h) { uint32_t m = (l + h) >> 1; if ((uint32_t)keys[m] < a) l = m + 1; else h = m; }
-    uint32_t l2 = l, h2 = hi;
-    while (l2 < h2) { uint32_t m = (l2 + h2) >> 1; if ((uint32_t)keys[m] <= a) l2 = m + 1; else h2 = m; }
-    return l2 - l;
-}
-
 // ------------------------------------------------------- streaming lists
 // One chunk of up to 64 S tuples of a group, lane j holding tuple si (when
 // `valid`): each tuple's iterated list streams past the staged one.  When the
@@ -731,14 +721,53 @@ __global__ void __launch_bounds__(WAVE) k_tri_batch_prefix(TriBatchArgs Bt) {
 // ----------------------------------------------- cascade, cyclic second join
 // For every (a, c) of I = R |x| S: the multiplicity of (c, a) in T, found in
 // T's sorted list of m(c) by binary search on m(a).
+// A pair's lookup is a chain of dependent random reads (directory, run, its
+// start, the searches for the first and last equal entry): four pairs a
+// thread walk theirs together, both searches of a pair at once (the
+// cascades in a batch of 64 joins: 467 -> 392 us).
 MJ_KERNEL(k_cas_probe_tri, 256, CasProbeTriArgs) {
     unsigned long long acc = 0;
-    for (uint64_t q = vg.bid * (uint64_t)blockDim.x + threadIdx.x; q < A.n;
-         q += (uint64_t)vg.nblk * blockDim.x) {
-        const uint2 iv = A.I[q];
-        uint32_t ts, y;
-        if (!run_lookup(A.T, mix32(iv.y, A.seed), ts, y)) continue;
-        acc += count_low(A.Tk, ts, ts + y, mix32(iv.x, A.seed));
+    const uint64_t step = 4 * uint64_t(blockDim.x);
+    for (uint64_t q = vg.bid * step + threadIdx.x; q < A.n; q += vg.nblk * step) {
+        uint32_t key[4], a[4], r[4], l[4], h[4], l2[4], h2[4];
+        bool live[4];
+        uint2 iv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) iv[u] = A.I[min<uint64_t>(q + uint64_t(u) * blockDim.x, A.n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            live[u] = q + uint64_t(u) * blockDim.x < A.n;
+            key[u] = mix32(iv[u].y, A.seed);
+            a[u] = mix32(iv[u].x, A.seed);
+        }
+        run_find4(A.T, key, live, r);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {                     // run 0 stands in for a missing one
+            const bool found = r[u] != 0xFFFFFFFFu;
+            const uint32_t i = found ? r[u] : 0u;
+            l[u] = l2[u] = A.T.run_start[i];
+            const uint32_t e = A.T.run_start[i + 1];
+            h[u] = h2[u] = found ? e : l[u];
+        }
+        bool any = true;
+        while (any) {
+            uint32_t k[4], k2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (l[u] < h[u]) k[u] = (uint32_t)A.Tk[(l[u] + h[u]) >> 1];
+                if (l2[u] < h2[u]) k2[u] = (uint32_t)A.Tk[(l2[u] + h2[u]) >> 1];
+            }
+            any = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t m = (l[u] + h[u]) >> 1, m2 = (l2[u] + h2[u]) >> 1;
+                if (l[u] < h[u]) { if (k[u] < a[u]) l[u] = m + 1; else h[u] = m; }
+                if (l2[u] < h2[u]) { if (k2[u] <= a[u]) l2[u] = m2 + 1; else h2[u] = m2; }
+                any = any || l[u] < h[u] || l2[u] < h2[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += l2[u] - l[u];
     }
     block_add_u64(A.total, acc);
 }
