@@ -319,7 +319,8 @@ void take_table(Bump& B, TableLayout& L, uint64_t n, uint32_t bits, bool narrow 
     const uint64_t nrows = split_rows(n, bits);
     L.rows = B.take<uint2>(nrows * DB_CAP);
     L.row_special = B.take<uint32_t>(nrows);
-    L.row_n = B.take<uint32_t>(nrows);
+    // (the partition's histogram is read for the last time before the tables are built)
+    L.row_n = nrows <= uint64_t(nb) * ntiles_of(n) ? L.hist : B.take<uint32_t>(nrows);
     L.npool = narrow ? B.take<uint32_t>(L.pool_slots) : nullptr;
     L.ndir = narrow ? B.take<uint32_t>(nb) : nullptr;
 }
@@ -346,11 +347,12 @@ void take_part(Bump& B, RelPart& P, uint64_t n, uint32_t bits) {
 // 2^ACELL_MAX_SHIFT values; false when the domain needs more.  In a batch the
 // other joins fill the chip, and workgroups of 2K tuples cost more to start
 // than they save: at least 8K there.
-bool key_ranges(uint64_t n, uint32_t domain, uint32_t& bits, uint32_t& shift, bool in_batch = false) {
+bool key_ranges(uint64_t n, uint32_t domain, uint32_t& bits, uint32_t& shift, bool in_batch = false,
+                bool compact = false) {
     if (domain == 0) return false;
     const uint32_t L = ceil_log2(domain);
     const uint64_t least = in_batch ? 8192 : 1024;
-    const uint32_t fill = std::min<uint32_t>(9, n >= 2 * least ? ceil_log2(n / least + 1) - 1 : 0);
+    const uint32_t fill = compact ? 0u : std::min<uint32_t>(9, n >= 2 * least ? ceil_log2(n / least + 1) - 1 : 0);
     bits = std::min<uint32_t>({std::max(fill, ceil_log2((n + 32767) / 32768)), PART_MAX_BITS, L});
     if (L - bits > ACELL_MAX_SHIFT) bits = L - ACELL_MAX_SHIFT;
     shift = L - bits;
@@ -359,8 +361,8 @@ bool key_ranges(uint64_t n, uint32_t domain, uint32_t& bits, uint32_t& shift, bo
 
 // Ranges of A for the per-A counts.  False when a_domain needs more than
 // there can be (the cells then add into the output with atomics).
-bool a_ranges(const mj_plan_t& p, uint32_t& bits, uint32_t& shift) {
-    return key_ranges(p.n_r, p.a_domain, bits, shift);
+bool a_ranges(const mj_plan_t& p, uint32_t& bits, uint32_t& shift, bool compact = false) {
+    return key_ranges(p.n_r, p.a_domain, bits, shift, false, compact);
 }
 
 // Range pairs in 4 bytes: the key's place in its range beside the other value
@@ -406,17 +408,22 @@ DenseLayout dense_layout(void* ws, const mj_plan_t& p) {
     key_ranges(p.n_t, p.c_domain, L.c_bits, L.c_shift, in_batch);
     key_ranges(p.n_s, p.b_domain, L.b_bits, L.b_shift, in_batch);
     key_ranges(p.n_r, p.a_domain, L.a_bits, L.a_shift, in_batch);
-    auto part = [&](RelPart& P, uint64_t n, uint32_t bits, bool pairs) {
+    // 8 bytes a pair, or 4 where the pairs are packed whichever partitions are
+    // shared (then read four at a time)
+    auto part = [&](RelPart& P, uint64_t n, uint32_t bits, uint64_t pair_bytes) {
         const uint32_t nb = 1u << bits;
         P.hist = B.take<uint32_t>(uint64_t(nb) * ntiles_of(n));
         P.counts = B.take<uint32_t>(nb);
         P.starts = B.take<uint32_t>(nb + 1);
-        P.pairs = pairs ? B.take<uint2>(std::max<uint64_t>(n, 4)) : nullptr;   // (packed: read four at a time)
+        P.pairs = pair_bytes ? B.take<uint2>((((n + 3) & ~uint64_t(3)) + 4) * pair_bytes / 8) : nullptr;
     };
-    part(L.T, p.n_t, L.c_bits, false);
+    uint32_t x;
+    const bool s_packed = pack_pairs(L.b_shift, std::max(p.b_domain, p.c_domain), x);
+    const bool r_packed = pack_pairs(L.a_shift, p.b_domain, x);
+    part(L.T, p.n_t, L.c_bits, 0);
     L.tkeys = B.take<uint32_t>(std::max<uint64_t>(p.n_t, 1));
-    part(L.S, p.n_s, L.b_bits, true);
-    part(L.R, p.n_r, L.a_bits, true);
+    part(L.S, p.n_s, L.b_bits, s_packed ? 4 : 8);
+    part(L.R, p.n_r, L.a_bits, r_packed ? 4 : 8);
     L.Tsplit = take_items(B, p.n_t, L.c_bits);
     L.Ssplit = take_items(B, p.n_s, L.b_bits);
     L.Rsplit = take_items(B, p.n_r, L.a_bits);
@@ -472,13 +479,17 @@ uint32_t sl_pieces(const mj_plan_t& p) {
     return (uint32_t)std::min<uint64_t>(k, 64);
 }
 
-LinearLayout linear_layout(void* ws, const mj_plan_t& p) {
+// `compact`: without the tables' narrow forms and with few ranges of A, for a
+// workspace that has no room for them (one sized for an earlier plan)
+LinearLayout linear_layout(void* ws, const mj_plan_t& p, bool compact = false) {
+    const uint32_t count_pct = compact ? MJ_SPLIT_PCT : COUNT_SPLIT_PCT;
+    const bool narrow = !compact && nt_bits_ok(p.log2_nb);
     Bump B(ws);
     LinearLayout L;
     take_part(B, L.R, p.n_r, p.log2_nb);
     take_part(B, L.S, p.n_s, s_part_bits(p));
-    take_table(B, L.T, p.n_t, p.log2_nc, p.algo != MJ_ALGO_SLARGE);
-    L.by_range = a_ranges(p, L.a_bits, L.a_shift);
+    take_table(B, L.T, p.n_t, p.log2_nc, p.algo != MJ_ALGO_SLARGE && !compact);
+    L.by_range = a_ranges(p, L.a_bits, L.a_shift, compact);
     L.wdir = nullptr; L.wpool = nullptr; L.npool = nullptr; L.ndir = nullptr; L.wcursor = nullptr; L.wslots = 0;
     L.Rasplit = BucketItems{}; L.rows = nullptr;
     L.Ssplit = BucketItems{}; L.wrows = nullptr; L.wrow_special = nullptr; L.wrow_n = nullptr;
@@ -488,8 +499,8 @@ LinearLayout linear_layout(void* ws, const mj_plan_t& p) {
         L.Ra.hist = B.take<uint32_t>(uint64_t(na) * ntiles_of(p.n_r));
         L.Ra.counts = B.take<uint32_t>(na);
         L.Ra.starts = B.take<uint32_t>(na + 1);
-        L.Rasplit = take_items(B, p.n_r, L.a_bits, COUNT_SPLIT_PCT);
-        L.rows = B.take<unsigned long long>(split_rows(p.n_r, L.a_bits, COUNT_SPLIT_PCT) << L.a_shift);
+        L.Rasplit = take_items(B, p.n_r, L.a_bits, count_pct);
+        L.rows = B.take<unsigned long long>(split_rows(p.n_r, L.a_bits, count_pct) << L.a_shift);
         const uint32_t nb = 1u << p.log2_nb;
         L.wdir = B.take<WDirEntry>(nb);
         if (p.algo == MJ_ALGO_SLARGE) {
@@ -502,13 +513,13 @@ LinearLayout linear_layout(void* ws, const mj_plan_t& p) {
             // a bucket's table holds at most 4 slots per S tuple (a power of
             // two >= twice its keys), plus the minimum per bucket and the
             // empty head
-            L.wslots = 4 * p.n_s + uint64_t(W_MIN_CAP) * (nb + 1) + (nt_bits_ok(p.log2_nb) ? NT_MIN_SLOTS : 0u);
+            L.wslots = 4 * p.n_s + uint64_t(W_MIN_CAP) * (nb + 1) + (narrow ? NT_MIN_SLOTS : 0u);
             L.Ssplit = take_items(B, p.n_s, p.log2_nb);
             const uint64_t nrows = split_rows(p.n_s, p.log2_nb);
             L.wrows = B.take<WSlot>(nrows * CELL_CAP);
             L.wrow_special = B.take<unsigned long long>(nrows);
-            L.wrow_n = B.take<uint32_t>(nrows);
-            if (nt_bits_ok(p.log2_nb)) {
+            L.wrow_n = nrows <= uint64_t(nb) * ntiles_of(p.n_s) ? L.S.hist : B.take<uint32_t>(nrows);
+            if (narrow) {
                 L.npool = B.take<uint32_t>(L.wslots);
                 L.ndir = B.take<uint32_t>(nb);
             }
@@ -544,7 +555,7 @@ struct CascadeLayout {
 
 constexpr uint64_t CAS_DEFAULT_I_CAP = uint64_t(1) << 28;   // 2 GiB of (a, c) pairs
 
-CascadeLayout cascade_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
+CascadeLayout cascade_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes, bool compact = false) {
     Bump B(ws);
     CascadeLayout L;
     take_part(B, L.R, p.n_r, p.log2_nb);
@@ -552,7 +563,7 @@ CascadeLayout cascade_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
     L.Tr = RelPart{}; L.tkeys = nullptr; L.deg = nullptr; L.deg16 = nullptr; L.dflags = nullptr;
     L.c_bits = L.c_shift = 0;
     if (dense_plan(p)) {
-        key_ranges(p.n_t, p.c_domain, L.c_bits, L.c_shift);
+        key_ranges(p.n_t, p.c_domain, L.c_bits, L.c_shift, false, compact);
         const uint32_t nb = 1u << L.c_bits;
         L.Tr.hist = B.take<uint32_t>(uint64_t(nb) * ntiles_of(p.n_t));
         L.Tr.counts = B.take<uint32_t>(nb);
@@ -562,7 +573,7 @@ CascadeLayout cascade_layout(void* ws, const mj_plan_t& p, uint64_t ws_bytes) {
         L.deg16 = B.take<uint16_t>(std::max<uint32_t>(p.c_domain, 1));
         L.dflags = B.take<uint32_t>(3);
     } else {
-        take_table(B, L.T, p.n_t, p.log2_nc, true);
+        take_table(B, L.T, p.n_t, p.log2_nc, !compact);
     }
     // join 1 groups S's C values by B and probes with R's tuples
     L.Rgrp = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
@@ -756,12 +767,12 @@ TriLayout tri_layout(void* ws, const mj_plan_t& p) {
     L.Sk = B.take<unsigned long long>(std::max<uint64_t>(p.n_s, 1));
     L.Sk2 = B.take<unsigned long long>(std::max<uint64_t>(p.n_s, 1));
     L.Tk = B.take<unsigned long long>(std::max<uint64_t>(p.n_t, 1));
-    L.Rl = B.take<uint32_t>(std::max<uint64_t>(p.n_r, 1));
-    L.Sl = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
-    L.Sl2 = B.take<uint32_t>(std::max<uint64_t>(p.n_s, 1));
-    L.Tl = B.take<uint32_t>(std::max<uint64_t>(p.n_t, 1));
     L.tmp[0] = B.take<unsigned long long>(nmax);
     L.tmp[1] = B.take<unsigned long long>(nmax);
+    // the low words are written after the sorts, two arrays to a sort buffer
+    uint32_t *l0 = reinterpret_cast<uint32_t*>(L.tmp[0]), *l1 = reinterpret_cast<uint32_t*>(L.tmp[1]);
+    L.Rl = l0; L.Sl = l0 ? l0 + nmax : nullptr;          // (null while only sizing)
+    L.Sl2 = l1; L.Tl = l1 ? l1 + nmax : nullptr;
     for (int i = 0; i < 4; ++i) L.rs_hist[i] = B.take<uint32_t>(256 * rs_tiles(nmax));
     L.rs_counts = B.take<uint32_t>(4 * 256);
     take_runs(B, L.R, p.n_r, true);
@@ -2071,9 +2082,10 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
         if (std::max({R->n, S->n, T->n}) <= SMALL_MAX) return run_small(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
         return run_dense(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
     }
-    LinearLayout L = linear_layout(nullptr, p);
+    const bool compact = ws_bytes < linear_layout(nullptr, p).bytes;
+    LinearLayout L = linear_layout(nullptr, p, compact);
     if (ws_bytes < L.bytes || (!ws && L.bytes)) return MJ_ERR_WORKSPACE;
-    L = linear_layout(ws, p);
+    L = linear_layout(ws, p, compact);
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     const bool empty = R->n == 0 || S->n == 0 || T->n == 0;
@@ -2245,6 +2257,8 @@ int mj_cascade2_count(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, c
         return run_star_cascade(ctx, R, S, T, a_domain, out, p, ws, ws_bytes, static_cast<hipStream_t>(stream));
     if (!ws) return MJ_ERR_WORKSPACE;
     CascadeLayout L = cascade_layout(ws, p, ws_bytes);
+    if (L.i_cap < std::min<uint64_t>(p.join2_size, CAS_DEFAULT_I_CAP))      // I before the narrow tables
+        L = cascade_layout(ws, p, ws_bytes, true);
     if (ws_bytes < L.base_bytes || (p.join2_size && L.i_cap == 0)) return MJ_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     Prof* prof = &ctx->prof;
