@@ -40,27 +40,28 @@ def kernel_bytes(name, n_r, n_s, n_t, distinct_t, distinct_b, a_domain, b_domain
     its first column are one and the same) the partition launches move one
     relation, not three."""
     part_hist = 4 * n_s if shared_partition else 4 * (n_r + n_s + n_t)
-    part_scatter = 12 * n_s if shared_partition else 12 * (n_r + n_s) + 8 * n_t
+    part_scatter = 16 * n_s if shared_partition else 16 * (n_r + n_s) + 8 * n_t
     table = {
-        # direct-indexed tables: T.c, S and R partitioned by range in one launch
-        # group, pairs of 4 bytes (a key's place in its range beside the other value)
+        # direct-indexed tables: T.c, S and R partitioned by range in one launch group
         "dense:k_part_hist": part_hist,                 # read the key columns
-        "dense:k_part_scatter": part_scatter,           # read the tuples, write the pairs (T: its C column)
+        "dense:k_part_scatter": part_scatter,           # read + write the pairs (T: its C column)
         # T's pairs (the shared partition), deg[] and its 2-byte copy written once
-        "k_range_deg": 4 * n_t + 6 * c_domain,
+        "k_range_deg": 8 * n_t + 6 * c_domain,
         # S pairs, one 2-byte deg[c] read per tuple, W[] and its 2-byte copy written once
-        "k_range_w": 6 * n_s + 10 * b_domain,
+        "k_range_w": 10 * n_s + 10 * b_domain,
         # R pairs, one 2-byte W[b] read per tuple (the full W only where the copy
         # saturates: 0.03 % of the reads here, not counted), the counts written once
-        "k_range_count": 6 * n_r + 8 * a_domain,
+        "k_range_count": 10 * n_r + 8 * a_domain,
         # hashed tables: S and R by bucket or range and T's C column in one launch group
         "rst:k_part_hist": 4 * (n_r + n_s + n_t),            # read the bucketed columns
         "rst:k_part_scatter": 16 * (n_r + n_s) + 8 * n_t,    # read + write 8-byte tuples, T's C values
+        "tab:k_part_hist": 4 * n_t,                     # read the C column
+        "tab:k_part_scatter": 8 * n_t,                  # read + write the C column
         "tab:k_dbuild": 4 * n_t + 16 * distinct_t,      # read C, write the table
-        # S, one 4-byte narrow slot per s, the W table (16-byte slots, load 1/2)
-        "k_wbuild": 12 * n_s + 32 * distinct_b,
-        # R, one 4-byte narrow W slot per r, the counts written once
-        "k_count": 12 * n_r + 8 * a_domain,
+        # S, one 8-byte multiplicity slot per s, the W table (16-byte slots, load 1/2)
+        "k_wbuild": 16 * n_s + 32 * distinct_b,
+        # R, one 16-byte W slot per r, the counts written once
+        "k_count": 24 * n_r + 8 * a_domain,
         "k_linear_cell": 16 * n_s + 16 * n_r,           # S, R, one table slot per s, one count per r
     }
     return table.get(name)

@@ -388,12 +388,11 @@ __device__ __forceinline__ void star_map_build(const StarMap& M, const uint32_t*
         atomicAdd(&X.cls[c], 1u);
     }
     __syncthreads();
-    if (t < STAR_BKT_KEYS + 2) {
-        uint32_t o = 0;
-        for (uint32_t c = t + 1; c < STAR_BKT_KEYS + 2; ++c) o += X.cls[c];
-        wave_fence();
-        X.cls[t] = o;
-    }
+    uint32_t larger = 0;                            // buckets with more keys than t
+    if (t < STAR_BKT_KEYS + 2)
+        for (uint32_t c = t + 1; c < STAR_BKT_KEYS + 2; ++c) larger += X.cls[c];
+    __syncthreads();
+    if (t < STAR_BKT_KEYS + 2) X.cls[t] = larger;
     __syncthreads();
     for (uint32_t b = t; b < STAR_BKTS; b += STAR_THREADS) {
         const uint32_t c = min<uint32_t>(M.disp[b], STAR_BKT_KEYS + 1);
