@@ -357,6 +357,9 @@ def star_path(mj, ctx):
     from workloads import generators as G
     sys.path.insert(0, os.path.join(ROOT, "tests"))
     import brute
+    # this sequence ended with an illegal access on the GPU and the cause is
+    # not shown; the star plans themselves are tested at this size
+    raise RuntimeError("the star leg is switched off: a GPU fault in it is not explained yet")
     log("generating the star schema (2^26 fact tuples, 4096-tuple dimensions)")
     R, S, T = G.star_schema()
     a_dom = G.STAR["a_domain"]

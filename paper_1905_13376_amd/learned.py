@@ -385,6 +385,9 @@ def main():
         print(f"[learned] {m}", file=sys.stderr, flush=True)
     ctx = L.Context()
     if args.cmd == "label":
+        # thousands of instances, every plan of each: such a run ended with an
+        # illegal access on the GPU, and the cause is not shown
+        raise RuntimeError("labelling is switched off: a GPU fault in it is not explained yet")
         label(ctx, args.count, args.seed, args.lo, args.hi, args.out, log)
         return
     D = load_rows(args.train)
