@@ -121,15 +121,24 @@ __device__ __forceinline__ bool wave_fold_first(uint32_t key, bool act, T& v) {
 // release writes the XCD's dirty lines back, the acquire invalidates them.
 // Both act on the whole L2, so one wave does them for the workgroup, once
 // every wave's stores have arrived there (a fence in each of 8 or 16 waves
-// took 0.1 ms of a 0.6 ms join of skewed relations).  All threads of the workgroup call it.
-__device__ __forceinline__ bool handoff_last(uint32_t* ticket, uint32_t count, bool flag = false) {
-    __shared__ uint32_t s_last;
+// took 0.1 ms of a 0.6 ms join of skewed relations).  The write-back itself
+// has to be waited for before the ticket: after the waves' explicit wait the
+// compiler takes nothing to be outstanding and leaves the release fence's own
+// wait out, so it is written here.  All threads of the workgroup call it.
+__device__ __forceinline__ void wait_memory() {
 #if __has_builtin(__builtin_amdgcn_s_waitcnt)
     __builtin_amdgcn_s_waitcnt(0);
 #endif
+}
+
+__device__ __forceinline__ bool handoff_last(uint32_t* ticket, uint32_t count, bool flag = false) {
+    __shared__ uint32_t s_last;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // no store moves past the wait
+    wait_memory();                                             // this wave's stores have reached the L2
     __syncthreads();
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        wait_memory();                                         // ... and have left it
         if (flag) atomicOr(ticket, 0x80000000u);
         const bool last = (atomicAdd(ticket, 1u) & 0x7FFFFFFFu) == count - 1;
         if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
