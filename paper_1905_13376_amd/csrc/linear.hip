@@ -152,7 +152,8 @@ __device__ __forceinline__ void row_compact(const uint32_t* keys, uint32_t cap, 
 
 // The entries of `pcs` compacted rows, eight rows' reads in flight per thread
 // (one slot at a time, each waits for another XCD's lines: adding up a hub's
-// nine rows took 0.1 ms).  Stops once *over is set.
+// nine rows took 0.1 ms).  A count is a word of memory and bounds the reads,
+// so it is held to the row's length.  Stops once *over is set.
 template <class E, class F>
 __device__ __forceinline__ void rows_for_each(const E* rows, const uint32_t* row_n, uint32_t row_cap, uint32_t pcs,
                                               const uint32_t* over, F&& add) {
@@ -160,7 +161,7 @@ __device__ __forceinline__ void rows_for_each(const E* rows, const uint32_t* row
     for (uint32_t r0 = 0; r0 < pcs; r0 += ROWS) {
         uint32_t n[ROWS], most = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < ROWS; ++u) n[u] = r0 + u < pcs ? row_n[r0 + u] : 0u;
+        for (uint32_t u = 0; u < ROWS; ++u) n[u] = r0 + u < pcs ? min(row_n[r0 + u], row_cap) : 0u;
 #pragma unroll
         for (uint32_t u = 0; u < ROWS; ++u) most = max(most, n[u]);
         for (uint32_t i = threadIdx.x; i < most; i += blockDim.x) {
