@@ -715,7 +715,7 @@ uint64_t rs_tiles(uint64_t n) { return (std::max<uint64_t>(n, 1) + RS_TILE - 1) 
 
 struct PassBuf {                      // work queues of one pass of the cyclic join
     uint2* light;
-    uint32_t* ctr;                    // [TRI_CTR_WORDS] nlight, heavy_next, heavy (64 bits); the light queues
+    uint32_t* ctr;                    // [TRI_CTR_WORDS] nlight, -, heavy, heavy_next (64 bits each); the light queues
     uint32_t* heavy_group;
     unsigned long long* heavy_off;
 };
@@ -1078,7 +1078,7 @@ TriJoinArgs tri_join_args(const TriLayout& L, const mj_plan_t& p, uint32_t first
     J.nlight = P.ctr; J.light = P.light; J.light_next = P.ctr + TRI_QUEUE_PAD;
     J.heavy = reinterpret_cast<unsigned long long*>(P.ctr + 2);
     J.heavy_group = P.heavy_group; J.heavy_off = P.heavy_off;
-    J.heavy_next = P.ctr + 1; J.share = 1u << p.log2_share; J.total = out;
+    J.heavy_next = reinterpret_cast<unsigned long long*>(P.ctr + 4); J.share = 1u << p.log2_share; J.total = out;
     return J;
 }
 

@@ -821,12 +821,12 @@ constexpr uint32_t TRI_HEAVY_X = 2048;     // slice of a staged list handled by 
 constexpr uint32_t TRI_HEAVY_DIR_BITS = 12;// its directory
 constexpr uint32_t TRI_HEAVY_PER_CU = 2048 / TRI_HEAVY_THREADS;   // workgroups that fill a CU's waves
 static_assert(TRI_HEAVY_X <= 65535, "directory entries hold 16-bit positions and counts");
-constexpr uint32_t TRI_HEAVY_S = 2048;     // S tuples per heavy item (chunks of at most 64 per wave)
+constexpr uint32_t TRI_HEAVY_S = 2048;     // S tuples per heavy item (chunks of at most 64 per wave), more in groups beyond 2^27
 constexpr uint32_t TRI_SHORT_LIST = 16;    // lists walked by one lane
 constexpr uint32_t TRI_LIGHT_PER_CU = 6;   // workgroups of the light kernel that fit a CU (LDS)
 constexpr uint32_t TRI_QUEUES = 32;        // queues of light items, their counters
 constexpr uint32_t TRI_QUEUE_PAD = 32;     // this many words apart (a cache line each)
-constexpr uint32_t TRI_CTR_WORDS = TRI_QUEUE_PAD * (1 + TRI_QUEUES);   // nlight, heavy_next, heavy (64 bits); queues
+constexpr uint32_t TRI_CTR_WORDS = TRI_QUEUE_PAD * (1 + TRI_QUEUES);   // nlight, -, heavy, heavy_next (64 bits each); queues
 
 struct RunIndex {                          // runs of equal high words of sorted keys
     const uint32_t* run_key;               // [nruns]
@@ -984,7 +984,7 @@ struct TriJoinArgs {
     const unsigned long long* heavy;       // heavy groups << HEAVY_SHIFT | their items
     const uint32_t* heavy_group;
     const unsigned long long* heavy_off;
-    uint32_t* heavy_next;
+    unsigned long long* heavy_next;
     uint32_t share;
     uint32_t low_bits;                     // lists are ordered by their words' bits from low_bits up (at most 16)
     unsigned long long* total;

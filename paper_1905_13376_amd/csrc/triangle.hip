@@ -158,12 +158,19 @@ MJ_KERNEL(k_run_emit, RUN_THREADS, RunLaunch) {
 // --------------------------------------------------------------- classify
 // Light: R list of b short and S group small -> one wave.  Heavy: otherwise
 // -> (slice of R's list) x (range of the S group) workgroup items, counted
-// per group here and enumerated through a scan of the counts.
-__device__ __forceinline__ void heavy_shape(uint32_t x, uint32_t gn, uint32_t share,
-                                            uint32_t& nsl, uint32_t& nsr) {
-    nsl = (x + TRI_HEAVY_X - 1) / TRI_HEAVY_X;
-    nsl = max(nsl, min(share, (x + 63) / 64));
-    nsr = (gn + TRI_HEAVY_S - 1) / TRI_HEAVY_S;
+// per group here and enumerated through the counts before each group.
+// `range` is the S tuples of an item: TRI_HEAVY_S, more only where a group
+// would have over 2^TRI_HEAVY_RANGE_BITS ranges, so that the items of any
+// relations of under 2^32 tuples stay within HEAVY_SHIFT bits (a hub of 2^27
+// tuples on both sides has 2^32 of them).
+constexpr uint32_t TRI_HEAVY_RANGE_BITS = 16;
+__device__ __forceinline__ void heavy_shape(uint32_t x, uint32_t gn, uint32_t share, uint32_t& nsl, uint32_t& nsr,
+                                            uint32_t& range) {
+    nsl = (uint32_t)((uint64_t(x) + TRI_HEAVY_X - 1) / TRI_HEAVY_X);
+    nsl = max(nsl, min(share, (uint32_t)((uint64_t(x) + 63) / 64)));
+    range = TRI_HEAVY_S;
+    while (gn > uint64_t(range) << TRI_HEAVY_RANGE_BITS) range *= 2;
+    nsr = (uint32_t)((uint64_t(gn) + range - 1) / range);
 }
 
 // Groups are appended with one atomic per workgroup and round of 1024 groups
@@ -180,8 +187,8 @@ MJ_KERNEL(k_tri_classify, 256, TriClassifyPair) {
     const uint64_t ng = *C.Grp.nruns;
     const int lane = lane_id(), w = threadIdx.x / WAVE;
     for (uint64_t g0 = bid * 1024ull; g0 < ng; g0 += A.per * 1024ull) {      // uniform over the block
-        uint32_t key[4], run[4], items[4], nlight = 0;
-        unsigned long long nheavy = 0;
+        uint32_t key[4], run[4], nlight = 0;
+        unsigned long long items[4], nheavy = 0;
         bool live[4], light[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -202,9 +209,9 @@ MJ_KERNEL(k_tri_classify, 256, TriClassifyPair) {
             if (light[u]) {
                 ++nlight;
             } else {
-                uint32_t nsl, nsr;
-                heavy_shape(x, gn, C.share, nsl, nsr);
-                items[u] = nsl * nsr;
+                uint32_t nsl, nsr, range;
+                heavy_shape(x, gn, C.share, nsl, nsr, range);
+                items[u] = (unsigned long long)nsl * nsr;
                 nheavy += (1ull << HEAVY_SHIFT) | items[u];
             }
         }
@@ -564,16 +571,16 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
     // item -> (heavy group, slice of the staged list, range of the group)
     const uint32_t lo = wave_last_le(A.heavy_off, (uint32_t)(*A.heavy >> HEAVY_SHIFT), it);
     const uint32_t g = A.heavy_group[lo];
-    const uint32_t local = (uint32_t)(it - A.heavy_off[lo]);
+    const unsigned long long local = it - A.heavy_off[lo];
     uint32_t rs = 0, x = 0;
     run_lookup(A.Stg, A.Grp.run_key[g], rs, x);
     const uint32_t gs = A.Grp.run_start[g], gn = A.Grp.run_start[g + 1] - gs;
-    uint32_t nsl, nsr;
-    heavy_shape(x, gn, A.share, nsl, nsr);
-    const uint32_t sa = local / nsr, sb = local % nsr;
+    uint32_t nsl, nsr, range;
+    heavy_shape(x, gn, A.share, nsl, nsr, range);
+    const uint32_t sa = (uint32_t)(local / nsr), sb = (uint32_t)(local % nsr);
     const uint32_t r0 = rs + (uint32_t)((uint64_t)x * sa / nsl);
     const uint32_t r1 = rs + (uint32_t)((uint64_t)x * (sa + 1) / nsl);
-    const uint32_t s0 = gs + sb * TRI_HEAVY_S, s1 = min(gs + gn, s0 + TRI_HEAVY_S);
+    const uint32_t s0 = gs + sb * range, s1 = gs + (uint32_t)min<uint64_t>(gn, (uint64_t(sb) + 1) * range);
     if (r0 == r1) return 0;                           // uniform across the block
     const uint32_t len = r1 - r0;
     const uint32_t low = (1u << A.low_bits) - 1u;      // the bits the lists are not ordered by
@@ -619,16 +626,16 @@ __device__ unsigned long long tri_heavy_item(const TriJoinArgs& A, unsigned long
 MJ_KERNEL(k_tri_heavy, TRI_HEAVY_THREADS, TriJoinPair) {
     (void)vg;
     TRI_HEAVY_SETUP
-    __shared__ uint32_t s_item;
+    __shared__ unsigned long long s_item;
     unsigned long long acc = 0;
     for (int pass = 0; pass < 2; ++pass) {
         const TriJoinArgs& P = A.pass[pass];
         const unsigned long long nitems = *P.heavy & ((1ull << HEAVY_SHIFT) - 1ull);
         while (nitems) {                              // uniform across the block
             __syncthreads();
-            if (threadIdx.x == 0) { s_item = atomicAdd(P.heavy_next, 1u); hchunk = 0; hdup = 0; }
+            if (threadIdx.x == 0) { s_item = atomicAdd(P.heavy_next, 1ull); hchunk = 0; hdup = 0; }
             __syncthreads();
-            const uint32_t it = s_item;
+            const unsigned long long it = s_item;
             if (it >= nitems) break;
             acc += tri_heavy_item(P, it, B);
         }
