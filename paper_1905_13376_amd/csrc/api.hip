@@ -1272,8 +1272,12 @@ int run_star3(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel* T, ui
         A.r0 = R->col0; A.r1 = R->col1; A.r_stride = R->stride; A.n_r = (uint32_t)R->n;
         A.s0 = S->col0; A.s1 = S->col1; A.s_stride = S->stride; A.n_s = S->n;
         A.t0 = T->col0; A.t_stride = T->stride; A.n_t = (uint32_t)T->n;
-        A.partial = L.partial; A.rep = L.occ; A.count = count; A.a_domain = a_domain;
         const uint32_t grid = star_grid_cu(S->n, ctx->num_cu);
+        const bool fill = a_domain > uint64_t(grid) * STAR_ZERO_MAX;
+        A.partial = L.partial; A.rep = L.occ; A.count = count; A.nzero = fill ? 0 : a_domain;
+        if (fill)
+            MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(grid_for(a_domain, 256, 4096)), dim3(256), 0, s,
+                      count, (uint64_t)a_domain, 0ull);
         MJ_LAUNCHM(prof, "k_star_stream", k_star_stream, dim3(grid), dim3(STAR_THREADS), 0, s, A);
         StarFinishArgs F;
         F.r0 = R->col0; F.r_stride = R->stride; F.n_r = A.n_r;

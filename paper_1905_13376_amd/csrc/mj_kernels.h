@@ -566,6 +566,11 @@ static_assert(STAR_GROUPS < STAR_STRIDE, "the cascade's sums fit a workgroup's s
 constexpr uint32_t STAR_SMALL = 4096;
 constexpr uint32_t STAR_BKTS = 2048;       // displacement buckets of a table
 constexpr uint32_t STAR_PAIRS = 4;         // pairs of rows per thread per step (2: 7 % longer)
+// counts a workgroup zeroes before its pass at most; more of them get a fill
+// launch of their own.  A workgroup writes 2^15 counts in about 3 us, a launch
+// takes about 5: with 2^24 counts and at most 16,384 tuples in S (one
+// workgroup) 1803 us without the fill, 72 us with it
+constexpr uint32_t STAR_ZERO_MAX = 1u << 15;
 
 struct StarStreamArgs {
     const uint32_t* r0; const uint32_t* r1; int64_t r_stride; uint32_t n_r;   // R(A, B)
@@ -573,8 +578,8 @@ struct StarStreamArgs {
     const uint32_t* t0; int64_t t_stride; uint32_t n_t;                       // T's C column
     unsigned long long* partial;   // [gridDim][STAR_STRIDE] sums per first R tuple of a B value
     uint32_t* rep;                 // [n_r + 2] first R tuple with the same B; the finish's ticket, its flag
-    unsigned long long* count;     // zeroed here
-    uint32_t a_domain;
+    unsigned long long* count;
+    uint32_t nzero;                // entries of count zeroed here: a_domain, or none
 };
 MJ_KERNEL_DECL(k_star_stream, StarStreamArgs);
 

@@ -557,7 +557,7 @@ MJ_KERNEL(k_star_stream, STAR_THREADS, StarStreamArgs) {
     __shared__ uint32_t s_special[2];
     static_assert(sizeof(acc) >= STAR_LDS_SLOTS * sizeof(uint32_t), "the sums' space holds a build's scratch");
     const uint32_t t = threadIdx.x;
-    for (uint64_t i = uint64_t(vg.bid) * STAR_THREADS + t; i < A.a_domain; i += uint64_t(vg.nblk) * STAR_THREADS)
+    for (uint64_t i = uint64_t(vg.bid) * STAR_THREADS + t; i < A.nzero; i += uint64_t(vg.nblk) * STAR_THREADS)
         A.count[i] = 0;
     const StarMap TM{tkey, reinterpret_cast<uint16_t*>(tval), tdisp};
     const StarMap RM{rkey, reinterpret_cast<uint16_t*>(rval), rdisp};
