@@ -1145,8 +1145,8 @@ int cascade_triangle(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
 }
 
 // ------------------------------------------------------------- star join
+static_assert(DENSE_MAX_A == 1u << (PART_MAX_BITS + ACELL_MAX_SHIFT), "planner and layouts agree on the A ranges");
 static_assert(STAR_GROUPS == STAR_PLAN_MAX_R, "planner and kernels agree on the star limit");
-static_assert(SMALL_MAX == DENSE_SMALL_MAX, "planner and kernels agree on the small joins' limit");
 
 struct StarLayout {
     TableLayout Rt, Tt;               // one-bucket tables: R on B, T on C
@@ -1511,9 +1511,7 @@ int run_dense(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, con
     return MJ_OK;
 }
 
-// Small relations, dense keys: three launches, no partition.  The line lies
-// where reading a relation in every workgroup costs what its partition does
-// (SMALL_MAX tuples); the domains are within 2 n + 4096 of it.
+// Small relations, dense keys (small_dense): three launches, no partition.
 int run_small(Prof* prof, const mj_rel& R, const mj_rel& S, const mj_rel& T, const mj_plan_t& p,
               unsigned long long* count, void* ws, hipStream_t s) {
     const DenseLayout L = dense_layout(ws, p);
@@ -2083,7 +2081,7 @@ int mj_linear3_count(mj_ctx* ctx, const mj_rel* R, const mj_rel* S, const mj_rel
                       cnt, (uint64_t)a_domain, 0ull);
             return MJ_OK;
         }
-        if (std::max({R->n, S->n, T->n}) <= SMALL_MAX) return run_small(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
+        if (small_dense(p)) return run_small(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
         return run_dense(&ctx->prof, *R, *S, *T, p, cnt, ws, sd);
     }
     const bool compact = ws_bytes < linear_layout(nullptr, p).bytes;

@@ -1026,9 +1026,9 @@ MJ_KERNEL(k_range_count, RANGE_THREADS, RangeCountArgs) {
 // The same three sums with no partition: one workgroup per range of keys
 // reads every tuple and keeps those of its range.  At these sizes a launch
 // costs more than reading the relation from L2 in every workgroup, so a join
-// is three launches instead of seven: 34.8 -> 18.4 us at 16,384 tuples a
-// relation, 34.2 -> 22.8 us at 32,768; at 65,536 (38.7 us) the partition is
-// the faster way (35.1 us).  Bound by the range test of every tuple in every
+// is three launches instead of seven: 30.2 -> 16.3 us at 16,384 tuples a
+// relation, 30.2 -> 23.7 us at 32,768 (keys below 4096); DENSE_SMALL_MAX says
+// where the line lies.  Bound by the range test of every tuple in every
 // workgroup's vector units.
 template <bool LAST, class TW, class TO>
 __device__ __forceinline__ void small_accumulate(const SmallAccArgs<TW, TO>& A, TO* acc, VGrid vg) {

@@ -476,7 +476,6 @@ MJ_KERNEL_DECL(k_range_count, RangeCountArgs);
 // Small joins: the three sums without a partition, each a launch of one
 // workgroup per range of keys that reads the whole relation.
 constexpr int SMALL_THREADS = 1024;
-constexpr uint32_t SMALL_MAX = 49152;        // tuples per relation
 constexpr uint32_t SMALL_RANGES = 64;        // workgroups (more when the domain needs them)
 constexpr uint32_t SMALL_SPAN = 4096;        // keys per workgroup at most (32 KB of sums)
 template <class TW, class TO>

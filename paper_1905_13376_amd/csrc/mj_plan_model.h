@@ -28,8 +28,20 @@ inline bool star_plan_fits(const mj_plan_t& p) {
 }
 
 // dense keys and at most this many tuples per relation: the sums run without
-// a partition (the kernels' SMALL_MAX)
-constexpr uint64_t DENSE_SMALL_MAX = 49152;
+// a partition, three launches whose workgroups each read a whole relation.
+// The line lies where the two ways cross: at 40,960 tuples 27.7 us without the
+// partition and 29.9 with it for keys below 4096, 34.7 and 33.2-35.4 us for
+// keys below the number of tuples, 85.5 and 86.4 us with 2^24 A values (then
+// 4096 workgroups read R, but writing the counts takes longer); at 49,152
+// tuples 40.1 and 33.7 us
+constexpr uint64_t DENSE_SMALL_MAX = 40960;
+// direct-indexed sums: A values below 2^12 ranges of at most 2^12
+constexpr uint32_t DENSE_MAX_A = 1u << 24;
+// the planner's and the dispatch's rule
+inline bool small_dense(const mj_plan_t& p) {
+    return (p.flags & MJ_PLAN_DENSE_KEYS) && p.a_domain <= DENSE_MAX_A && p.n_r <= DENSE_SMALL_MAX &&
+           p.n_s <= DENSE_SMALL_MAX && p.n_t <= DENSE_SMALL_MAX;
+}
 
 // the degree-oriented cyclic join pays for its orientation pass (about
 // 0.4 ms of extra launches) when the relation is large and its wedges dense:

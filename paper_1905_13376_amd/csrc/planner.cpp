@@ -180,8 +180,8 @@ int analytic_plan(int kind, mj_plan_t& p, int num_cu, const DeviceModel& m) {
         p.log2_nc = std::min<uint32_t>(10, ceil_log2((p.n_t + 4095) / 4096));
         p.est_ms_3way = model_linear_3way_ms(m, R, S, T);
         // small relations with dense keys: three launches and no partition
-        // (run_small; 18 us at 16,384 tuples where the star plan takes 95)
-        if ((p.flags & MJ_PLAN_DENSE_KEYS) && std::max({p.n_r, p.n_s, p.n_t}) <= DENSE_SMALL_MAX)
+        // (16 us at 16,384 tuples)
+        if (small_dense(p))
             p.est_ms_3way = 3.0 * m.launch_us * 1e-3;
         p.est_ms_cascade = model_linear_cascade_ms(m, R, S, T, I);
         p.est_ms_star = star_plan_fits(p) ? model_star_ms(m, R, S, T) : 0.0;
