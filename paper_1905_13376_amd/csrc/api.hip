@@ -1905,6 +1905,17 @@ static int column_maxima(Prof* prof, const mj_rel* const* src, const int* col, c
     return MJ_OK;
 }
 
+// least workspace a candidate of the autotuner runs in (hashed tables without
+// their narrow forms, the cascade's whole intermediate)
+static size_t tuned_bytes(const mj_plan_t& c) {
+    if (c.kind == MJ_LINEAR && c.algo == MJ_ALGO_3WAY && !dense_plan(c)) return linear_layout(nullptr, c, true).bytes;
+    if (c.kind == MJ_LINEAR && c.algo == MJ_ALGO_CASCADE && !dense_plan(c)) {
+        const CascadeLayout C = cascade_layout(nullptr, c, 0, true);
+        return C.base_bytes + C.i_cap * sizeof(uint2) + 256;
+    }
+    return c.workspace_bytes;
+}
+
 uint64_t mj_plan_workspace(int kind, uint64_t n_r, uint64_t n_s, uint64_t n_t) {
     return plan_layout(nullptr, kind, n_r, n_s, n_t).bytes;
 }
@@ -2609,7 +2620,8 @@ static mj_plan_t batch_plan(const mj_batch_item& it) {
 static size_t batch_item_bytes(const mj_batch_item& it) {
     if (it.plan.algo != MJ_ALGO_3WAY) return it.plan.workspace_bytes;
     if (it.kind == MJ_LINEAR)
-        return dense_plan(it.plan) ? dense_layout(nullptr, batch_plan(it)).bytes : linear_layout(nullptr, it.plan).bytes;
+        return dense_plan(it.plan) ? dense_layout(nullptr, batch_plan(it)).bytes
+                                   : linear_layout(nullptr, it.plan, true).bytes;
     return tri_layout(nullptr, it.plan).bytes;
 }
 
@@ -2648,7 +2660,7 @@ static int record_batch(mj_ctx* ctx, const mj_batch_item* items, int n, char* ba
             st = run_plan(ctx, it.kind, &it.R, &it.S, &it.T, it.a_domain, it.out, batch_plan(it), wsi, bytes, s);
         } else if (it.kind == MJ_LINEAR) {
             st = [&]() -> int {
-                LinearLayout L = linear_layout(wsi, p);
+                LinearLayout L = linear_layout(wsi, p, true);      // (its cells read no narrow form)
                 unsigned long long* count = reinterpret_cast<unsigned long long*>(it.out);
                 if (it.a_domain)
                     MJ_LAUNCHM(prof, "k_fill_u64", k_fill_u64, dim3(grid_for(it.a_domain, 256, 4096)), dim3(256), 0, s,
@@ -2993,7 +3005,7 @@ int mj_autotune(mj_ctx* ctx, int kind, const mj_rel* R, const mj_rel* S, const m
     for (mj_plan_t c : cand) {
         int st = plan_workspace(c);
         if (st) return st;
-        if (c.workspace_bytes > ws_bytes) continue;
+        if (tuned_bytes(c) > ws_bytes) continue;
         if (kind == MJ_LINEAR && (st = run_plan(ctx, kind, R, S, T, a_domain, out, c, ws, ws_bytes, stream)))
             return st;
         MJ_HIP(hipEventRecord(e0, s));
@@ -3033,13 +3045,19 @@ int plan_workspace(mj_plan_t& p) {
     if (p.kind == MJ_LINEAR) {
         // enough for whichever algorithm the plan picked, for the other one
         // when the caller runs both on the same plan, and for every bucket
-        // count the autotuner tries (up to 2^10)
+        // count the autotuner tries (up to 2^10); with the tables' narrow
+        // forms where the plan's own route reads them, and in the tuner's
+        // bucket counts only where their least size (32 bytes a slot of
+        // NT_MIN_SLOTS) is small beside the tables: a join of 20,000 tuples
+        // asked for 21.6 MB instead of 4.3
         size_t need = 0;
+        const bool dense = dense_plan(p);
         for (int wide = 0; wide < 2; ++wide) {
             mj_plan_t q = p;
             if (wide) { q.log2_nb = std::max<uint32_t>(q.log2_nb, 10); q.log2_nc = std::max<uint32_t>(q.log2_nc, 10); }
-            const size_t lin = linear_layout(nullptr, q).bytes;
-            const CascadeLayout C = cascade_layout(nullptr, q, 0);
+            const bool compact = dense || (wide && std::min(p.n_s, p.n_t) < NT_MIN_SLOTS);
+            const size_t lin = linear_layout(nullptr, q, compact).bytes;
+            const CascadeLayout C = cascade_layout(nullptr, q, 0, compact && !dense);
             need = std::max({need, lin, C.base_bytes + C.i_cap * sizeof(uint2) + 256});
         }
         if (p.flags & MJ_PLAN_DENSE_KEYS) need = std::max(need, dense_layout(nullptr, p).bytes);

@@ -11,9 +11,10 @@ sim.cpp).  Output: _build/hostsim/replay (the benchmark's call sequence,
 replay.cpp), _build/hostsim/abi_check (argument checks that need a
 context, abi_check.cpp), _build/hostsim/multi_check (merged launches'
 block search, multi_check.cpp), _build/hostsim/handoff_check (the last
-piece of a split bucket among rows that have not arrived, handoff_check.cpp)
-and _build/hostsim/heavy_check (heavy work items beyond 32 bits of the
-cyclic join, heavy_check.cpp).
+piece of a split bucket among rows that have not arrived, handoff_check.cpp),
+_build/hostsim/heavy_check (heavy work items beyond 32 bits of the cyclic
+join, heavy_check.cpp) and _build/hostsim/workspace_check (what small plans
+ask for, workspace_check.cpp).
 """
 from __future__ import annotations
 
@@ -60,7 +61,7 @@ def build(sanitize: bool = True, jobs: int = 8, verbose: bool = False) -> str:
     units += [os.path.join(HERE, "sim.cpp")]
     mains = [os.path.join(HERE, "replay.cpp"), os.path.join(HERE, "abi_check.cpp"),
              os.path.join(HERE, "multi_check.cpp"), os.path.join(HERE, "handoff_check.cpp"),
-             os.path.join(HERE, "heavy_check.cpp")]
+             os.path.join(HERE, "heavy_check.cpp"), os.path.join(HERE, "workspace_check.cpp")]
     # uninitialised locals (kernel argument structs among them) hold a
     # non-zero pattern, so a field left unset reads as a wild value, not 0
     flags = ["-x", "c++", "-std=c++17", "-g", "-O1", "-fno-omit-frame-pointer", "-pthread",
