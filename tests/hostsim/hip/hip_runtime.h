@@ -73,6 +73,7 @@ const dim3& grid_dim();
 unsigned lane();
 void* dyn_smem();
 void syncthreads();
+void before_atomic();                  // HIPSIM_ORDER: may let other waves run first
 uint64_t wave_exchange(uint64_t v, int op, int arg, int width);   // op: see sim.cpp
 enum { OP_SHFL = 0, OP_UP = 1, OP_DOWN = 2, OP_XOR = 3, OP_BALLOT = 4 };
 
@@ -159,32 +160,35 @@ inline int32_t __float_as_int(float f) { int32_t u; memcpy(&u, &f, 4); return u;
 
 // atomics (global and LDS memory alike)
 template <class T>
-inline T atomicAdd(T* p, T v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
+inline T atomicAdd(T* p, T v) { ::hipsim::before_atomic(); return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
 inline float atomicAdd(float* p, float v) {
     float old = *p;
     while (!__atomic_compare_exchange(p, &old, (float[]){old + v}, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED)) {}
     return old;
 }
 template <class T>
-inline T atomicOr(T* p, T v) { return __atomic_fetch_or(p, v, __ATOMIC_RELAXED); }
+inline T atomicOr(T* p, T v) { ::hipsim::before_atomic(); return __atomic_fetch_or(p, v, __ATOMIC_RELAXED); }
 template <class T>
-inline T atomicAnd(T* p, T v) { return __atomic_fetch_and(p, v, __ATOMIC_RELAXED); }
+inline T atomicAnd(T* p, T v) { ::hipsim::before_atomic(); return __atomic_fetch_and(p, v, __ATOMIC_RELAXED); }
 template <class T>
-inline T atomicExch(T* p, T v) { return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
+inline T atomicExch(T* p, T v) { ::hipsim::before_atomic(); return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
 template <class T>
 inline T atomicMax(T* p, T v) {
+    ::hipsim::before_atomic();
     T old = __atomic_load_n(p, __ATOMIC_RELAXED);
     while (old < v && !__atomic_compare_exchange_n(p, &old, v, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED)) {}
     return old;
 }
 template <class T>
 inline T atomicMin(T* p, T v) {
+    ::hipsim::before_atomic();
     T old = __atomic_load_n(p, __ATOMIC_RELAXED);
     while (v < old && !__atomic_compare_exchange_n(p, &old, v, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED)) {}
     return old;
 }
 template <class T>
 inline T atomicCAS(T* p, T cmp, T v) {
+    ::hipsim::before_atomic();
     __atomic_compare_exchange_n(p, &cmp, v, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED);
     return cmp;
 }

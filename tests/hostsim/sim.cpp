@@ -94,7 +94,23 @@ struct Launch {
     uint64_t nblocks;
 };
 
+// HIPSIM_ORDER=seed: the workgroup's waves run in an order drawn anew each
+// round, some held back, and now and then a lane waits before an atomic, so
+// that steps which only a barrier should order really come in any order
+uint64_t order_seed() {
+    static const uint64_t seed = [] {
+        const char* e = std::getenv("HIPSIM_ORDER");
+        return e ? std::strtoull(e, nullptr, 0) + 1 : uint64_t(0);
+    }();
+    return seed;
+}
+
 struct Worker {
+    uint64_t rng = 0;                 // 0: lanes in their order
+    uint32_t draw() {
+        rng ^= rng << 13; rng ^= rng >> 7; rng ^= rng << 17;
+        return (uint32_t)(rng >> 20);
+    }
     std::vector<Lane> lanes;
     std::vector<Wave> waves;
     void* sched_sp = nullptr;
@@ -173,15 +189,25 @@ void run_block(Worker& w, uint64_t b) {
     }
     w.live = (int)nthr;
     w.at_barrier = 0;
+    w.rng = order_seed() ? (order_seed() * 0x9E3779B97F4A7C15ull) ^ (b + 1) * 0xBF58476D1CE4E5B9ull : 0;
+    uint32_t turn[MAX_THREADS / WAVE];
+    for (uint32_t q = 0; q < nwaves; ++q) turn[q] = q;
     while (w.live > 0) {
         bool ran = false;
-        for (uint32_t t = 0; t < nthr; ++t) {
-            Lane& l = w.lanes[t];
-            if (l.state != RUNNABLE) continue;
-            ran = true;
-            cur = &l;
-            hipsim_switch(&w.sched_sp, l.sp);
-            cur = nullptr;
+        if (w.rng)
+            for (uint32_t q = nwaves; q > 1; --q) std::swap(turn[q - 1], turn[w.draw() % q]);
+        for (uint32_t i = 0; i < nwaves; ++i) {
+            const uint32_t q = turn[i];
+            const bool hold = w.rng && i > 0 && w.draw() % 2;
+            for (uint32_t t = q * WAVE; t < nthr && t < (q + 1) * WAVE; ++t) {
+                Lane& l = w.lanes[t];
+                if (l.state != RUNNABLE) continue;
+                ran = true;
+                if (hold) break;
+                cur = &l;
+                hipsim_switch(&w.sched_sp, l.sp);
+                cur = nullptr;
+            }
         }
         // a barrier every live lane has reached opens
         if (w.at_barrier > 0 && w.at_barrier == w.live) {
@@ -309,6 +335,11 @@ void syncthreads() {
     l->state = AT_BARRIER;
     l->w->at_barrier += 1;
     to_scheduler(l);
+}
+
+void before_atomic() {
+    Lane* l = cur;
+    if (l && l->w->rng && l->w->draw() % 16 == 0) to_scheduler(l);
 }
 
 uint64_t wave_exchange(uint64_t v, int op, int arg, int width) {
