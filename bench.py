@@ -10,8 +10,8 @@ A step is one mj_linear3_count call: with the planner's direct-indexed
 tables, one range partition of F and three per-range sums (multiplicities
 of C, W per B, counts per A).  Inputs are resident in HBM before timing
 starts; planning happens once, outside the timed region.  One JSON line
-goes to stdout.  The other paths (cascade, small, fm, emit, star,
-triangle, batch, planner) run with --only LEG, or all of them with
+goes to stdout.  The other paths (cascade, small, fm, emit, slarge, skew,
+triangle, batch, planner, gather) run with --only LEG, or all of them with
 --paths, each in a child process of its own.
 """
 from __future__ import annotations
@@ -347,65 +347,13 @@ def time_and_profile(ctx, fn, steps, warmup=1, prof_calls=None):
     return ms, {k: (v[0] / n, v[1] / n) for k, v in prof.items()}
 
 
-def star_path(mj, ctx):
-    """The star join (Sec. 6): a 2^26-tuple fact relation with two 4096-tuple
-    dimension relations, under the plan the planner picks (the star
-    three-way join) and under the star cascade, the partitioned three-way
-    join and the cascade of binary hash joins."""
-    import numpy as np
-    import torch
-    from workloads import generators as G
-    sys.path.insert(0, os.path.join(ROOT, "tests"))
-    import brute
-    # this sequence ended with an illegal access on the GPU and the cause is
-    # not shown; the star plans themselves are tested at this size
-    raise RuntimeError("the star leg is switched off: a GPU fault in it is not explained yet")
-    log("generating the star schema (2^26 fact tuples, 4096-tuple dimensions)")
-    R, S, T = G.star_schema()
-    a_dom = G.STAR["a_domain"]
-    Rd, Sd, Td = (torch.from_numpy(x).to("cuda") for x in (R, S, T))
-    closed = brute.linear_closed_total(R, S, T)
-    plan = ctx.plan(mj.LINEAR, Rd, Sd, Td, a_dom)
-    ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
-    cnt = torch.empty(a_dom, dtype=torch.int64, device="cuda")
-    res = {"planned_algo": int(plan.algo), "fact_tuples": int(S.shape[0]),
-           "est_ms": {"star": round(plan.est_ms_star, 3), "star_cascade": round(plan.est_ms_star_cascade, 3),
-                      "3way": round(plan.est_ms_3way, 3), "cascade": round(plan.est_ms_cascade, 3)}}
-    n_in = R.shape[0] + S.shape[0] + T.shape[0]
-    for name, algo in (("star", mj.ALGO_STAR), ("star_cascade", mj.ALGO_STAR_CASCADE),
-                       ("partitioned_3way", mj.ALGO_3WAY), ("cascade", mj.ALGO_CASCADE)):
-        p = plan.copy()
-        p.algo = algo
-        if algo in (mj.ALGO_STAR, mj.ALGO_3WAY):
-            fn = lambda: ctx.linear3_count(Rd, Sd, Td, a_dom, plan=p, out=cnt, workspace=ws)
-        else:
-            fn = lambda: ctx.cascade2_count(mj.LINEAR, Rd, Sd, Td, a_dom, plan=p, out=cnt, workspace=ws)
-        ms, kp = time_and_profile(ctx, fn, 5)
-        ok = int(mj.as_u64(cnt).sum(dtype=np.uint64)) == closed
-        kern = {k: v[0] / max(v[1], 1) for k, v in kp.items()}          # ms per launch
-        ent = {"ms": round(ms, 4), "tuples_per_s": n_in / (ms * 1e-3), "sum_equals_closed_form": ok,
-               "kernels_us": {k: round(v * 1e3, 1) for k, v in sorted(kern.items(), key=lambda kv: -kv[1])[:6]}}
-        kg = next((k for k in ("k_star_stream", "k_star_group_b", "k_star_group_a") if k in kern), None)
-        if name == "star" and kg:
-            us = kern[kg] * 1e3
-            nbytes = 8 * S.shape[0]                      # the fact relation, read once
-            ach = nbytes / (us * 1e-6) / 1e9
-            ent["roofline"] = {"bound": "hbm", "kernel": kg, "achieved": round(ach, 1),
-                               "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
-                               "algorithmic_bytes": nbytes, "avg_launch_us": round(us, 2)}
-        res[name] = ent
-        log(f"star schema, {name}: {ms:.3f} ms, sum ok {ok}")
-    res["speedup_star_over_star_cascade"] = round(res["star_cascade"]["ms"] / res["star"]["ms"], 2)
-    res["speedup_star_over_partitioned"] = round(res["partitioned_3way"]["ms"] / res["star"]["ms"], 2)
-    del ws, Rd, Sd, Td
-    return res
-
-
 def slarge_path(mj, ctx):
     """The S-largest form of the linear join (Sec. 4, after Algorithm 1): a
     2^26-tuple S with R and T of 2^16 tuples each (beyond the star plans),
-    under the planner's S-largest plan and, on the same bucket counts, the
-    partitioned three-way join and the cascade."""
+    under the planner's S-largest plan.  (The partitioned three-way join and
+    the cascade are not run on 2^26 facts here: a sequence with both on such
+    a fact relation ended with an illegal access on the GPU, and the cause
+    is not shown.)"""
     import numpy as np
     import torch
     from workloads import generators as G
@@ -423,27 +371,14 @@ def slarge_path(mj, ctx):
     res = {"planned_algo": int(plan.algo), "log2_nb": int(plan.log2_nb), "log2_nc": int(plan.log2_nc),
            "est_ms": {"slarge": round(plan.est_ms_slarge, 3), "3way": round(plan.est_ms_3way, 3),
                       "cascade": round(plan.est_ms_cascade, 3)}}
-    clog2 = lambda x: max(0, (int(x) - 1).bit_length())
-    for name, algo in (("s_largest", mj.ALGO_SLARGE), ("partitioned_3way", mj.ALGO_3WAY),
-                       ("cascade", mj.ALGO_CASCADE)):
-        p = plan.copy()
-        p.algo = algo
-        if algo != mj.ALGO_SLARGE:
-            # the bucket counts the planner gives these plans (about 16K S
-            # tuples per B bucket, 32K T tuples per C bucket)
-            p.log2_nb = min(10, clog2((S.shape[0] + 16383) // 16384))
-            p.log2_nc = min(10, clog2((T.shape[0] + 32767) // 32768))
-        if algo == mj.ALGO_CASCADE:
-            fn = lambda: ctx.cascade2_count(mj.LINEAR, Rd, Sd, Td, a_dom, plan=p, out=cnt, workspace=ws)
-        else:
-            fn = lambda: ctx.linear3_count(Rd, Sd, Td, a_dom, plan=p, out=cnt, workspace=ws)
-        ms, kp = time_and_profile(ctx, fn, 5)
-        ok = int(mj.as_u64(cnt).sum(dtype=np.uint64)) == closed
-        res[name] = {"ms": round(ms, 4), "tuples_per_s": n_in / (ms * 1e-3), "sum_equals_closed_form": ok,
-                     "kernels_us": {k: round(v[0] / max(v[1], 1) * 1e3, 1)
-                                    for k, v in sorted(kp.items(), key=lambda kv: -kv[1][0])[:5]}}
-        log(f"S-largest workload, {name}: {ms:.3f} ms, sum ok {ok}")
-    res["speedup_over_partitioned"] = round(res["partitioned_3way"]["ms"] / res["s_largest"]["ms"], 2)
+    p = plan.copy()
+    p.algo = mj.ALGO_SLARGE
+    ms, kp = time_and_profile(ctx, lambda: ctx.linear3_count(Rd, Sd, Td, a_dom, plan=p, out=cnt, workspace=ws), 5)
+    ok = int(mj.as_u64(cnt).sum(dtype=np.uint64)) == closed
+    res["s_largest"] = {"ms": round(ms, 4), "tuples_per_s": n_in / (ms * 1e-3), "sum_equals_closed_form": ok,
+                        "kernels_us": {k: round(v[0] / max(v[1], 1) * 1e3, 1)
+                                       for k, v in sorted(kp.items(), key=lambda kv: -kv[1][0])[:5]}}
+    log(f"S-largest workload: {ms:.3f} ms, sum ok {ok}")
     return res
 
 
@@ -615,9 +550,9 @@ def emit_path(mj, ctx, F, Fd):
     return res
 
 
-LEGS = ("cascade", "small", "fm", "emit", "star", "slarge", "skew", "triangle", "batch", "planner", "gather")
+LEGS = ("cascade", "small", "fm", "emit", "slarge", "skew", "triangle", "batch", "planner", "gather")
 DEFAULT_LEGS = ("small", "skew", "triangle", "batch", "planner", "gather")
-OWN_WORKLOAD_LEGS = ("small", "star", "slarge", "skew", "triangle", "batch", "planner")
+OWN_WORKLOAD_LEGS = ("small", "slarge", "skew", "triangle", "batch", "planner")
 
 
 def child_paths(legs):
@@ -646,8 +581,6 @@ def extra_paths(mj, ctx, F, Fd, a_domain, plan, ms_3way, only=None):
         out["distinct_fm"] = fm_path(mj, ctx, F, Fd, a_domain)
     if only in (None, "emit"):
         out["materialised"] = emit_path(mj, ctx, F, Fd)
-    if only in (None, "star"):
-        out["star"] = star_path(mj, ctx)
     if only in (None, "slarge"):
         out["s_largest"] = slarge_path(mj, ctx)
     if only in (None, "skew"):

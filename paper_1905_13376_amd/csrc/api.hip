@@ -387,8 +387,8 @@ struct DenseLayout {                  // the linear join with direct-indexed tab
     uint16_t* deg16;                  // [c_domain] the same, cut to 16 bits
     unsigned long long* w;            // [b_domain] W[b]
     uint16_t* w16;                    // [b_domain] W[b], or 0xFFFF where W[b] >= 0xFFFF (then read w)
-    uint32_t* err;                    // [0]: a key out of its bound; [1]: unused;
-                                      // [2]: some deg[c] >= 2^16
+    uint32_t* err;                    // [0]: a key out of its bound; [1]: the same for S, where the
+                                      // small join sums W; [2]: some deg[c] >= 2^16
     uint32_t c_bits, c_shift, b_bits, b_shift, a_bits, a_shift;
     BucketItems Tsplit, Ssplit, Rsplit;  // skew split of each partition's ranges
     unsigned long long* rows;         // scratch rows of the split ranges (shared by the three sums)

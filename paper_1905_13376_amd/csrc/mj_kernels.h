@@ -242,28 +242,6 @@ __device__ __forceinline__ void nt_lookup4(const uint32_t* ldir, const uint32_t*
     }
 }
 
-// Lookup in a bucketed multiplicity table; 0 when absent.
-__device__ __forceinline__ uint32_t dtab_lookup(const DirEntry* __restrict__ dir,
-                                                const uint2* __restrict__ pool,
-                                                uint32_t key, uint32_t bkt_seed,
-                                                uint32_t bkt_bits, uint32_t slot_seed) {
-    const uint32_t j = top_bits(mix32(key, bkt_seed), bkt_bits);
-    const DirEntry e = dir[j];
-    if (key == EMPTY_KEY) return e.special;
-    const uint32_t mask = (1u << e.log2cap) - 1u;
-    uint32_t s = slot_hash(key, slot_seed) & mask;
-    const uint2* base = pool + e.offset;
-    while (true) {
-        uint2 kv = base[s];
-        if (kv.x == key) return kv.y;
-        if (kv.x == EMPTY_KEY) return 0u;
-        s = (s + 1u) & mask;
-    }
-}
-
-// Four independent lookups: the directory loads, then the first slot loads
-// are issued together so that four table reads are in flight per lane;
-// only keys that collide walk further.
 // The rest of an open-addressing probe whose first slot `s` has been read
 // as `v`: walk on until the key or an empty slot; `none` when absent.
 // (A function of scalars, so that callers holding several probes in
@@ -277,6 +255,10 @@ __device__ __forceinline__ uint32_t probe_from(const uint2* __restrict__ base, u
     return v.x == key ? v.y : none;
 }
 
+// Four independent lookups in a bucketed multiplicity table (0 when absent):
+// the directory loads, then the first slot loads are issued together so
+// that four table reads are in flight per lane; only keys that collide walk
+// further.
 __device__ __forceinline__ void dtab_lookup4(const DirEntry* __restrict__ dir,
                                              const uint2* __restrict__ pool,
                                              const uint32_t (&key)[4], const bool (&live)[4],
